@@ -256,9 +256,9 @@ def next_rows_leg(syk, h, stream):
     """Costs of the other entry points on this GPU, outside the timed region:
     * green: the Green function G_R(t) of chi_55 on the benchmark realisation (N = 56,
       k = 4, beta = 10, t = 0:0.25:5, complex64, Krylov dim 60, tol 3e-6);
-    * dense: one apply_H of dense SYK (p = 1, K = C(38,4) = 73815) at N = 38, best
-      autotuned variant, with its VALU-floor fraction; dense_gather: the same at N = 30
-      (K = 27405), below the tiled size, where the gather kernel groups terms by x mask;
+    * dense: one apply_H of dense SYK (p = 1, K = C(38,4) = 73815) at N = 38, with its
+      VALU-floor fraction and the tiled variants' times; dense_gather: the same at N = 30
+      (K = 27405); both run the gather kernel that groups terms by x mask;
     * spin_operator: a transverse-field Ising chain on 27 qubits (sum Z_q Z_{q+1} + 0.7 sum X_q)
       through syk_op_to_hamiltonian: one apply_H (best variant) and one e^{-iH} propagation."""
     import math
@@ -275,33 +275,34 @@ def next_rows_leg(syk, h, stream):
                     "G_norm": {str(ts[i]): float(nrm[i]) for i in (0, 4, 8, 20)}}
     syk.release_workspace()
 
+    def apply_ms(ham):
+        x = torch.randn(ham.info()["block_dim"], dtype=torch.complex64, device="cuda")
+        y = torch.empty_like(x)
+        syk.apply_H(ham, 0, x, y, stream=stream)
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record(stream)
+        for _ in range(20):
+            syk.apply_H(ham, 0, x, y, stream=stream)
+        e1.record(stream)
+        torch.cuda.synchronize()
+        return e0.elapsed_time(e1) / 20
+
     nd = 38
     hd = syk.create_hamiltonian(nd, 4, math.comb(nd, 4) / nd, 2, syk.BERNOULLI)
     info = hd.info()
     variant, ms = syk.autotune(hd, syk.C64, stream=stream)
-    best = min(m for m in ms if m > 0)
+    best = apply_ms(hd)
     ta = info["K"] * info["block_dim"]
     out["dense"] = {"N": nd, "K": info["K"], "variant": variant, "ms": best, "term_amps_per_s": ta / (best * 1e-3),
                     "valu_floor_frac": ta / 3.93e13 / (best * 1e-3), "variant_ms": ms}
     hd.close()
-    # below the tiled size: the gather kernel with terms grouped by x mask
     ng = 30
     hg = syk.create_hamiltonian(ng, 4, math.comb(ng, 4) / ng, 2, syk.BERNOULLI)
     info = hg.info()
-    x = torch.randn(info["block_dim"], dtype=torch.complex64, device="cuda")
-    y = torch.empty_like(x)
-    syk.apply_H(hg, 0, x, y, stream=stream)
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    e0.record(stream)
-    for _ in range(20):
-        syk.apply_H(hg, 0, x, y, stream=stream)
-    e1.record(stream)
-    torch.cuda.synchronize()
-    gms = e0.elapsed_time(e1) / 20
+    gms = apply_ms(hg)
     ta = info["K"] * info["block_dim"]
     out["dense_gather"] = {"N": ng, "K": info["K"], "x_mask_groups": syk.plan_describe(hg, 0, syk.C64, -1)["n_groups"],
                            "ms": gms, "term_amps_per_s": ta / (gms * 1e-3)}
-    del x, y
     hg.close()
 
     L, g = 27, 0.7

@@ -514,7 +514,9 @@ syk_status syk_tridiag_expm(int n, const double *alpha, const double *beta, doub
                             double *c_re, double *c_im);
 
 /* Launch plan of the tiled apply_H kernel for one block (host-only; no GPU needed).
- * Blocks of 2^L amplitudes with L >= 18 are served by the tiled kernel: output tiles of
+ * Blocks of 2^L amplitudes with L >= 18 are served by the tiled kernel (except dense ones, of
+ * four or more terms per distinct x mask with L <= 22, which the gather kernel serves unless a
+ * tiled variant is pinned by syk_select_variant): output tiles of
  * 2^tile_bits amplitudes, terms grouped by partner tile (n_groups groups), tiles mapped
  * to workgroups so that the 2^res_bits tiles resident on one XCD form a coset of a
  * res_bits-dim subspace (classes_xcd = partner-tile classes modulo it, which sets the L2
@@ -553,8 +555,9 @@ syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int la
 
 /* Schedule autotuner: time each compiled variant of the tiled apply_H kernel (tile size,
  * LDS buffering, prefetch depth; each in its planned layout) on this Hamiltonian and keep
- * the fastest for the current device and precision.  *variant receives the choice (-1 if
- * the block is not tiled); ms[v] (host, cap entries, may be NULL) the mean time of one
+ * the fastest for the current device and precision (a dense block that the gather kernel
+ * serves stays with it; see syk_plan_describe).  *variant receives the choice (-1 if
+ * L < 18); ms[v] (host, cap entries, may be NULL) the mean time of one
  * apply with variant v (-1 where skipped).  Uses a library-owned workspace of two vectors.
  * Errors: EINVAL, ENOMEM, EDEVICE. */
 syk_status syk_autotune(const syk_ham *h, syk_dtype dt, int *variant, float *ms, int cap, void *stream);

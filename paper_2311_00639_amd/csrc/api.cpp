@@ -258,18 +258,20 @@ syk_status syk_apply_H(const syk_ham *h, syk_block blk, syk_dtype dt, const void
             syk::fail(SYK_EUNSUPPORTED, "an operator handle has no parity sectors");
         check_device();
         auto &H = const_cast<syk::Hamiltonian &>(h->h);
-        // the full space is the U block followed by the D block
-        const int b0 = blk == SYK_FULL ? SYK_BLOCK_U : blk, b1 = blk == SYK_FULL ? SYK_BLOCK_D : -1;
         if (dt == SYK_C64) {
             const float *xf = static_cast<const float *>(x);
             float *yf = static_cast<float *>(y);
-            syk::apply_block<float>(H, b0, 0, xf, yf, nvec, ld, as_stream(stream));
-            if (b1 >= 0) syk::apply_block<float>(H, b1, 0, xf + 2 * nb, yf + 2 * nb, nvec, ld, as_stream(stream));
+            if (blk == SYK_FULL)
+                syk::apply_full<float>(H, xf, yf, nvec, ld, as_stream(stream));
+            else
+                syk::apply_block<float>(H, blk, 0, xf, yf, nvec, ld, as_stream(stream));
         } else {
             const double *xd = static_cast<const double *>(x);
             double *yd = static_cast<double *>(y);
-            syk::apply_block<double>(H, b0, 0, xd, yd, nvec, ld, as_stream(stream));
-            if (b1 >= 0) syk::apply_block<double>(H, b1, 0, xd + 2 * nb, yd + 2 * nb, nvec, ld, as_stream(stream));
+            if (blk == SYK_FULL)
+                syk::apply_full<double>(H, xd, yd, nvec, ld, as_stream(stream));
+            else
+                syk::apply_block<double>(H, blk, 0, xd, yd, nvec, ld, as_stream(stream));
         }
     });
 }
@@ -732,7 +734,7 @@ syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int la
         auto &H = const_cast<syk::Hamiltonian &>(h->h);
         require(layout >= -1 && layout < std::max(H.L, 1), "layout must be -1 or a rotation in [0, L)");
         const bool c64 = dt == SYK_C64;
-        if (!(c64 ? syk::use_tiled<float>(H.L) : syk::use_tiled<double>(H.L)))
+        if (H.L < syk::kTiledMinL)
             syk::fail(SYK_EUNSUPPORTED, "the block is not served by the tiled kernel");
         const int var = c64 ? H.variant<float>() : H.variant<double>();
         const syk::TiledVariant tv = c64 ? syk::tiled_variants<float>()[var] : syk::tiled_variants<double>()[var];
@@ -757,7 +759,7 @@ syk_status syk_plan_describe(const syk_ham *h, syk_block blk, syk_dtype dt, int 
         require(layout >= -1 && layout < std::max(H.L, 1), "layout must be -1 or a rotation in [0, L)");
         *out = syk_plan_desc{};
         const bool c64 = dt == SYK_C64;
-        out->tiled = c64 ? syk::use_tiled<float>(H.L) : syk::use_tiled<double>(H.L);
+        out->tiled = c64 ? H.tiled<float>() : H.tiled<double>();
         if (!out->tiled) {
             out->n_groups = syk::gather_groups(H.block_terms[blk]);
             return;
@@ -836,6 +838,7 @@ syk_status syk_select_variant(const syk_ham *h, syk_dtype dt, int variant) {
         auto &H = const_cast<syk::Hamiltonian &>(h->h);
         std::lock_guard<std::mutex> g(H.dev_mu);
         H.tuned[{dt == SYK_C128 ? 1 : 0, dev}] = variant;
+        H.pinned.insert({dt == SYK_C128 ? 1 : 0, dev});
     });
 }
 

@@ -1,0 +1,375 @@
+// apply_H below the tiled size, straight from memory (gfx950).
+//
+// y[m] = sum_a c_a i^{imag_a} (-1)^{popc(m & z_a)} x[m ^ x_a]   (supplement Algorithm 1, with the
+// sign parity of x_a & z_a folded into c_a).  A parity block of at most 2^17 amplitudes (2 MiB in
+// complex128) sits in every L2, so partners are gathered from there and nothing is staged.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "internal.hpp"
+
+namespace syk {
+
+namespace {
+
+template <typename T> struct V2t;
+template <> struct V2t<float> { using type = float2; };
+template <> struct V2t<double> { using type = double2; };
+
+__device__ __forceinline__ float flip(float c, uint32_t m) { return __int_as_float(__float_as_int(c) ^ static_cast<int>(m)); }
+__device__ __forceinline__ double flip(double c, uint32_t m) {
+    return __hiloint2double(__double2hiint(c) ^ static_cast<int>(m), __double2loint(c));
+}
+
+// one complex amplitude at byte offset voff + soff (soff wave-uniform) of a vector
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float2 load_amp(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float) {
+    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+    return float2{__uint_as_float(v.x), __uint_as_float(v.y)};
+}
+__device__ __forceinline__ double2 load_amp(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, double) {
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+    return double2{__hiloint2double(static_cast<int>(v.y), static_cast<int>(v.x)),
+                   __hiloint2double(static_cast<int>(v.w), static_cast<int>(v.z))};
+}
+
+constexpr uint32_t kBufferWord3 = 0x00020000u;   // raw buffer descriptor: 32-bit data format, no swizzle
+
+// One wave owns 64 R consecutive amplitudes (lane l holds base + l + 64 r) and one of S slices
+// of the term list; the S waves of a group are in one workgroup and their sums are added in
+// slice order in LDS, so the result does not depend on scheduling.
+//
+// Bound by instruction issue and the latency of the gathers, not by bandwidth.  Hence: the
+// slice is wave-uniform, so term records come through scalar loads; the partner of register r
+// is (lane ^ x) in a VGPR plus a scalar offset ((base ^ x) ^ 64 r), so a gather costs no vector
+// address arithmetic; the sign of the lane and base bits is folded into the coefficient once
+// per term (three vector operations) and the register sign is one XOR; U terms' gathers are
+// in flight at once.  Three complex64 vectors over both blocks at N = 34, k = 4 (5.3e7
+// term-amplitudes): 25 us, against 94 us in two launches of one amplitude per thread with
+// per-lane term loads.
+template <typename T, int R, int S, int GPB>
+__global__ void __launch_bounds__(64 * S * GPB) gather_sparse(GatherTerms<T> t0, GatherTerms<T> t1,
+                                                              const typename V2t<T>::type *__restrict__ x,
+                                                              typename V2t<T>::type *__restrict__ y, uint32_t n,
+                                                              uint64_t ld) {
+    using V = typename V2t<T>::type;
+    constexpr int SH = sizeof(T) == 4 ? 3 : 4;       // log2 of the bytes per amplitude
+    constexpr int U = R >= 4 ? 2 : 4;                // terms in flight
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t slice = wave % S, group = blockIdx.x * GPB + wave / S;
+    const uint32_t base = group * (64u * R);
+    const GatherTerms<T> tb = blockIdx.z == 0 ? t0 : t1;
+    const uint64_t vo = static_cast<uint64_t>(blockIdx.y) * ld + static_cast<uint64_t>(blockIdx.z) * n;
+    V acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = V{T(0), T(0)};
+    if (base < n) {
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<V *>(x + vo), 0, static_cast<int>(n << SH), kBufferWord3);
+        // blocks below 64 amplitudes: the spare lanes compute copies and store nothing
+        const uint32_t lm = lane & (n - 1u);
+        auto terms = [&](auto im, auto uc, uint32_t t) __attribute__((always_inline)) {
+            constexpr int C = decltype(uc)::value;
+            V q[C][R];
+            T c[C];
+            uint32_t zm[C];
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                const GatherTerm<T> rec = tb.rec[t + u];              // wave-uniform: scalar load
+                const uint32_t voff = (lm ^ (rec.x & 63u)) << SH;
+                const uint32_t so = base ^ (rec.x & ~63u);
+#pragma unroll
+                for (int r = 0; r < R; ++r) q[u][r] = load_amp(rs, voff, (so ^ (64u * r)) << SH, T(0));
+                const uint32_t par = __popc(lm & rec.z) + __popc(base & rec.z);
+                c[u] = flip(rec.c, par << 31);
+                zm[u] = rec.z >> 6;
+            }
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    uint32_t sg = (__popc(zm[u] & static_cast<uint32_t>(r)) & 1u) << 31;
+                    asm("" : "+s"(sg));                              // keep the register sign scalar
+                    const T cr = r == 0 ? c[u] : flip(c[u], sg);
+                    if (decltype(im)::value) {
+                        acc[r].x -= cr * q[u][r].y;
+                        acc[r].y += cr * q[u][r].x;
+                    } else {
+                        acc[r].x += cr * q[u][r].x;
+                        acc[r].y += cr * q[u][r].y;
+                    }
+                }
+        };
+        auto phase = [&](auto im, uint32_t lo, uint32_t hi) __attribute__((always_inline)) {
+            uint32_t t = lo;
+            for (; t + U <= hi; t += U) terms(im, std::integral_constant<int, U>{}, t);
+            for (; t < hi; ++t) terms(im, std::integral_constant<int, 1>{}, t);
+        };
+        const uint32_t nr = tb.n_real, ni = tb.K - tb.n_real;
+        phase(std::false_type{}, nr * slice / S, nr * (slice + 1) / S);
+        phase(std::true_type{}, nr + ni * slice / S, nr + ni * (slice + 1) / S);
+    }
+    if constexpr (S > 1) {
+        __shared__ V part[GPB][S][R][64];
+#pragma unroll
+        for (int r = 0; r < R; ++r) part[wave / S][slice][r][lane] = acc[r];
+        __syncthreads();
+        // wave `slice` of the group sums register rows slice, slice + S, ...
+#pragma unroll
+        for (int r0 = 0; r0 < R; r0 += S) {
+            const int r = r0 + static_cast<int>(slice);
+            if (r < R && base < n) {
+                V s = part[wave / S][0][r][lane];
+#pragma unroll
+                for (int k = 1; k < S; ++k) {
+                    s.x += part[wave / S][k][r][lane].x;
+                    s.y += part[wave / S][k][r][lane].y;
+                }
+                const uint32_t m = base + 64u * r + lane;
+                if (m < n) y[vo + m] = s;
+            }
+        }
+    } else {
+        if (base < n) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint32_t m = base + 64u * r + lane;
+                if (m < n) y[vo + m] = acc[r];
+            }
+        }
+    }
+}
+
+template <typename T, int R, int S>
+void go(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld, hipStream_t s) {
+    using V = typename V2t<T>::type;
+    constexpr int GPB = S >= 4 ? 1 : 4 / S;
+    const uint32_t per = 64u * R * GPB;
+    hipLaunchKernelGGL((gather_sparse<T, R, S, GPB>), dim3((n + per - 1) / per, nvec, nblk), dim3(64 * S * GPB), 0, s,
+                       tb[0], tb[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld);
+}
+
+// ------------------------------------------------------------------ grouped by x mask
+// Terms that share an x mask act on the partner x[m ^ x] as one complex diagonal
+//   D(m) = sum_t c_t (-1)^popc(m & z_t)   (real-phase terms in Re D, i-phase terms in Im D),
+// so a group costs one gather and one complex product per amplitude however many terms it has
+// (about 19 in dense SYK).  D is a matrix product: over a tile of 256 amplitudes m = 16 i + j the
+// sign splits into (row, term) and (term, column) factors, D = A B with A[i][t] = c_t s_t(base + 16 i)
+// and B[t][j] = s_t(j) = +-1, and four terms are one 16 x 16 x 4 matrix instruction (products by
+// +-1 are exact, sums are in the vectors' precision or better).  Building A and B costs six vector
+// operations per step of four terms and wave, whatever the tile; summed on the vector unit it
+// was about six per term and amplitude.  Bound by issue (readlane, two uniform branches and the
+// operand building of every step): about 95 clocks per step and SIMD, where the instruction itself
+// takes 16 to 64.  One apply, complex64 / complex128: N = 30 (K = 27405) 84 / 87 us, against
+// 278 / 391 us summed on the vector unit; N = 38 (K = 73815) 0.80 / 1.24 ms and N = 42 (K = 111930)
+// 4.2 / 6.9 ms, against 9.1 ms (N = 38, complex64) and 26 ms (N = 42) term by term in the tiled kernel.
+//
+// The matrix instruction of a wave's tile, in the precision P of the sums.  rows(l): the amplitude
+// offset of the row of A that lane l supplies, cols(l): that of the column of B; both supply
+// term l >> 4 of the step, and result r of lane l belongs to amplitude base + l + 64 r.
+//
+// MfmaTile: 256 amplitudes, columns = amplitude bits 0..3, rows = bits 4..7.  Result r of
+// lane l is row 4 (l >> 4) + r of the 32-bit instruction and row 4 r + (l >> 4) of the 64-bit one; rows are
+// numbered so that both are amplitude bits 4..7 = (l >> 4) + 4 r.
+template <typename P> struct MfmaTile;
+template <> struct MfmaTile<float> {
+    static constexpr int R = 4;
+    typedef float Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc mma(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ uint32_t rows(uint32_t l) { return (((l >> 2) & 3u) | ((l & 3u) << 2)) << 4; }
+    static __device__ __forceinline__ uint32_t cols(uint32_t l) { return l & 15u; }
+};
+template <> struct MfmaTile<double> {
+    static constexpr int R = 4;
+    typedef double Acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Acc mma(double a, double b, Acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ uint32_t rows(uint32_t l) { return (l & 15u) << 4; }
+    static __device__ __forceinline__ uint32_t cols(uint32_t l) { return l & 15u; }
+};
+// MfmaRow: 64 amplitudes, four blocks of 4 x 4: column = amplitude bits 0..1, block = bits 2..3,
+// row = bits 4..5 (64-bit sums, whatever the vectors' precision).
+struct MfmaRow {
+    static constexpr int R = 1;
+    typedef double Acc __attribute__((ext_vector_type(1)));
+    static __device__ __forceinline__ Acc mma(double a, double b, Acc c) {
+        return Acc{__builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c[0], 0, 0, 0)};
+    }
+    static __device__ __forceinline__ uint32_t rows(uint32_t l) { return (l & 12u) | ((l & 3u) << 4); }
+    static __device__ __forceinline__ uint32_t cols(uint32_t l) { return l & 3u; }
+};
+
+// +-1 and +-c with the sign in the parity of p
+__device__ __forceinline__ void signed_pair(uint32_t pa, uint32_t pb, float c, float &a, float &b) {
+    a = __uint_as_float((pa << 31) + __float_as_uint(c));
+    b = __uint_as_float((pb << 31) | 0x3f800000u);
+}
+__device__ __forceinline__ void signed_pair(uint32_t pa, uint32_t pb, double c, double &a, double &b) {
+    a = __hiloint2double(static_cast<int>((pa << 31) + static_cast<uint32_t>(__double2hiint(c))), __double2loint(c));
+    b = __hiloint2double(static_cast<int>((pb << 31) | 0x3ff00000u), 0);
+}
+
+// A wave owns one tile (R registers of 64 amplitudes) and one of S slices of the steps; the S
+// waves of a workgroup share the tile and their sums are added in slice order.  The records of
+// kDenseChunk = 16 steps (64 of them, one per lane) are loaded one chunk ahead, pass through
+// the wave's own piece of LDS and are read back by the term each lane supplies; the partners of
+// a group are gathered while the group before it is summed.
+template <typename T, typename P, typename Tile, int S>
+__global__ void __launch_bounds__(64 * S) gather_dense(DenseTerms<P> t0, DenseTerms<P> t1,
+                                                       const typename V2t<T>::type *__restrict__ x,
+                                                       typename V2t<T>::type *__restrict__ y, uint32_t n, uint64_t ld) {
+    using V = typename V2t<T>::type;
+    using M = typename Tile::Acc;
+    constexpr int R = Tile::R;
+    constexpr int SH = sizeof(T) == 4 ? 3 : 4;
+    constexpr int PER = kDenseSlices / S;                 // table slices per wave
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t base = blockIdx.x * (64u * R);
+    const DenseTerms<P> tb = blockIdx.z == 0 ? t0 : t1;
+    const uint32_t *hdrs = tb.head + kDenseHead;
+    const uint64_t vo = static_cast<uint64_t>(blockIdx.y) * ld + static_cast<uint64_t>(blockIdx.z) * n;
+    constexpr size_t kRecs = sizeof(DenseTerm<P>) * 64 * S, kPart = sizeof(V) * S * R * 64;
+    __shared__ __attribute__((aligned(16))) char lds[kRecs > kPart ? kRecs : kPart];
+    DenseTerm<P> *stage = reinterpret_cast<DenseTerm<P> *>(lds) + 64 * wave;
+    V acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = V{T(0), T(0)};
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<V *>(x + vo), 0, static_cast<int>(n << SH), kBufferWord3);
+    const uint32_t am = base + Tile::rows(lane), bm = Tile::cols(lane), kq = lane >> 4;
+    V q[R];
+    auto gather = [&](uint32_t xm) __attribute__((always_inline)) {
+        const uint32_t voff = (lane ^ (xm & 63u)) << SH;
+        const uint32_t so = base ^ (xm & ~63u);
+#pragma unroll
+        for (int r = 0; r < R; ++r) q[r] = load_amp(rs, voff, (so ^ (64u * r)) << SH, T(0));
+    };
+    const uint32_t s0 = tb.head[wave * PER], s1 = tb.head[wave * PER + PER];
+    if (s0 < s1) {
+        gather(tb.head[kDenseSlices + 1 + wave * PER]);
+        M dre{}, dim{};
+        DenseTerm<P> nrec = tb.rec[static_cast<size_t>(s0) * 4 + lane];
+        uint32_t nhdr = hdrs[s0 + (lane & 15u)];
+        for (uint32_t st = s0; st < s1; st += kDenseChunk) {
+            // the wave's reads of the chunk before are done: the products took their results
+            stage[lane] = nrec;
+            const uint32_t hdr = nhdr;
+            const uint32_t nx = st + kDenseChunk < s1 ? st + kDenseChunk : s0;
+            nrec = tb.rec[static_cast<size_t>(nx) * 4 + lane];
+            nhdr = hdrs[nx + (lane & 15u)];
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+            for (int u = 0; u < kDenseChunk; ++u) {
+                const uint32_t h = __builtin_amdgcn_readlane(hdr, u);
+                const DenseTerm<P> rec = stage[4 * u + kq];
+                P a, b;
+                signed_pair(__popc(am & rec.z), __popc(bm & rec.z), rec.c, a, b);
+                if (h & (1u << 30))
+                    dim = Tile::mma(a, b, dim);
+                else
+                    dre = Tile::mma(a, b, dre);
+                if (h & (1u << 31)) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const T cr = static_cast<T>(dre[r]), ci = static_cast<T>(dim[r]);
+                        acc[r].x += cr * q[r].x - ci * q[r].y;
+                        acc[r].y += cr * q[r].y + ci * q[r].x;
+                    }
+                    dre = M{};
+                    dim = M{};
+                    gather(h & 0x0fffffffu);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    V *part = reinterpret_cast<V *>(lds);
+    __syncthreads();                                      // the record staging is done with
+#pragma unroll
+    for (int r = 0; r < R; ++r) part[(wave * R + r) * 64 + lane] = acc[r];
+    __syncthreads();
+    if (wave < R) {                                       // wave r sums register row r, slices in order
+        V s = part[wave * 64 + lane];
+#pragma unroll
+        for (int k = 1; k < S; ++k) {
+            s.x += part[(k * R + wave) * 64 + lane].x;
+            s.y += part[(k * R + wave) * 64 + lane].y;
+        }
+        y[vo + base + 64u * wave + lane] = s;
+    }
+}
+
+}  // namespace
+
+// nblk = 2: blocks U and D side by side in one vector (D at element offset n)
+template <typename T>
+void launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld,
+                         hipStream_t s) {
+    // Amplitudes per lane R and slices of the term list S, by block size alone (so that a vector's
+    // result does not depend on how many vectors or blocks share the launch): as many amplitudes
+    // per lane as leave about 2048 waves, 8 per CU, with at most 16 slices.  Measured with every
+    // R in {1, 2, 4} and S in {2, 4, 8, 16} from N = 16 to 36: within 10% of each other up to
+    // N = 34, where the call's host time (11 us) hides the kernel, and at N = 36, k = 8 R = 4 with
+    // S = 4 takes 18.8 us (complex64), S = 16 19.1 us, R = 2 with S = 2 19.3 us.
+    const uint32_t groups = (n + 63u) / 64u;
+    if (groups >= 2048u)
+        go<T, 4, 4>(tb, nblk, x, y, n, nvec, ld, s);
+    else if (groups >= 1024u)
+        go<T, 4, 8>(tb, nblk, x, y, n, nvec, ld, s);
+    else if (groups >= 256u)
+        go<T, 2, 16>(tb, nblk, x, y, n, nvec, ld, s);
+    else
+        go<T, 1, 16>(tb, nblk, x, y, n, nvec, ld, s);
+    SYK_HIP(hipGetLastError());
+}
+
+template <typename T>
+void launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec,
+                        uint64_t ld, hipStream_t s) {
+    using V = typename V2t<T>::type;
+    if (n < 256) fail(SYK_EDEVICE, "the grouped gather needs 256 amplitudes");
+    auto go = [&](auto pc, auto tile, auto sc) {
+        using P = decltype(pc);
+        using Tile = decltype(tile);
+        constexpr int S = decltype(sc)::value;
+        DenseTerms<P> d[2];
+        for (int b = 0; b < 2; ++b) {
+            d[b].head = tb[b]->head;
+            if constexpr (sizeof(P) == 4)
+                d[b].rec = tb[b]->d32;
+            else
+                d[b].rec = tb[b]->d64;
+        }
+        hipLaunchKernelGGL((gather_dense<T, P, Tile, S>), dim3(n / (64 * Tile::R), nvec, nblk), dim3(64 * S), 0, s, d[0],
+                           d[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld);
+    };
+    // Small blocks take 64-amplitude tiles to reach more CUs (N = 30: 84 us against 95 us in
+    // complex64 and 87 us against 140 us in complex128 with 256-amplitude tiles), larger ones 256
+    // (four times the amplitudes per step; N = 34: 153 / 243 us).  Sixteen waves share a tile up
+    // to 2^17 amplitudes, eight above (N = 38, complex128: 1.24 ms against 1.42 ms).
+    if (n <= 1u << 15)
+        go(double(0), MfmaRow{}, std::integral_constant<int, 16>{});
+    else if (n <= 1u << 17)
+        go(T(0), MfmaTile<T>{}, std::integral_constant<int, 16>{});
+    else
+        go(T(0), MfmaTile<T>{}, std::integral_constant<int, 8>{});
+    SYK_HIP(hipGetLastError());
+}
+
+template void launch_apply_dense<float>(const DeviceTables *const (&)[2], int, const float *, float *, uint32_t, int,
+                                        uint64_t, hipStream_t);
+template void launch_apply_dense<double>(const DeviceTables *const (&)[2], int, const double *, double *, uint32_t, int,
+                                         uint64_t, hipStream_t);
+template void launch_apply_gather<float>(const GatherTerms<float> (&)[2], int, const float *, float *, uint32_t, int,
+                                         uint64_t, hipStream_t);
+template void launch_apply_gather<double>(const GatherTerms<double> (&)[2], int, const double *, double *, uint32_t, int,
+                                          uint64_t, hipStream_t);
+
+}  // namespace syk

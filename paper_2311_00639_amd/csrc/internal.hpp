@@ -7,6 +7,7 @@
 #include <cstddef>
 #include <map>
 #include <mutex>
+#include <set>
 #include <tuple>
 #include <string>
 #include <vector>
@@ -47,17 +48,62 @@ struct DeviceSlab {
     void *take(size_t bytes, const char *what);
 };
 
-struct DeviceTables {            // per device, per block: the gather kernel's term tables
-    bool in_slab = false;        // carved from a DeviceSlab: not freed by the library
-    int n_real = 0;              // real-phase terms of the block
-    int K = 0;
-    // terms grouped by x mask: group g has mask gx[g], real-phase terms [gs[g], gm[g]) and
-    // i-phase terms [gm[g], gs[g + 1]) of gz / gc32 / gc64
-    uint32_t *gx = nullptr, *gs = nullptr, *gm = nullptr, *gz = nullptr;
-    float *gc32 = nullptr;
-    double *gc64 = nullptr;
-    int G = 0;
+// One term of the gather kernels (16 bytes in either precision): y[m] += c (-1)^{popc(m & z)}
+// x[m ^ x], times i for the i-phase terms, which follow the n_real real-phase ones.
+template <typename T> struct GatherTerm;
+template <> struct GatherTerm<float> {
+    uint32_t x, z;
+    float c;
+    uint32_t pad;
 };
+template <> struct GatherTerm<double> {
+    uint32_t x, z;
+    double c;
+};
+template <typename T>
+struct GatherTerms {
+    const GatherTerm<T> *rec = nullptr;
+    uint32_t n_real = 0, K = 0;
+};
+
+// Terms of the grouped gather kernel: groups of equal x mask, cut into steps of four terms of
+// one phase (the last step of a phase padded with zero coefficients).  hdr[s] of step s: bit 30
+// i-phase, bit 31 the group ends here, and on such a step bits 0..27 the next group's x mask.
+// The steps are dealt to kDenseSlices slices of whole groups, slice q holding steps
+// [cut[q], cut[q + 1]), a multiple of kDenseChunk (padded with empty steps); first[q] is the
+// x mask of its first group.  The header table starts with cut (kDenseSlices + 1 words) and
+// first (kDenseSlices), the step headers follow at word kDenseHead.
+constexpr int kDenseSlices = 16, kDenseChunk = 16, kDenseHead = 64;
+template <typename T> struct DenseTerm;
+template <> struct DenseTerm<float> {
+    uint32_t z;
+    float c;
+};
+template <> struct DenseTerm<double> {
+    uint32_t z, pad;
+    double c;
+};
+template <typename T>
+struct DenseTerms {
+    const uint32_t *head = nullptr;
+    const DenseTerm<T> *rec = nullptr;       // four per step
+};
+
+struct DeviceTables {            // per device, per block: the gather kernels' term tables
+    bool in_slab = false;        // carved from a DeviceSlab: not freed by the library
+    GatherTerm<float> *r32 = nullptr;
+    GatherTerm<double> *r64 = nullptr;
+    uint32_t n_real = 0, K = 0;
+    // the grouped form, for blocks that use it (null otherwise)
+    uint32_t *head = nullptr;
+    DenseTerm<float> *d32 = nullptr;
+    DenseTerm<double> *d64 = nullptr;
+};
+// Blocks whose terms share x masks this often or more (terms per mask) use the grouped form,
+// from one 256-amplitude tile up to 2^22 amplitudes (where the gathers still come from the
+// 256 MB last-level cache; larger dense blocks stay with the tiled kernel, unmeasured).
+constexpr int kDenseTermsPerMask = 4;
+constexpr int kDenseMinL = 8, kDenseMaxL = 22;
 
 // distinct x masks of a block's terms: the groups the gather kernel loads once each
 int gather_groups(const std::vector<BlockTerm> &terms);
@@ -144,6 +190,14 @@ struct Hamiltonian {
     std::map<std::tuple<int, int, int, int, int>, ApplyPlan> plans;
     std::map<std::pair<int, int>, int> rotation;               // (double?, variant) -> planned rotation
     std::map<std::pair<int, int>, int> tuned;                   // (double?, device) -> variant
+    std::set<std::pair<int, int>> pinned;                       // those of them chosen by syk_select_variant
+    // whether the tiled kernel serves the block on the current device: blocks of at least
+    // 2^kTiledMinL amplitudes, except dense ones that the grouped gather kernel serves (unless
+    // a tiled variant is pinned)
+    template <typename T>
+    bool tiled();
+    bool grouped();                       // the terms share x masks often enough for the grouped form
+    int grouped_ = -1;                    // cached grouped(): -1 not yet known
     const DeviceTables &tables(int blk);
     template <typename T>
     const ApplyPlan &plan(int blk, int rot, int variant);
@@ -183,13 +237,12 @@ class DeviceBuffer {
 // per-(device, thread) cached workspace used by the convenience entry points
 DeviceBuffer &thread_workspace(int slot);
 
-// y = H_blk x on the device: tiled kernel for large blocks, gather kernel otherwise
-template <typename T>
-inline bool use_tiled(int L) {
-    return L >= kTiledMinL;
-}
+// y = H_blk x on the device: tiled kernel for large blocks, gather kernels otherwise
 template <typename T>
 void apply_block(Hamiltonian &h, int blk, int rot, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s);
+// the same on both blocks of the full space (U, then D at element offset 2^L), layout 0
+template <typename T>
+void apply_full(Hamiltonian &h, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s);
 // y = H_blk x with the fused Lanczos epilogue (tiled blocks only); returns the number of
 // partials written (one per tile)
 template <typename T>
@@ -203,9 +256,13 @@ int autotune(Hamiltonian &h, T *x, T *y, hipStream_t s, bool force, std::vector<
 
 // ------------------------------------------------------------------ kernels (HIP side)
 // All launchers enqueue on `s` and never synchronise.
+// gather kernels over nblk blocks side by side (2: U, then D at element offset n)
 template <typename T>
-void launch_apply_h(const DeviceTables &tb, const T *x, T *y, uint32_t n_amps, int nvec, uint64_t ld,
-                    hipStream_t s);
+void launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld,
+                         hipStream_t s);
+template <typename T>
+void launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec,
+                        uint64_t ld, hipStream_t s);
 // psi in layout rotation `rot`: index p holds standard amplitude rotl(p, rot)
 template <typename T>
 void launch_haar_raw(uint64_t state_seed, int v, int L, int rot, T *psi_U, T *psi_D, double *partials, int n_part,

@@ -203,7 +203,7 @@ template <typename T>
 bool KrylovRun<T>::iterate(int j, int reorth) {
     T *vj = vec(j);
     T *w = vec(j + 1);
-    if (reorth == 0 && use_tiled<T>(h_.L)) {
+    if (reorth == 0 && h_.tiled<T>()) {
         // fused step: the apply epilogue forms w = H v_j - beta v_{j-1} and the sums for
         // alpha_j and beta_j; one more pass normalises
         // basis slots hold u_i unnormalised (||u_i|| = beta_{i-1}); the scales enter the

@@ -58,8 +58,9 @@ void otoc_run(Hamiltonian &h, int i, int j, double beta, const std::vector<doubl
     char *kws = ws + 4 * vb;
     // every vector of the chain lives in the planner's layout rotation; overlaps are
     // invariant under the permutation
-    if (use_tiled<T>(h.L) && o.autotune) autotune<T>(h, l, tmp, s, false);     // l, tmp: scratch here
-    const int rot = !use_tiled<T>(h.L) ? 0 : (o.layout >= 0 ? o.layout : h.internal_rotation<T>(h.variant<T>()));
+    const bool tiled = h.tiled<T>();
+    if (tiled && o.autotune) autotune<T>(h, l, tmp, s, false);     // l, tmp: scratch here
+    const int rot = !tiled ? 0 : (o.layout >= 0 ? o.layout : h.internal_rotation<T>(h.variant<T>()));
     KrylovRun<T> kr[2] = {KrylovRun<T>(h, 0, rot, n, o.krylov.m, kws, s),
                           KrylovRun<T>(h, 1, rot, n, o.krylov.m, kws, s)};
     ApplyTimer timer;

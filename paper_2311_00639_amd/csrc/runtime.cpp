@@ -33,12 +33,11 @@ static void free_tables(DeviceTables &t) {
         t = DeviceTables{};
         return;
     }
-    ignore_status(hipFree(t.gx));
-    ignore_status(hipFree(t.gs));
-    ignore_status(hipFree(t.gm));
-    ignore_status(hipFree(t.gz));
-    ignore_status(hipFree(t.gc32));
-    ignore_status(hipFree(t.gc64));
+    ignore_status(hipFree(t.r32));
+    ignore_status(hipFree(t.r64));
+    ignore_status(hipFree(t.head));
+    ignore_status(hipFree(t.d32));
+    ignore_status(hipFree(t.d64));
     t = DeviceTables{};
 }
 
@@ -60,58 +59,150 @@ static void upload_vec(U *&d, const std::vector<U> &h, DeviceSlab *slab) {
     if (!h.empty()) SYK_HIP(hipMemcpy(d, h.data(), h.size() * sizeof(U), hipMemcpyHostToDevice));
 }
 
+bool Hamiltonian::grouped() {
+    std::lock_guard<std::mutex> g(dev_mu);
+    if (grouped_ < 0)
+        grouped_ = L >= kDenseMinL && L <= kDenseMaxL &&
+                   K >= kDenseTermsPerMask * static_cast<int64_t>(gather_groups(block_terms[0]));
+    return grouped_ != 0;
+}
+
+template <typename T>
+bool Hamiltonian::tiled() {
+    if (L < kTiledMinL) return false;
+    if (!grouped()) return true;
+    int d = 0;
+    if (hipGetDevice(&d) != hipSuccess) d = 0;       // host-only queries: plans of device 0
+    std::lock_guard<std::mutex> g(dev_mu);
+    return pinned.count({sizeof(T) == 8 ? 1 : 0, d}) != 0;
+}
+template bool Hamiltonian::tiled<float>();
+template bool Hamiltonian::tiled<double>();
+
+// the grouped form of a block's terms (see DenseTerms)
+static void dense_steps(const std::vector<BlockTerm> &bt, std::vector<uint32_t> &head, std::vector<uint32_t> &z,
+                        std::vector<double> &c) {
+    std::vector<uint32_t> hdr;
+    head.assign(kDenseHead, 0u);
+    uint32_t *cut = head.data(), *first = head.data() + kDenseSlices + 1;
+    static_assert(2 * kDenseSlices + 1 <= kDenseHead, "table head");
+    std::vector<int> order(bt.size());
+    for (size_t a = 0; a < order.size(); ++a) order[a] = static_cast<int>(a);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+        return bt[a].x != bt[b].x ? bt[a].x < bt[b].x : (!bt[a].imag && bt[b].imag);
+    });
+    struct Group {
+        size_t lo, mid, hi;
+        size_t steps() const { return (mid - lo + 3) / 4 + (hi - mid + 3) / 4; }
+    };
+    std::vector<Group> groups;
+    size_t total = 0;
+    for (size_t i = 0; i < order.size();) {
+        Group g{i, i, i};
+        while (g.hi < order.size() && bt[order[g.hi]].x == bt[order[i]].x) {
+            if (!bt[order[g.hi]].imag) g.mid = g.hi + 1;
+            ++g.hi;
+        }
+        groups.push_back(g);
+        total += g.steps();
+        i = g.hi;
+    }
+    size_t gi = 0, done = 0;
+    for (int q = 0; q < kDenseSlices; ++q) {
+        cut[q] = static_cast<uint32_t>(hdr.size());
+        first[q] = gi < groups.size() ? bt[order[groups[gi].lo]].x : 0u;
+        // whole groups up to this slice's share of the steps
+        const size_t until = total * (q + 1) / kDenseSlices;
+        while (gi < groups.size() && (done < until || q == kDenseSlices - 1)) {
+            const Group &g = groups[gi++];
+            done += g.steps();
+            for (int ph = 0; ph < 2; ++ph) {
+                const size_t lo = ph ? g.mid : g.lo, hi = ph ? g.hi : g.mid;
+                for (size_t t = lo; t < hi; t += 4) {
+                    hdr.push_back(ph ? 1u << 30 : 0u);
+                    for (size_t u = t; u < t + 4; ++u) {
+                        z.push_back(u < hi ? bt[order[u]].z : 0u);
+                        c.push_back(u < hi ? bt[order[u]].c : 0.0);
+                    }
+                }
+            }
+            hdr.back() |= (1u << 31) | (gi < groups.size() ? bt[order[groups[gi].lo]].x : 0u);
+        }
+        while ((hdr.size() - cut[q]) % kDenseChunk != 0) {
+            hdr.push_back(0u);
+            z.insert(z.end(), 4, 0u);
+            c.insert(c.end(), 4, 0.0);
+        }
+    }
+    cut[kDenseSlices] = static_cast<uint32_t>(hdr.size());
+    head.insert(head.end(), hdr.begin(), hdr.end());
+}
+
 const DeviceTables &Hamiltonian::tables(int blk) {
     int dev = 0;
     SYK_HIP(hipGetDevice(&dev));
+    const bool dense = grouped();
     std::lock_guard<std::mutex> g(dev_mu);
     for (int b = 0; b < 2; ++b)
         if (static_cast<int>(this->dev[b].size()) <= dev) this->dev[b].resize(dev + 1);
     DeviceTables &t = this->dev[blk][dev];
-    if (t.gx) return t;
+    if (t.K) return t;
     const auto &bt = block_terms[blk];
     DeviceTables nt;
     nt.in_slab = slab != nullptr;
-    nt.n_real = n_real[blk];
-    nt.K = K;
-    if (K > 0) {
-        // terms ordered by (x, phase): one gather per x group, the group's real- and
-        // i-phase coefficients summed per amplitude before the multiply
-        std::vector<int> order(K);
-        for (int a = 0; a < K; ++a) order[a] = a;
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-            return bt[a].x != bt[b].x ? bt[a].x < bt[b].x : (!bt[a].imag && bt[b].imag);
-        });
-        std::vector<uint32_t> gx, gs, gm, gz(K);
-        std::vector<float> gc32(K);
-        std::vector<double> gc64(K);
-        for (int i = 0; i < K; ++i) {
-            const BlockTerm &t = bt[order[i]];
-            if (i == 0 || t.x != bt[order[i - 1]].x) {
-                gx.push_back(t.x);
-                gs.push_back(static_cast<uint32_t>(i));
-                gm.push_back(static_cast<uint32_t>(i));
+    nt.n_real = static_cast<uint32_t>(n_real[blk]);
+    nt.K = static_cast<uint32_t>(K);
+    try {
+        if (dense) {
+            std::vector<uint32_t> head, z;
+            std::vector<double> c;
+            dense_steps(bt, head, z, c);
+            std::vector<DenseTerm<float>> d32(z.size());
+            std::vector<DenseTerm<double>> d64(z.size());
+            for (size_t i = 0; i < z.size(); ++i) {
+                d32[i] = {z[i], static_cast<float>(c[i])};
+                d64[i] = {z[i], 0u, c[i]};
             }
-            if (!t.imag) gm.back() = static_cast<uint32_t>(i + 1);
-            gz[i] = t.z;
-            gc64[i] = t.c;
-            gc32[i] = static_cast<float>(t.c);
+            upload_vec(nt.head, head, slab);
+            upload_vec(nt.d32, d32, slab);
+            upload_vec(nt.d64, d64, slab);
+        } else {
+            std::vector<GatherTerm<float>> r32(K);
+            std::vector<GatherTerm<double>> r64(K);
+            for (int i = 0; i < K; ++i) {
+                r32[i] = {bt[i].x, bt[i].z, static_cast<float>(bt[i].c), 0u};
+                r64[i] = {bt[i].x, bt[i].z, bt[i].c};
+            }
+            upload_vec(nt.r32, r32, slab);
+            upload_vec(nt.r64, r64, slab);
         }
-        gs.push_back(static_cast<uint32_t>(K));
-        try {
-            upload_vec(nt.gx, gx, slab);
-            upload_vec(nt.gs, gs, slab);
-            upload_vec(nt.gm, gm, slab);
-            upload_vec(nt.gz, gz, slab);
-            upload_vec(nt.gc32, gc32, slab);
-            upload_vec(nt.gc64, gc64, slab);
-        } catch (...) {
-            free_tables(nt);
-            throw;
-        }
-        nt.G = static_cast<int>(gx.size());
+    } catch (...) {
+        free_tables(nt);
+        throw;
     }
     t = nt;
     return t;
+}
+
+template <typename T>
+static void apply_gather(Hamiltonian &h, const int (&blks)[2], int nblk, const T *x, T *y, int nvec, uint64_t ld,
+                         hipStream_t s) {
+    const uint32_t n = 1u << h.L;
+    const DeviceTables *tb[2] = {&h.tables(blks[0]), &h.tables(blks[nblk - 1])};
+    if (tb[0]->head) {
+        launch_apply_dense<T>(tb, nblk, x, y, n, nvec, ld, s);
+        return;
+    }
+    GatherTerms<T> g[2];
+    for (int b = 0; b < 2; ++b) {
+        if constexpr (sizeof(T) == 4)
+            g[b].rec = tb[b]->r32;
+        else
+            g[b].rec = tb[b]->r64;
+        g[b].n_real = tb[b]->n_real;
+        g[b].K = tb[b]->K;
+    }
+    launch_apply_gather<T>(g, nblk, x, y, n, nvec, ld, s);
 }
 
 template <>
@@ -173,7 +264,7 @@ template const ApplyPlan &Hamiltonian::plan<double>(int, int, int);
 
 template <typename T>
 int Hamiltonian::internal_rotation(int variant) {
-    if (!use_tiled<T>(L)) return 0;
+    if (L < kTiledMinL) return 0;
     const int prec = sizeof(T) == 8 ? 1 : 0;
     const TiledVariant &tv = tiled_variants<T>().at(variant);     // throws for an unknown variant
     std::lock_guard<std::mutex> g(dev_mu);
@@ -199,20 +290,33 @@ template int Hamiltonian::variant<double>();
 
 template <typename T>
 void apply_block(Hamiltonian &h, int blk, int rot, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s) {
-    if (use_tiled<T>(h.L)) {
+    if (h.tiled<T>()) {
         launch_apply_tiled<T>(h.plan<T>(blk, rot, h.variant<T>()), x, y, nvec, ld, s);
     } else {
         if (rot != 0) fail(SYK_EDEVICE, "rotated layouts are only planned for tiled blocks");
-        launch_apply_h<T>(h.tables(blk), x, y, 1u << h.L, nvec, ld, s);
+        apply_gather<T>(h, {blk, blk}, 1, x, y, nvec, ld, s);
     }
 }
+
+template <typename T>
+void apply_full(Hamiltonian &h, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s) {
+    const uint64_t nb = 1ULL << h.L;
+    if (h.tiled<T>()) {
+        apply_block<T>(h, SYK_BLOCK_U, 0, x, y, nvec, ld, s);
+        apply_block<T>(h, SYK_BLOCK_D, 0, x + 2 * nb, y + 2 * nb, nvec, ld, s);
+    } else {
+        apply_gather<T>(h, {SYK_BLOCK_U, SYK_BLOCK_D}, 2, x, y, nvec, ld, s);
+    }
+}
+template void apply_full<float>(Hamiltonian &, const float *, float *, int, uint64_t, hipStream_t);
+template void apply_full<double>(Hamiltonian &, const double *, double *, int, uint64_t, hipStream_t);
 template void apply_block<float>(Hamiltonian &, int, int, const float *, float *, int, uint64_t, hipStream_t);
 template void apply_block<double>(Hamiltonian &, int, int, const double *, double *, int, uint64_t, hipStream_t);
 
 template <typename T>
 int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s) {
-    if (!use_tiled<T>(h.L)) fail(SYK_EDEVICE, "the fused Lanczos step needs a tiled block");
+    if (!h.tiled<T>()) fail(SYK_EDEVICE, "the fused Lanczos step needs a tiled block");
     const ApplyPlan &pl = h.plan<T>(blk, rot, h.variant<T>());
     if (pl.n_wg > lanczos_partials_max(h.L)) fail(SYK_EDEVICE, "partials buffer too small");
     launch_apply_tiled<T>(pl, x, y, 1, 1ULL << h.L, s, &lf);
@@ -228,7 +332,7 @@ template int apply_block_lanczos<double>(Hamiltonian &, int, int, const double *
 // device vectors of 2^L amplitudes.
 template <typename T>
 int autotune(Hamiltonian &h, T *x, T *y, hipStream_t s, bool force, std::vector<float> *times) {
-    if (!use_tiled<T>(h.L)) return -1;
+    if (h.L < kTiledMinL) return -1;
     int dev = 0;
     SYK_HIP(hipGetDevice(&dev));
     if (!force) {
@@ -286,7 +390,7 @@ Hamiltonian::~Hamiltonian() {
     bool have = hipGetDevice(&cur) == hipSuccess;
     for (int b = 0; b < 2; ++b) {
         for (size_t d = 0; d < dev[b].size(); ++d)
-            if (dev[b][d].gx) {
+            if (dev[b][d].K) {
                 if (have) ignore_status(hipSetDevice(static_cast<int>(d)));
                 free_tables(dev[b][d]);
             }
