@@ -168,16 +168,17 @@ typedef struct {
 
 typedef struct {
     int substeps;      /* restarts taken */
-    int matvecs;       /* apply_H calls */
+    int matvecs;       /* apply_H calls that the result uses (reorth = 0 may have enqueued one or
+                          two more when the estimate met the tolerance) */
     int breakdown;     /* 1 if an invariant subspace ended a Lanczos run (exact) */
     double err_est;    /* sum over sub-steps of the accepted error estimates, relative */
     int reorths;       /* Lanczos steps given a full reorthogonalisation (reorth 2 and 3) */
 } syk_krylov_stats;
 
 /* Fill `o` with defaults for dtype dt (m = 30, tol = 1e-12 for C128 / 1e-7 for C64,
- * reorth = 0, max_substeps = 0).  With reorth = 0 on blocks served by the tiled kernel,
- * each Lanczos step is one fused apply (w = H v_j - beta v_{j-1} plus the alpha/beta sums)
- * and one normalising pass. */
+ * reorth = 0, max_substeps = 0).  With reorth = 0 each Lanczos step is one fused apply
+ * (w = H v_j - beta v_{j-1} plus the alpha sums) and one residual pass, and steps are enqueued
+ * ahead of the host's checks. */
 void syk_krylov_default_opts(syk_dtype dt, syk_krylov_opts *o);
 
 /* out = e^{z H_blk} v, z = z_re + i z_im, by Lanczos with restarts (the restarted Krylov

@@ -847,6 +847,7 @@ syk_status syk_release_workspace(void) {
         check_device();
         syk::thread_workspace(0).release();
         syk::thread_workspace(1).release();
+        syk::HostScalars::trim();
     });
 }
 

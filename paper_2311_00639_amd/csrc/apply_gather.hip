@@ -37,6 +37,65 @@ __device__ __forceinline__ double2 load_amp(__amdgpu_buffer_rsrc_t r, uint32_t v
 
 constexpr uint32_t kBufferWord3 = 0x00020000u;   // raw buffer descriptor: 32-bit data format, no swizzle
 
+// The Lanczos epilogue (LanczosFuse) of a workgroup of S waves, S >= 4.  n_j^2 is the sum of the partials
+// the previous pass left (at most 512): the first 256 threads load them before the apply and the
+// sum is ready after the barrier that ends it, so no launch of its own is needed for it.
+template <typename T, int S>
+struct Epilogue {
+    using V = typename V2t<T>::type;
+    const LanczosFuse<T> &lf;
+    double *sh;                               // S + 4 doubles of LDS: norm shares, then row shares
+    double norm = 0.0;
+    T sc = 0, bp = 0;
+    __device__ __forceinline__ void load() {
+        if (threadIdx.x < 256)
+            for (int p = threadIdx.x; p < lf.n_parts; p += 256) norm += lf.norm_parts[p];
+    }
+    // before the barrier that ends the apply
+    __device__ __forceinline__ void share() {
+        if (threadIdx.x < 256) {
+            for (int off = 32; off > 0; off >>= 1) norm += __shfl_down(norm, off, 64);
+            if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = norm;
+        }
+    }
+    // after it: the scales (a zero vector after an exact breakdown stays zero)
+    __device__ __forceinline__ void scales() {
+        const double n2 = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            lf.norm2[lf.j] = n2;
+            __hip_atomic_store(lf.norm2_host, n2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        const double nj = sqrt(n2);
+        const double njm = lf.j >= 1 ? sqrt(lf.norm2[lf.j - 1]) : 0.0;
+        sc = nj > 1e-300 ? static_cast<T>(1.0 / nj) : T(0);
+        bp = njm > 1e-300 ? static_cast<T>(nj / njm) : T(0);
+    }
+    // w = H v_j - beta_{j-1} v_{j-1} of amplitude m from s = (H u_j)[m]; adds to Re <v_j, w>
+    __device__ __forceinline__ V row(V s, uint32_t m, double &sum) {
+        V w{sc * s.x, sc * s.y};
+        if (lf.vprev) {
+            const V p = reinterpret_cast<const V *>(lf.vprev)[m];
+            w.x -= bp * p.x;
+            w.y -= bp * p.y;
+        }
+        const V u = reinterpret_cast<const V *>(lf.vcur)[m];
+        const V c{sc * u.x, sc * u.y};
+        sum += static_cast<double>(c.x) * w.x + static_cast<double>(c.y) * w.y;
+        return w;
+    }
+    // every wave's share of Re <v_j, w> -> partials[blockIdx.x]
+    __device__ __forceinline__ void finish(double sum) {
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+        if ((threadIdx.x & 63u) == 0) sh[4 + (threadIdx.x >> 6)] = sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double v = 0.0;
+            for (int k = 0; k < S; ++k) v += sh[4 + k];
+            lf.partials[blockIdx.x] = v;
+        }
+    }
+};
+
 // One wave owns 64 R consecutive amplitudes (lane l holds base + l + 64 r) and one of S slices
 // of the term list; the S waves of a group are in one workgroup and their sums are added in
 // slice order in LDS, so the result does not depend on scheduling.
@@ -49,24 +108,27 @@ constexpr uint32_t kBufferWord3 = 0x00020000u;   // raw buffer descriptor: 32-bi
 // in flight at once.  Three complex64 vectors over both blocks at N = 34, k = 4 (5.3e7
 // term-amplitudes): 25 us, against 94 us in two launches of one amplitude per thread with
 // per-lane term loads.
-template <typename T, int R, int S, int GPB>
-__global__ void __launch_bounds__(64 * S * GPB) gather_sparse(GatherTerms<T> t0, GatherTerms<T> t1,
-                                                              const typename V2t<T>::type *__restrict__ x,
-                                                              typename V2t<T>::type *__restrict__ y, uint32_t n,
-                                                              uint64_t ld) {
+template <typename T, int R, int S, bool FUSE>
+__global__ void __launch_bounds__(64 * S) gather_sparse(GatherTerms<T> t0, GatherTerms<T> t1,
+                                                        const typename V2t<T>::type *__restrict__ x,
+                                                        typename V2t<T>::type *__restrict__ y, uint32_t n, uint64_t ld,
+                                                        LanczosFuse<T> lf) {
+    static_assert(S >= 4, "the epilogue sums with four waves");
     using V = typename V2t<T>::type;
     constexpr int SH = sizeof(T) == 4 ? 3 : 4;       // log2 of the bytes per amplitude
     constexpr int U = R >= 4 ? 2 : 4;                // terms in flight
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t slice = wave % S, group = blockIdx.x * GPB + wave / S;
-    const uint32_t base = group * (64u * R);
+    const uint32_t slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t base = blockIdx.x * (64u * R);
+    __shared__ double sh[S + 4];
+    Epilogue<T, S> epi{lf, sh};
+    if constexpr (FUSE) epi.load();
     const GatherTerms<T> tb = blockIdx.z == 0 ? t0 : t1;
     const uint64_t vo = static_cast<uint64_t>(blockIdx.y) * ld + static_cast<uint64_t>(blockIdx.z) * n;
     V acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = V{T(0), T(0)};
-    if (base < n) {
+    {
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<V *>(x + vo), 0, static_cast<int>(n << SH), kBufferWord3);
         // blocks below 64 amplitudes: the spare lanes compute copies and store nothing
@@ -112,44 +174,43 @@ __global__ void __launch_bounds__(64 * S * GPB) gather_sparse(GatherTerms<T> t0,
         phase(std::false_type{}, nr * slice / S, nr * (slice + 1) / S);
         phase(std::true_type{}, nr + ni * slice / S, nr + ni * (slice + 1) / S);
     }
-    if constexpr (S > 1) {
-        __shared__ V part[GPB][S][R][64];
+    __shared__ V part[S][R][64];
 #pragma unroll
-        for (int r = 0; r < R; ++r) part[wave / S][slice][r][lane] = acc[r];
-        __syncthreads();
-        // wave `slice` of the group sums register rows slice, slice + S, ...
+    for (int r = 0; r < R; ++r) part[slice][r][lane] = acc[r];
+    if constexpr (FUSE) epi.share();
+    __syncthreads();
+    if constexpr (FUSE) epi.scales();
+    double dot = 0.0;
+    // wave q sums register rows q, q + S, ..., the slices in order
+    for (uint32_t r = slice; r < R; r += S) {
+        V s = part[0][r][lane];
 #pragma unroll
-        for (int r0 = 0; r0 < R; r0 += S) {
-            const int r = r0 + static_cast<int>(slice);
-            if (r < R && base < n) {
-                V s = part[wave / S][0][r][lane];
-#pragma unroll
-                for (int k = 1; k < S; ++k) {
-                    s.x += part[wave / S][k][r][lane].x;
-                    s.y += part[wave / S][k][r][lane].y;
-                }
-                const uint32_t m = base + 64u * r + lane;
-                if (m < n) y[vo + m] = s;
-            }
+        for (int k = 1; k < S; ++k) {
+            s.x += part[k][r][lane].x;
+            s.y += part[k][r][lane].y;
         }
-    } else {
-        if (base < n) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const uint32_t m = base + 64u * r + lane;
-                if (m < n) y[vo + m] = acc[r];
-            }
+        const uint32_t m = base + 64u * r + lane;
+        if (m < n) {
+            if constexpr (FUSE) s = epi.row(s, m, dot);
+            y[vo + m] = s;
         }
     }
+    if constexpr (FUSE) epi.finish(dot);
 }
 
 template <typename T, int R, int S>
-void go(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld, hipStream_t s) {
+int go(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld, hipStream_t s,
+       const LanczosFuse<T> *lf) {
     using V = typename V2t<T>::type;
-    constexpr int GPB = S >= 4 ? 1 : 4 / S;
-    const uint32_t per = 64u * R * GPB;
-    hipLaunchKernelGGL((gather_sparse<T, R, S, GPB>), dim3((n + per - 1) / per, nvec, nblk), dim3(64 * S * GPB), 0, s,
-                       tb[0], tb[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld);
+    const uint32_t g = (n + 64u * R - 1) / (64u * R);
+    if (lf)
+        hipLaunchKernelGGL((gather_sparse<T, R, S, true>), dim3(g), dim3(64 * S), 0, s, tb[0], tb[0],
+                           reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld, *lf);
+    else
+        hipLaunchKernelGGL((gather_sparse<T, R, S, false>), dim3(g, nvec, nblk), dim3(64 * S), 0, s, tb[0],
+                           tb[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld,
+                           LanczosFuse<T>{});
+    return static_cast<int>(g);
 }
 
 // ------------------------------------------------------------------ grouped by x mask
@@ -220,10 +281,11 @@ __device__ __forceinline__ void signed_pair(uint32_t pa, uint32_t pb, double c, 
 // kDenseChunk = 16 steps (64 of them, one per lane) are loaded one chunk ahead, pass through
 // the wave's own piece of LDS and are read back by the term each lane supplies; the partners of
 // a group are gathered while the group before it is summed.
-template <typename T, typename P, typename Tile, int S>
+template <typename T, typename P, typename Tile, int S, bool FUSE>
 __global__ void __launch_bounds__(64 * S) gather_dense(DenseTerms<P> t0, DenseTerms<P> t1,
                                                        const typename V2t<T>::type *__restrict__ x,
-                                                       typename V2t<T>::type *__restrict__ y, uint32_t n, uint64_t ld) {
+                                                       typename V2t<T>::type *__restrict__ y, uint32_t n, uint64_t ld,
+                                                       LanczosFuse<T> lf) {
     using V = typename V2t<T>::type;
     using M = typename Tile::Acc;
     constexpr int R = Tile::R;
@@ -237,6 +299,9 @@ __global__ void __launch_bounds__(64 * S) gather_dense(DenseTerms<P> t0, DenseTe
     const uint64_t vo = static_cast<uint64_t>(blockIdx.y) * ld + static_cast<uint64_t>(blockIdx.z) * n;
     constexpr size_t kRecs = sizeof(DenseTerm<P>) * 64 * S, kPart = sizeof(V) * S * R * 64;
     __shared__ __attribute__((aligned(16))) char lds[kRecs > kPart ? kRecs : kPart];
+    __shared__ double sh[S + 4];
+    Epilogue<T, S> epi{lf, sh};
+    if constexpr (FUSE) epi.load();
     DenseTerm<P> *stage = reinterpret_cast<DenseTerm<P> *>(lds) + 64 * wave;
     V acc[R];
 #pragma unroll
@@ -294,7 +359,10 @@ __global__ void __launch_bounds__(64 * S) gather_dense(DenseTerms<P> t0, DenseTe
     __syncthreads();                                      // the record staging is done with
 #pragma unroll
     for (int r = 0; r < R; ++r) part[(wave * R + r) * 64 + lane] = acc[r];
+    if constexpr (FUSE) epi.share();
     __syncthreads();
+    if constexpr (FUSE) epi.scales();
+    double dot = 0.0;
     if (wave < R) {                                       // wave r sums register row r, slices in order
         V s = part[wave * 64 + lane];
 #pragma unroll
@@ -302,16 +370,20 @@ __global__ void __launch_bounds__(64 * S) gather_dense(DenseTerms<P> t0, DenseTe
             s.x += part[(k * R + wave) * 64 + lane].x;
             s.y += part[(k * R + wave) * 64 + lane].y;
         }
-        y[vo + base + 64u * wave + lane] = s;
+        const uint32_t m = base + 64u * wave + lane;
+        if constexpr (FUSE) s = epi.row(s, m, dot);
+        y[vo + m] = s;
     }
+    if constexpr (FUSE) epi.finish(dot);
 }
 
 }  // namespace
 
 // nblk = 2: blocks U and D side by side in one vector (D at element offset n)
 template <typename T>
-void launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld,
-                         hipStream_t s) {
+int launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld,
+                        hipStream_t s, const LanczosFuse<T> *lf) {
+    int g;
     // Amplitudes per lane R and slices of the term list S, by block size alone (so that a vector's
     // result does not depend on how many vectors or blocks share the launch): as many amplitudes
     // per lane as leave about 2048 waves, 8 per CU, with at most 16 slices.  Measured with every
@@ -320,21 +392,23 @@ void launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T 
     // S = 4 takes 18.8 us (complex64), S = 16 19.1 us, R = 2 with S = 2 19.3 us.
     const uint32_t groups = (n + 63u) / 64u;
     if (groups >= 2048u)
-        go<T, 4, 4>(tb, nblk, x, y, n, nvec, ld, s);
+        g = go<T, 4, 4>(tb, nblk, x, y, n, nvec, ld, s, lf);
     else if (groups >= 1024u)
-        go<T, 4, 8>(tb, nblk, x, y, n, nvec, ld, s);
+        g = go<T, 4, 8>(tb, nblk, x, y, n, nvec, ld, s, lf);
     else if (groups >= 256u)
-        go<T, 2, 16>(tb, nblk, x, y, n, nvec, ld, s);
+        g = go<T, 2, 16>(tb, nblk, x, y, n, nvec, ld, s, lf);
     else
-        go<T, 1, 16>(tb, nblk, x, y, n, nvec, ld, s);
+        g = go<T, 1, 16>(tb, nblk, x, y, n, nvec, ld, s, lf);
     SYK_HIP(hipGetLastError());
+    return g;
 }
 
 template <typename T>
-void launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec,
-                        uint64_t ld, hipStream_t s) {
+int launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec,
+                       uint64_t ld, hipStream_t s, const LanczosFuse<T> *lf) {
     using V = typename V2t<T>::type;
     if (n < 256) fail(SYK_EDEVICE, "the grouped gather needs 256 amplitudes");
+    int g = 0;
     auto go = [&](auto pc, auto tile, auto sc) {
         using P = decltype(pc);
         using Tile = decltype(tile);
@@ -347,8 +421,14 @@ void launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x
             else
                 d[b].rec = tb[b]->d64;
         }
-        hipLaunchKernelGGL((gather_dense<T, P, Tile, S>), dim3(n / (64 * Tile::R), nvec, nblk), dim3(64 * S), 0, s, d[0],
-                           d[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld);
+        g = static_cast<int>(n / (64 * Tile::R));
+        if (lf)
+            hipLaunchKernelGGL((gather_dense<T, P, Tile, S, true>), dim3(g), dim3(64 * S), 0, s, d[0], d[0],
+                               reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld, *lf);
+        else
+            hipLaunchKernelGGL((gather_dense<T, P, Tile, S, false>), dim3(g, nvec, nblk), dim3(64 * S), 0, s, d[0],
+                               d[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld,
+                               LanczosFuse<T>{});
     };
     // Small blocks take 64-amplitude tiles to reach more CUs (N = 30: 84 us against 95 us in
     // complex64 and 87 us against 140 us in complex128 with 256-amplitude tiles), larger ones 256
@@ -361,15 +441,15 @@ void launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x
     else
         go(T(0), MfmaTile<T>{}, std::integral_constant<int, 8>{});
     SYK_HIP(hipGetLastError());
+    return g;
 }
 
-template void launch_apply_dense<float>(const DeviceTables *const (&)[2], int, const float *, float *, uint32_t, int,
-                                        uint64_t, hipStream_t);
-template void launch_apply_dense<double>(const DeviceTables *const (&)[2], int, const double *, double *, uint32_t, int,
-                                         uint64_t, hipStream_t);
-template void launch_apply_gather<float>(const GatherTerms<float> (&)[2], int, const float *, float *, uint32_t, int,
-                                         uint64_t, hipStream_t);
-template void launch_apply_gather<double>(const GatherTerms<double> (&)[2], int, const double *, double *, uint32_t, int,
-                                          uint64_t, hipStream_t);
+#define SYK_INST(T)                                                                                                 \
+    template int launch_apply_dense<T>(const DeviceTables *const (&)[2], int, const T *, T *, uint32_t, int,        \
+                                       uint64_t, hipStream_t, const LanczosFuse<T> *);                              \
+    template int launch_apply_gather<T>(const GatherTerms<T> (&)[2], int, const T *, T *, uint32_t, int, uint64_t,  \
+                                        hipStream_t, const LanczosFuse<T> *);
+SYK_INST(float)
+SYK_INST(double)
 
 }  // namespace syk

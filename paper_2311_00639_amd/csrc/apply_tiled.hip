@@ -492,15 +492,14 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
         static_for<0, TPW>(store);
         return;
     }
-    // Lanczos epilogue: w = H v_j - beta_{j-1} v_{j-1}, and this workgroup's shares of
-    // <v_j, w> (re, im), ||w||^2 and ||v_j||^2 in double
-    // scales of the unnormalised basis (see LanczosFuse)
-    // (a zero vector after an exact breakdown stays zero)
-    const double nj = lf.j >= 1 ? sqrt(lf.beta2[lf.j]) : 1.0;
-    const double njm = lf.j >= 2 ? sqrt(lf.beta2[lf.j - 1]) : 1.0;
+    // Lanczos epilogue: w = H v_j - beta_{j-1} v_{j-1} and this workgroup's share of
+    // Re <v_j, w> in double, with the scales of the unnormalised basis (see LanczosFuse; a zero
+    // vector after an exact breakdown stays zero)
+    const double nj = sqrt(lf.norm2[lf.j]);
+    const double njm = lf.j >= 1 ? sqrt(lf.norm2[lf.j - 1]) : 0.0;
     const T sc = nj > 1e-300 ? static_cast<T>(1.0 / nj) : T(0);
     const T bp = (lf.vprev && njm > 1e-300) ? static_cast<T>(nj / njm) : T(0);
-    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    double sum = 0.0;
     auto epi_tile = [&](auto has_prev, auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
         {
@@ -519,10 +518,7 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
                 }
                 const V c = V{sc * vc[m].x, sc * vc[m].y};
                 dst[m] = w;
-                sum[0] += static_cast<double>(c.x) * w.x + static_cast<double>(c.y) * w.y;
-                sum[1] += static_cast<double>(c.x) * w.y - static_cast<double>(c.y) * w.x;
-                sum[2] += static_cast<double>(w.x) * w.x + static_cast<double>(w.y) * w.y;
-                sum[3] += static_cast<double>(c.x) * c.x + static_cast<double>(c.y) * c.y;
+                sum += static_cast<double>(c.x) * w.x + static_cast<double>(c.y) * w.y;
                 // bound the loads in flight: with several workgroups per CU the register
                 // budget is 64 VGPRs
                 if (r % 2 == 1) __builtin_amdgcn_sched_barrier(0);
@@ -536,18 +532,14 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
         epilogue(std::true_type{});
     else
         epilogue(std::false_type{});
-    __shared__ double red[4][NT / 64];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double v = sum[k];
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        if ((tid & 63) == 0) red[k][tid >> 6] = v;
-    }
+    __shared__ double red[NT / 64];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+    if ((tid & 63) == 0) red[tid >> 6] = sum;
     __syncthreads();
-    if (tid < 4) {
+    if (tid == 0) {
         double v = 0.0;
-        for (int w = 0; w < NT / 64; ++w) v += red[tid][w];
-        lf.partials[static_cast<size_t>(blockIdx.x) * 4 + tid] = v;
+        for (int w = 0; w < NT / 64; ++w) v += red[w];
+        lf.partials[blockIdx.x] = v;
     }
 }
 

@@ -149,20 +149,24 @@ struct ApplyPlan {
     double *c64 = nullptr;
 };
 
-// Optional epilogue of the tiled apply_H for Lanczos step j of the fused path, where the
-// basis is stored unnormalised: slot i >= 1 holds u_i with ||u_i|| = sqrt(beta2[i]) (so
-// v_i = u_i / sqrt(beta2[i])), slot 0 holds v_0.  With x = u_j (vcur) the epilogue forms
-//   y = H v_j - beta_{j-1} v_{j-1} = s_j H u_j - (beta_{j-1} s_{j-1}) u_{j-1}
-// (s_i = 1 / ||u_i||, s_0 = 1, beta_{j-1} = ||u_j||; vprev = u_{j-1}, null for j = 0) and
-// per-workgroup partial sums (re <v_j,y>, im <v_j,y>, ||y||^2, ||v_j||^2) at
-// partials[4 * blockIdx.x].
+// Optional epilogue of apply_H for Lanczos step j, where the basis is stored unnormalised:
+// slot i holds u_i with n_i = ||u_i|| (so v_i = u_i / n_i and beta_i = n_{i+1}); slot 0 is the start
+// vector itself.  With x = u_j (vcur) the epilogue forms
+//   y = H v_j - beta_{j-1} v_{j-1} = H u_j / n_j - (n_j / n_{j-1}) u_{j-1}
+// (vprev = u_{j-1}, null for j = 0) and one partial sum of Re <v_j, y> per workgroup at
+// partials[blockIdx.x].  norm2[i] = n_i^2 (device) holds n_{j-1}, and n_j too where the tiled kernel
+// runs; the gather kernels take n_j^2 as the sum of the n_parts partials at norm_parts (left by the pass
+// that wrote u_j) and workgroup 0 writes it to norm2[j] and to norm2_host.
 template <typename T>
 struct LanczosFuse {
     const T *vprev = nullptr;
     const T *vcur = nullptr;
-    const double *beta2 = nullptr;     // device, indexed by basis slot
+    double *norm2 = nullptr;           // device, indexed by basis slot
     int j = 0;
     double *partials = nullptr;
+    const double *norm_parts = nullptr;
+    int n_parts = 0;
+    double *norm2_host = nullptr;      // pinned host memory, the slot of n_j^2
 };
 
 // ------------------------------------------------------------------ host-side model
@@ -243,26 +247,31 @@ void apply_block(Hamiltonian &h, int blk, int rot, const T *x, T *y, int nvec, u
 // the same on both blocks of the full space (U, then D at element offset 2^L), layout 0
 template <typename T>
 void apply_full(Hamiltonian &h, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s);
-// y = H_blk x with the fused Lanczos epilogue (tiled blocks only); returns the number of
-// partials written (one per tile)
+// y = H_blk x with the fused Lanczos epilogue; returns the number of partials written (one per
+// workgroup)
 template <typename T>
 int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s);
-// upper bound on the partials apply_block_lanczos writes for a block of 2^L amplitudes
-inline uint64_t lanczos_partials_max(int L) { return 1ULL << (L > 10 ? L - 10 : 0); }
+// upper bound on the partials apply_block_lanczos writes for a block of 2^L amplitudes (tiled:
+// one per tile of 2^10 or more; gather: at most 512 workgroups below the tiled size, and one
+// per 256 amplitudes for a dense block above it)
+inline uint64_t lanczos_partials_max(int L) {
+    return L >= kTiledMinL ? 1ULL << (L > kDenseMaxL ? L - 10 : L - 8) : 512;
+}
 // time the tiled-kernel variants and keep the fastest; returns it (-1: block not tiled)
 template <typename T>
 int autotune(Hamiltonian &h, T *x, T *y, hipStream_t s, bool force, std::vector<float> *times = nullptr);
 
 // ------------------------------------------------------------------ kernels (HIP side)
 // All launchers enqueue on `s` and never synchronise.
-// gather kernels over nblk blocks side by side (2: U, then D at element offset n)
+// gather kernels over nblk blocks side by side (2: U, then D at element offset n); with lf (one
+// block, one vector) the Lanczos epilogue.  Return the workgroups launched per vector and block.
 template <typename T>
-void launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld,
-                         hipStream_t s);
+int launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld,
+                        hipStream_t s, const LanczosFuse<T> *lf = nullptr);
 template <typename T>
-void launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec,
-                        uint64_t ld, hipStream_t s);
+int launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec,
+                       uint64_t ld, hipStream_t s, const LanczosFuse<T> *lf = nullptr);
 // psi in layout rotation `rot`: index p holds standard amplitude rotl(p, rot)
 template <typename T>
 void launch_haar_raw(uint64_t state_seed, int v, int L, int rot, T *psi_U, T *psi_D, double *partials, int n_part,
@@ -289,22 +298,31 @@ void launch_lanczos_orth2(T *w, const T *vcur, const double *alpha, uint64_t n, 
                           hipStream_t s);
 template <typename T>
 void launch_lanczos_normalize(T *w, const double *beta, uint64_t n, hipStream_t s);
-// sums[0..4) = (re <v,w>, im <v,w>, ||w||^2, ||v||^2) -> alpha = (re, im) at alpha_out[0..2),
-// beta^2 = ||w - alpha_re v||^2 at beta2_out (expanded in the sums)
-void launch_lanczos_scalars(const double *partials, int n_part, double *alpha_out, double *beta2_out,
-                            hipStream_t s);
-// fused path: w <- w - alpha_j s_j u_j (v = u_j, s_j from beta2[j], j >= 1; 1 for j = 0) and
-// ||w||^2 at beta2_out, summed in a fixed order over per-workgroup partials (one workgroup
-// per 256 amplitudes, at most partials_cap of them) and a 512-double stage buffer
+// The scalars of the fused path are summed over per-workgroup partials in a fixed order (256
+// threads striding the partials, then lanes, then waves), wherever the sum is formed, and each is also
+// stored to a slot of pinned host memory.
+// dst = dst_host = sum of n_part partials
+void launch_publish_sum(const double *partials, int n_part, double *dst, double *dst_host, hipStream_t s);
+// u_{j+1} = w - (alpha_j / n_j) u_j in place on w (v = u_j, n_j^2 = norm2[j]), and n_part partials of
+// ||u_{j+1}||^2.  a_parts > 0: alpha_j is the sum of a_parts partials at a_part, which every workgroup
+// forms (workgroup 0 stores it to alpha and alpha_host); 0: alpha_j is read from alpha.
 template <typename T>
-void launch_lanczos_residual(T *w, const T *v, const double *alpha, const double *beta2, int j, uint64_t n,
-                             double *partials, uint64_t partials_cap, double *stage, double *beta2_out,
-                             hipStream_t s);
+void launch_lanczos_residual(T *w, const T *v, double *alpha, double *alpha_host, const double *a_part, int a_parts,
+                             const double *norm2, int j, uint64_t n, double *partials, int n_part, hipStream_t s);
+// the sum of many partials in two stages (stage: 512 doubles), published as launch_publish_sum
+void launch_publish_sum2(const double *partials, int n_part, double *stage, double *dst, double *dst_host,
+                         hipStream_t s);
 template <typename T>
 void launch_scale_copy(const T *src, T *dst, uint64_t n, double scale, hipStream_t s);
+// out = coef[0] v0 + sum_{k >= 1} coef[k] basis_k (complex coefficients); out may equal v0
 template <typename T>
-void launch_combine(const T *basis, uint64_t stride, int nb, const double *coef_dev, T *out, uint64_t n,
+void launch_combine(const T *v0, const T *basis, uint64_t stride, int nb, const double *coef_dev, T *out, uint64_t n,
                     hipStream_t s);
+// the same for nb <= kCombineArgs vectors with the coefficients (host) passed by value
+constexpr int kCombineArgs = 64;
+template <typename T>
+void launch_combine_args(const T *v0, const T *basis, uint64_t stride, int nb, const double *coef, T *out, uint64_t n,
+                         hipStream_t s);
 // subtract projections: w -= sum_k c_k v_k with c_k = <v_k, w> taken from coef_dev (complex)
 template <typename T>
 void launch_subtract_proj(T *w, const T *basis, uint64_t stride, int nb, const double *coef_dev, uint64_t n,

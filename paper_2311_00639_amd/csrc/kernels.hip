@@ -324,27 +324,34 @@ void launch_lanczos_normalize(T *w, const double *norm2, uint64_t n, hipStream_t
     SYK_HIP(hipGetLastError());
 }
 
-__global__ void __launch_bounds__(kBlock) lanczos_scalars_kernel(const double *__restrict__ partials, int n_part,
-                                                                 double *__restrict__ alpha_out,
-                                                                 double *__restrict__ beta2_out) {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int p = threadIdx.x; p < n_part; p += kBlock)
-        for (int k = 0; k < 4; ++k) acc[k] += partials[static_cast<size_t>(p) * 4 + k];
-    __shared__ double tot[4];
-    block_sum<4>(acc, tot);
+// Sum of n_part partials in every thread: thread t adds partials t, t + 256, ..., then lanes,
+// then the four waves (the order every sum of the fused path uses).  Ends after a barrier.
+__device__ inline double total_of(const double *__restrict__ partials, int n_part, double *sh) {
+    double a = 0.0;
+    for (int p = threadIdx.x; p < n_part; p += kBlock) a += partials[p];
+    for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
     __syncthreads();
+    return ((sh[0] + sh[1]) + sh[2]) + sh[3];
+}
+
+// a scalar the host polls for while later kernels run
+__device__ inline void to_host(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ void __launch_bounds__(kBlock) publish_sum_kernel(const double *__restrict__ partials, int n_part,
+                                                             double *__restrict__ dst, double *dst_host) {
+    __shared__ double sh[kBlock / 64];
+    const double v = total_of(partials, n_part, sh);
     if (threadIdx.x == 0) {
-        alpha_out[0] = tot[0];
-        alpha_out[1] = tot[1];
-        // beta is not formed from these sums (||y||^2 - alpha^2 cancels when the Krylov
-        // space is nearly invariant); the residual pass computes it from the vector
-        if (beta2_out) beta2_out[0] = 0.0;
+        dst[0] = v;
+        to_host(dst_host, v);
     }
 }
 
-void launch_lanczos_scalars(const double *partials, int n_part, double *alpha_out, double *beta2_out,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(lanczos_scalars_kernel, dim3(1), dim3(kBlock), 0, s, partials, n_part, alpha_out, beta2_out);
+void launch_publish_sum(const double *partials, int n_part, double *dst, double *dst_host, hipStream_t s) {
+    hipLaunchKernelGGL(publish_sum_kernel, dim3(1), dim3(kBlock), 0, s, partials, n_part, dst, dst_host);
     SYK_HIP(hipGetLastError());
 }
 
@@ -355,27 +362,44 @@ template <typename T> struct Wide;
 template <> struct Wide<float> { using type = float4; static constexpr int amps = 2; };
 template <> struct Wide<double> { using type = double2; static constexpr int amps = 1; };
 
-// fused Lanczos: w <- w - (alpha_j / ||u_j||) u_j, with one partial of ||w||^2 per
-// workgroup.  One amplitude per thread and as many workgroups as that takes: at 2^27
-// complex64 amplitudes this streams at 6.2 TB/s, against 5.3 TB/s for 2048 workgroups
-// walking contiguous slices and 5.6-5.9 TB/s for two or four amplitudes per thread.
-template <typename T>
+// fused Lanczos: w <- w - (alpha_j / n_j) u_j, with one partial of ||w||^2 per workgroup.
+// REDUCE: every workgroup first forms alpha_j from the apply's partials (at most 1024 doubles
+// out of L2, behind the loads of its first amplitudes), which saves a one-workgroup launch per Lanczos
+// step; at most 1024 workgroups then.  Otherwise one amplitude per thread and as many workgroups as
+// that takes: at 2^27 complex64 amplitudes this streams at 6.2 TB/s, against 5.3 TB/s for 2048
+// workgroups walking contiguous slices and 5.6-5.9 TB/s for two or four amplitudes per thread.
+template <typename T, bool REDUCE>
 __global__ void __launch_bounds__(kBlock) lanczos_residual(V2<T> *__restrict__ w, const V2<T> *__restrict__ v,
-                                                           const double *__restrict__ alpha,
-                                                           const double *__restrict__ beta2, int j, uint64_t n,
+                                                           double *alpha, double *alpha_host,
+                                                           const double *__restrict__ a_part, int a_parts,
+                                                           const double *__restrict__ norm2, int j, uint64_t n,
                                                            double *__restrict__ partials) {
-    const double nj = j >= 1 ? sqrt(beta2[j]) : 1.0;
-    const double sj = nj > 1e-300 ? 1.0 / nj : 0.0;
-    const T a = static_cast<T>(alpha[0] * sj);
+    uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    V2<T> u = i < n ? w[i] : V2<T>{T(0), T(0)}, c = i < n ? v[i] : V2<T>{T(0), T(0)};
+    double al;
+    if constexpr (REDUCE) {
+        __shared__ double sh[kBlock / 64];
+        al = total_of(a_part, a_parts, sh);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            alpha[0] = al;
+            to_host(alpha_host, al);
+        }
+    } else {
+        al = alpha[0];
+    }
+    const double nj = sqrt(norm2[j]);
+    const T a = static_cast<T>(nj > 1e-300 ? al / nj : 0.0);
     double acc[1] = {0.0};
-    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
-         i += static_cast<uint64_t>(gridDim.x) * kBlock) {
-        V2<T> u = w[i];
-        const V2<T> c = v[i];
+    while (i < n) {
         u.x -= a * c.x;
         u.y -= a * c.y;
         w[i] = u;
         acc[0] += static_cast<double>(u.x) * u.x + static_cast<double>(u.y) * u.y;
+        i += static_cast<uint64_t>(gridDim.x) * kBlock;
+        if (i < n) {
+            u = w[i];
+            c = v[i];
+        }
     }
     block_sum<1>(acc, partials + blockIdx.x);
 }
@@ -393,21 +417,26 @@ __global__ void __launch_bounds__(kBlock) sum_chunks_kernel(const double *__rest
 }
 
 template <typename T>
-void launch_lanczos_residual(T *w, const T *v, const double *alpha, const double *beta2, int j, uint64_t n,
-                             double *partials, uint64_t partials_cap, double *stage, double *beta2_out,
-                             hipStream_t s) {
+void launch_lanczos_residual(T *w, const T *v, double *alpha, double *alpha_host, const double *a_part, int a_parts,
+                             const double *norm2, int j, uint64_t n, double *partials, int n_part, hipStream_t s) {
+    if (a_parts > 0)
+        hipLaunchKernelGGL((lanczos_residual<T, true>), dim3(n_part), dim3(kBlock), 0, s, reinterpret_cast<V2<T> *>(w),
+                           reinterpret_cast<const V2<T> *>(v), alpha, alpha_host, a_part, a_parts, norm2, j, n,
+                           partials);
+    else
+        hipLaunchKernelGGL((lanczos_residual<T, false>), dim3(n_part), dim3(kBlock), 0, s, reinterpret_cast<V2<T> *>(w),
+                           reinterpret_cast<const V2<T> *>(v), alpha, alpha_host, a_part, a_parts, norm2, j, n,
+                           partials);
+    SYK_HIP(hipGetLastError());
+}
+
+void launch_publish_sum2(const double *partials, int n_part, double *stage, double *dst, double *dst_host,
+                         hipStream_t s) {
     constexpr int kStage = 512;              // first-stage workgroups (stage holds this many doubles)
-    uint64_t g = (n + kBlock - 1) / kBlock;
-    if (g > partials_cap) g = partials_cap;  // then each thread takes several amplitudes
-    if (g < 1 || g > (1u << 30)) fail(SYK_EDEVICE, "lanczos_residual: bad partials capacity");
-    hipLaunchKernelGGL(lanczos_residual<T>, dim3(static_cast<unsigned>(g)), dim3(kBlock), 0, s,
-                       reinterpret_cast<V2<T> *>(w), reinterpret_cast<const V2<T> *>(v), alpha, beta2, j, n,
-                       partials);
+    const int st = n_part < kStage ? n_part : kStage;
+    hipLaunchKernelGGL(sum_chunks_kernel, dim3(st), dim3(kBlock), 0, s, partials, n_part, stage);
     SYK_HIP(hipGetLastError());
-    const int st = g < static_cast<uint64_t>(kStage) ? static_cast<int>(g) : kStage;
-    hipLaunchKernelGGL(sum_chunks_kernel, dim3(st), dim3(kBlock), 0, s, partials, static_cast<int>(g), stage);
-    SYK_HIP(hipGetLastError());
-    launch_reduce_partials(stage, st, 1, beta2_out, s);
+    launch_publish_sum(stage, st, dst, dst_host, s);
 }
 
 template <typename T>
@@ -448,18 +477,30 @@ __device__ inline void store_unit(float4 *p, const double (&acc)[4]) {
 }
 __device__ inline void store_unit(double2 *p, const double (&acc)[4]) { *p = double2{acc[0], acc[1]}; }
 
-template <typename T>
-__global__ void __launch_bounds__(kBlock) combine_kernel(const V2<T> *__restrict__ basis, uint64_t stride, int nb,
-                                                         const double *__restrict__ coef, V2<T> *__restrict__ out,
+struct CombineDev {               // coefficients in device memory
+    const double *c;
+    __device__ double operator[](int k) const { return c[k]; }
+};
+struct CombineArgs {              // coefficients passed by value (no copy to enqueue first)
+    double c[2 * kCombineArgs];
+    __device__ double operator[](int k) const { return c[k]; }
+};
+
+// vector 0 of the sum is v0 (it may be `out`: each thread reads its unit of every vector before
+// it writes it), vector k >= 1 sits at basis + k stride
+template <typename T, typename C>
+__global__ void __launch_bounds__(kBlock) combine_kernel(const V2<T> *v0, const V2<T> *__restrict__ basis,
+                                                         uint64_t stride, int nb, const C coef, V2<T> *out,
                                                          uint64_t n) {
     using W = typename Wide<T>::type;
-    const W *bw = reinterpret_cast<const W *>(basis);
+    const W *bw = reinterpret_cast<const W *>(basis), *b0 = reinterpret_cast<const W *>(v0);
     W *ow = reinterpret_cast<W *>(out);
     const uint64_t nw = n / Wide<T>::amps, sw = stride / Wide<T>::amps;
     for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < nw;
          i += static_cast<uint64_t>(gridDim.x) * kBlock) {
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        int k = 0;
+        cmac(acc, coef[0], coef[1], b0[i]);
+        int k = 1;
         for (; k + kUnroll <= nb; k += kUnroll) {
             W b[kUnroll];
 #pragma unroll
@@ -472,16 +513,32 @@ __global__ void __launch_bounds__(kBlock) combine_kernel(const V2<T> *__restrict
     }
 }
 
-template <typename T>
-void launch_combine(const T *basis, uint64_t stride, int nb, const double *coef_dev, T *out, uint64_t n,
+template <typename T, typename C>
+static void combine(const T *v0, const T *basis, uint64_t stride, int nb, const C &coef, T *out, uint64_t n,
                     hipStream_t s) {
     if (n % Wide<T>::amps != 0 || stride % Wide<T>::amps != 0 || reinterpret_cast<uintptr_t>(basis) % 16 != 0 ||
-        reinterpret_cast<uintptr_t>(out) % 16 != 0)
+        reinterpret_cast<uintptr_t>(v0) % 16 != 0 || reinterpret_cast<uintptr_t>(out) % 16 != 0)
         fail(SYK_EDEVICE, "combine needs 16-byte aligned vectors of whole 16-byte units");
-    hipLaunchKernelGGL(combine_kernel<T>, dim3(grid_for(n / Wide<T>::amps)), dim3(kBlock), 0, s,
-                       reinterpret_cast<const V2<T> *>(basis), stride, nb, coef_dev,
+    hipLaunchKernelGGL((combine_kernel<T, C>), dim3(grid_for(n / Wide<T>::amps)), dim3(kBlock), 0, s,
+                       reinterpret_cast<const V2<T> *>(v0), reinterpret_cast<const V2<T> *>(basis), stride, nb, coef,
                        reinterpret_cast<V2<T> *>(out), n);
     SYK_HIP(hipGetLastError());
+}
+
+template <typename T>
+void launch_combine(const T *v0, const T *basis, uint64_t stride, int nb, const double *coef_dev, T *out, uint64_t n,
+                    hipStream_t s) {
+    combine<T>(v0, basis, stride, nb, CombineDev{coef_dev}, out, n, s);
+}
+
+template <typename T>
+void launch_combine_args(const T *v0, const T *basis, uint64_t stride, int nb, const double *coef, T *out, uint64_t n,
+                         hipStream_t s) {
+    if (nb < 1 || nb > kCombineArgs) fail(SYK_EDEVICE, "too many vectors for coefficients by value");
+    CombineArgs a;
+    for (int k = 0; k < 2 * nb; ++k) a.c[k] = coef[k];
+    for (int k = 2 * nb; k < 2 * kCombineArgs; ++k) a.c[k] = 0.0;
+    combine<T>(v0, basis, stride, nb, a, out, n, s);
 }
 
 // partials[p][k] = sum_i conj(v_k[i]) w[i] for k < nb (complex, width 2 nb)
@@ -550,10 +607,13 @@ void launch_subtract_proj(T *w, const T *basis, uint64_t stride, int nb, const d
                                           hipStream_t);                                                            \
     template void launch_lanczos_orth2<T>(T *, const T *, const double *, uint64_t, double *, int, hipStream_t);   \
     template void launch_lanczos_normalize<T>(T *, const double *, uint64_t, hipStream_t);                         \
-    template void launch_lanczos_residual<T>(T *, const T *, const double *, const double *, int, uint64_t,          \
-                                             double *, uint64_t, double *, double *, hipStream_t);              \
+    template void launch_lanczos_residual<T>(T *, const T *, double *, double *, const double *, int,              \
+                                             const double *, int, uint64_t, double *, int, hipStream_t);           \
     template void launch_scale_copy<T>(const T *, T *, uint64_t, double, hipStream_t);                             \
-    template void launch_combine<T>(const T *, uint64_t, int, const double *, T *, uint64_t, hipStream_t);         \
+    template void launch_combine<T>(const T *, const T *, uint64_t, int, const double *, T *, uint64_t,            \
+                                    hipStream_t);                                                                  \
+    template void launch_combine_args<T>(const T *, const T *, uint64_t, int, const double *, T *, uint64_t,       \
+                                         hipStream_t);                                                             \
     template void launch_subtract_proj<T>(T *, const T *, uint64_t, int, const double *, uint64_t, hipStream_t);   \
     template void launch_multi_dot_partials<T>(const T *, uint64_t, int, const T *, uint64_t, double *, int,       \
                                                hipStream_t);

@@ -14,6 +14,8 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <mutex>
+#include <thread>
 
 #include "krylov.hpp"
 
@@ -22,10 +24,9 @@ namespace syk {
 // ------------------------------------------------------------------ tridiagonal eigensolver
 // Implicit QL iteration with shifts for a real symmetric tridiagonal matrix (Bowdler,
 // Martin, Reinsch & Wilkinson, Numer. Math. 11 (1968)): d <- eigenvalues, Z <- orthonormal
-// eigenvectors (column k of Z, row-major n x n).  e[i] couples d[i] and d[i+1].
-bool tridiag_eig(int n, std::vector<double> &d, std::vector<double> e, std::vector<double> &Z) {
-    Z.assign(static_cast<size_t>(n) * n, 0.0);
-    for (int i = 0; i < n; ++i) Z[static_cast<size_t>(i) * n + i] = 1.0;
+// eigenvectors (column k of Z, row-major).  e[i] couples d[i] and d[i+1].  Z holds `rows` rows of
+// the identity on entry (all n of them, or those whose eigenvector components are wanted).
+static bool tridiag_ql(int n, std::vector<double> &d, std::vector<double> e, std::vector<double> &Z, int rows) {
     e.resize(n, 0.0);
     e[n - 1] = 0.0;
     const double eps = 2.220446049250313e-16;
@@ -64,7 +65,7 @@ bool tridiag_eig(int n, std::vector<double> &d, std::vector<double> e, std::vect
                 p = s * r;
                 d[i + 1] = g + p;
                 g = c * r - b;
-                for (int k = 0; k < n; ++k) {
+                for (int k = 0; k < rows; ++k) {
                     double *row = &Z[static_cast<size_t>(k) * n];
                     const double zf = row[i + 1];
                     row[i + 1] = s * row[i] + c * zf;
@@ -78,6 +79,30 @@ bool tridiag_eig(int n, std::vector<double> &d, std::vector<double> e, std::vect
         }
     }
     return true;
+}
+
+bool tridiag_eig(int n, std::vector<double> &d, std::vector<double> e, std::vector<double> &Z) {
+    Z.assign(static_cast<size_t>(n) * n, 0.0);
+    for (int i = 0; i < n; ++i) Z[static_cast<size_t>(i) * n + i] = 1.0;
+    return tridiag_ql(n, d, std::move(e), Z, n);
+}
+
+TriLast::TriLast(int n, const double *alpha, const double *beta_off) : lam_(alpha, alpha + n), w_(n) {
+    std::vector<double> e(std::max(n, 1), 0.0), Z(2 * static_cast<size_t>(n), 0.0);
+    for (int i = 0; i + 1 < n; ++i) e[i] = beta_off[i];
+    Z[0] = 1.0;                                    // row 0 and row n - 1 of the identity
+    Z[2 * static_cast<size_t>(n) - 1] = 1.0;
+    ok_ = tridiag_ql(n, lam_, std::move(e), Z, 2);
+    for (int k = 0; k < n; ++k) {
+        w_[k] = Z[k] * Z[static_cast<size_t>(n) + k];
+        if (!std::isfinite(lam_[k])) ok_ = false;
+    }
+}
+
+double TriLast::last(std::complex<double> z) const {
+    std::complex<double> acc = 0.0;
+    for (size_t k = 0; k < lam_.size(); ++k) acc += std::exp(z * lam_[k]) * w_[k];
+    return std::abs(acc);
 }
 
 TriExp::TriExp(int n, const double *alpha, const double *beta_off) : n_(n) {
@@ -159,11 +184,21 @@ static size_t basis_stride_bytes(uint64_t n, size_t elem_bytes) {
     return ((static_cast<size_t>(n) * 2 * elem_bytes + 255) & ~static_cast<size_t>(255)) + 4096;
 }
 
+// partial sums of the fused step: the apply's, one per workgroup, and, above 2^21 amplitudes in
+// the same buffer once alpha_j is formed, the residual pass's, one per 256 amplitudes
+constexpr uint64_t kBigBlock = 1ULL << 21;
+static size_t fused_partials(uint64_t n) {
+    return std::max<uint64_t>(lanczos_partials_max(log2_of(n)), n > kBigBlock ? n / 256 : 0);
+}
+// workgroups (and partial sums) of a residual pass up to 2^21 amplitudes, at most: every workgroup
+// of the next pass may add them up
+constexpr int kNormParts = 1024;
+
 size_t krylov_workspace_bytes(uint64_t n, int m, size_t elem_bytes) {
     const size_t vec = basis_stride_bytes(n, elem_bytes);
     const size_t part = static_cast<size_t>(reduction_blocks(n)) * 2 * (m + 2) * sizeof(double);
     const size_t scal = static_cast<size_t>(8 * (m + 4)) * sizeof(double);
-    const size_t fused = static_cast<size_t>(lanczos_partials_max(log2_of(n))) * 4 * sizeof(double);
+    const size_t fused = (fused_partials(n) + kNormParts) * sizeof(double);
     auto up = [](size_t b) { return (b + 255) & ~static_cast<size_t>(255); };
     return static_cast<size_t>(m + 1) * up(vec) + up(part) + up(scal) + up(fused);
 }
@@ -183,7 +218,88 @@ KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, cha
     coef_ = beta2_ + (m + 2);                 // 2 (m+2)
     scratch_ = coef_ + 2 * (m + 2);           // 2 (m+2)
     p += up(static_cast<size_t>(8 * (m + 4)) * sizeof(double));
-    fused_ = reinterpret_cast<double *>(p);   // 4 per tile
+    fused_ = reinterpret_cast<double *>(p);
+    norms_ = fused_ + fused_partials(n);
+    direct_ = !h_.tiled<T>();
+    big_ = n > kBigBlock;
+    n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ && !direct_ ? n / 256 : kNormParts));
+}
+
+template <typename T>
+KrylovRun<T>::~KrylovRun() {
+    // steps enqueued ahead of the last check may still store to the pinned scalars
+    if (pending_) ignore_status(hipStreamSynchronize(s_));
+}
+
+// ------------------------------------------------------------------ pinned scalars
+namespace {
+std::mutex pin_mu;
+std::vector<double *> *pin_pool() {
+    static auto *v = new std::vector<double *>();   // never destroyed: no HIP calls at exit
+    return v;
+}
+// what an empty slot holds: a NaN whose payload no arithmetic produces
+const uint64_t kEmptySlot = 0x7ff8a5a5deadbeefULL;
+}  // namespace
+
+HostScalars::HostScalars() {
+    {
+        std::lock_guard<std::mutex> g(pin_mu);
+        if (!pin_pool()->empty()) {
+            p_ = pin_pool()->back();
+            pin_pool()->pop_back();
+        }
+    }
+    if (!p_) SYK_HIP(hipHostMalloc(reinterpret_cast<void **>(&p_), 2 * kSlots * sizeof(double), hipHostMallocPortable));
+    void *d = nullptr;
+    const hipError_t e = hipHostGetDevicePointer(&d, p_, 0);
+    if (e != hipSuccess) {
+        std::lock_guard<std::mutex> g(pin_mu);
+        pin_pool()->push_back(p_);
+        hip_check(e, "hipHostGetDevicePointer");
+    }
+    dev_ = static_cast<double *>(d);
+}
+
+HostScalars::~HostScalars() {
+    std::lock_guard<std::mutex> g(pin_mu);
+    pin_pool()->push_back(p_);
+}
+
+void HostScalars::trim() {
+    std::lock_guard<std::mutex> g(pin_mu);
+    for (double *p : *pin_pool()) ignore_status(hipHostFree(p));
+    pin_pool()->clear();
+}
+
+void HostScalars::next() {
+    set_ ^= 1;
+    for (int i = 0; i < kSlots; ++i) std::memcpy(p_ + set_ * kSlots + i, &kEmptySlot, sizeof(double));
+}
+
+double HostScalars::wait(const double *slot, hipStream_t s) const {
+    const volatile uint64_t *q = reinterpret_cast<const volatile uint64_t *>(slot);
+    uint64_t b;
+    for (uint64_t spin = 0; (b = *q) == kEmptySlot; ++spin) {
+        if (spin < 4096) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        if (spin % 256 == 0) {
+            // the kernel that stores the slot is on the stream: once the stream has drained
+            // (or failed) there is nothing to wait for
+            const hipError_t e = hipStreamQuery(s);
+            if (e != hipErrorNotReady) {
+                hip_check(e, "Lanczos step");
+                b = *q;
+                break;
+            }
+        }
+        std::this_thread::yield();
+    }
+    double v;
+    std::memcpy(&v, &b, sizeof v);
+    return v;
 }
 
 template <typename T>
@@ -198,34 +314,11 @@ double KrylovRun<T>::norm(const T *v) {
     return std::sqrt(h);
 }
 
-// one Lanczos iteration j: fills slot j+1, alpha[j], beta2[j+1]
+// one unfused Lanczos iteration j: fills slot j+1, alpha[j], beta2[j+1]
 template <typename T>
 bool KrylovRun<T>::iterate(int j, int reorth) {
     T *vj = vec(j);
     T *w = vec(j + 1);
-    if (reorth == 0 && h_.tiled<T>()) {
-        // fused step: the apply epilogue forms w = H v_j - beta v_{j-1} and the sums for
-        // alpha_j and beta_j; one more pass normalises
-        // basis slots hold u_i unnormalised (||u_i|| = beta_{i-1}); the scales enter the
-        // apply epilogue, the residual pass and the recombination coefficients
-        LanczosFuse<T> lf;
-        lf.vprev = j > 0 ? vec(j - 1) : nullptr;
-        lf.vcur = vj;
-        lf.beta2 = beta2_;
-        lf.j = j;
-        lf.partials = fused_;
-        if (timer_) timer_->begin(s_);
-        const int np = apply_block_lanczos<T>(h_, blk_, rot_, vj, w, lf, s_);
-        if (timer_) timer_->end(s_);
-        launch_lanczos_scalars(fused_, np, alpha_ + 2 * j, nullptr, s_);
-        // alpha_j is formed: the epilogue's partials buffer takes the residual's partials
-        // (the stage buffer needs 512 doubles; tiled blocks have at least 2^18 amplitudes)
-        if (static_cast<size_t>(n_part_) * 2 * (m_ + 2) < 512) fail(SYK_EDEVICE, "partials buffer too small");
-        launch_lanczos_residual<T>(w, vj, alpha_ + 2 * j, beta2_, j, n_, fused_,
-                                   lanczos_partials_max(log2_of(n_)) * 4, partials_, beta2_ + j + 1, s_);
-        unnormalised_ = true;
-        return false;
-    }
     if (timer_) timer_->begin(s_);
     apply_block<T>(h_, blk_, rot_, vj, w, 1, n_, s_);
     if (timer_) timer_->end(s_);
@@ -311,10 +404,192 @@ bool KrylovRun<T>::partial_estimate(int j) {
     return due;
 }
 
+// largest fraction f <= remaining with err(f) <= tol f (bisection in log f)
+template <typename T>
+template <typename E>
+double KrylovRun<T>::bisect(const E &err, double remaining, double tol) {
+    double lo = 0.0, hi = remaining;
+    for (int it = 0; it < 200; ++it) {
+        const double mid = (lo == 0.0) ? hi * 0.5 : std::sqrt(lo * hi);
+        if (err(mid) <= tol * mid)
+            lo = mid;
+        else
+            hi = mid;
+        if (lo > 0.0 && hi / lo < 1.0 + 1e-3) break;
+        if (lo == 0.0 && hi < 1e-14 * remaining) break;
+    }
+    if (lo <= 1e-12 * remaining) fail(SYK_ENOTCONV, "Krylov step size underflow (tolerance too strict)");
+    return lo;
+}
+
 template <typename T>
 void KrylovRun<T>::run(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st) {
+    if (z == std::complex<double>(0.0, 0.0)) {
+        norm(v);                                   // refuses a non-finite vector
+        if (out != v) launch_scale_copy<T>(v, out, n_, 1.0, s_);
+    } else if (o.reorth == 0) {
+        run_fused(z, v, out, o, st);
+    } else {
+        run_plain(z, v, out, o, st);
+    }
+}
+
+// One fused Lanczos step: the apply, whose epilogue forms y = H v_j - beta_{j-1} v_{j-1} and the partial
+// sums of alpha_j, and one pass that writes u_{j+1} = y - alpha_j v_j unnormalised with the
+// partial sums of its norm (the scales 1 / n_i enter wherever a slot is read).  Who adds the partials up:
+//   gather kernels: each reader, behind its own loads (two launches a step);
+//   tiled, up to 2^21 amplitudes: alpha the residual pass, the norm a one-workgroup launch;
+//   larger: launches of their own (too many partials for every workgroup to add).
+// Measured with the host following through pinned scalars instead of copies and stream waits:
+// N = 26, complex128 (12 steps) 582 -> 158 us a propagation, N = 40, complex128 (27 steps) 2187 ->
+// 1433 us; from N = 50 on the apply is nearly all of it (17.9 -> 17.2 ms).
+template <typename T>
+void KrylovRun<T>::enqueue(int j, const T *u0) {
+    const T *u = j == 0 ? u0 : vec(j);
+    T *w = vec(j + 1);
+    LanczosFuse<T> lf;
+    lf.vprev = j == 0 ? nullptr : j == 1 ? u0 : vec(j - 1);
+    lf.vcur = u;
+    lf.norm2 = beta2_;
+    lf.j = j;
+    lf.partials = fused_;
+    lf.norm_parts = norms_;
+    lf.n_parts = n_norm_;
+    lf.norm2_host = host_.dev(host_.norm2(j));
+    pending_ = true;
+    if (timer_) timer_->begin(s_);
+    const int np = apply_block_lanczos<T>(h_, blk_, rot_, u, w, lf, s_);
+    if (timer_) timer_->end(s_);
+    double *al = alpha_ + j, *al_host = host_.dev(host_.alpha(j));
+    const bool reduce = n_norm_ <= kNormParts && np <= kNormParts;
+    if (!reduce) launch_publish_sum(fused_, np, al, al_host, s_);
+    double *parts = n_norm_ <= kNormParts ? norms_ : fused_;      // fused_ is free once alpha_j is formed
+    launch_lanczos_residual<T>(w, u, al, al_host, fused_, reduce ? np : 0, beta2_, j, n_, parts, n_norm_, s_);
+    if (direct_) return;                                             // the next apply sums the norm
+    double *nh = host_.dev(host_.norm2(j + 1));
+    if (n_norm_ <= kNormParts)
+        launch_publish_sum(parts, n_norm_, beta2_ + j + 1, nh, s_);
+    else
+        launch_publish_sum2(parts, n_norm_, partials_, beta2_ + j + 1, nh, s_);
+}
+
+template <typename T>
+void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o,
+                             syk_krylov_stats &st) {
+    // the two-stage sum of large blocks stages 512 doubles in partials_
+    if (n_norm_ > kNormParts && static_cast<size_t>(n_part_) * 2 * (m_ + 2) < 512)
+        fail(SYK_EDEVICE, "partials buffer too small");
+    double remaining = 1.0;
+    const T *cur = v;
+    std::vector<double> al(m_ + 1), n2(m_ + 2), bo(m_ + 1), coef(2 * (m_ + 1));
+    std::vector<std::complex<double>> c(m_ + 1);
+    while (remaining > 0.0) {
+        if (o.max_substeps > 0 && st.substeps >= o.max_substeps)
+            fail(SYK_ENOTCONV, "Krylov propagation exceeded max_substeps");
+        host_.next();
+        pending_ = true;
+        if (direct_) {
+            launch_norm2_partials<T>(cur, n_, norms_, n_norm_, s_);
+        } else {
+            launch_norm2_partials<T>(cur, n_, partials_, n_part_, s_);
+            launch_publish_sum(partials_, n_part_, beta2_, host_.dev(host_.norm2(0)), s_);
+        }
+        int k = 0, enq = 0;        // steps checked, enqueued
+        double tau = 0.0, nrm = 0.0;
+        // log error estimates of the last three checks, newest first: the step at which the
+        // estimate meets the tolerance is extrapolated from them (the decay steepens, so the
+        // last slope and its change are used)
+        double e0 = 0.0, e1 = 0.0, e2 = 0.0;
+        int converges = m_;        // that step, as far as known
+        for (;;) {
+            // Steps are enqueued ahead of the one being checked, so that the GPU does not wait
+            // for the host: two where a step takes microseconds, one for large blocks, none beyond
+            // the step expected to converge (a step enqueued in vain costs its whole time).
+            const int ahead = std::min(k + 1 + (n_ >= kBigBlock ? 1 : 2), std::max(k + 1, converges));
+            while (enq < std::min(ahead, m_)) enqueue(enq++, cur);
+            if (direct_ && enq == k + 1)             // no later step to sum this norm
+                launch_publish_sum(norms_, n_norm_, beta2_ + enq, host_.dev(host_.norm2(enq)), s_);
+            if (k == 0) {
+                n2[0] = host_.wait(host_.norm2(0), s_);
+                if (!std::isfinite(n2[0])) fail(SYK_ENUMERIC, "non-finite norm in Krylov propagation");
+                nrm = std::sqrt(n2[0]);
+            }
+            al[k] = host_.wait(host_.alpha(k), s_);
+            n2[k + 1] = host_.wait(host_.norm2(k + 1), s_);
+            ++k;
+            if (nrm == 0.0) break;
+            double tnorm = 0.0;
+            for (int i = 0; i < k; ++i) {
+                if (!std::isfinite(al[i])) fail(SYK_ENUMERIC, "non-finite Lanczos alpha");
+                tnorm = std::max(tnorm, std::fabs(al[i]));
+            }
+            for (int i = 0; i + 1 < k; ++i) {
+                bo[i] = std::sqrt(n2[i + 1]);
+                tnorm = std::max(tnorm, bo[i]);
+            }
+            const double bk = std::sqrt(n2[k]);
+            if (!std::isfinite(bk)) fail(SYK_ENUMERIC, "non-finite Lanczos beta");
+            const bool breakdown = bk <= 1e-14 * std::max(tnorm, 1e-300);
+            const TriLast tl(k, al.data(), bo.data());
+            if (!tl.ok()) fail(SYK_ENUMERIC, "tridiagonal eigensolver failed");
+            auto err = [&](double f) { return breakdown ? 0.0 : bk * tl.last(f * z); };
+            const double e = err(remaining);
+            if (e <= o.tol * remaining) {
+                tau = remaining;
+                if (breakdown) st.breakdown = 1;
+                break;
+            }
+            if (k == m_) {
+                tau = bisect(err, remaining, o.tol);
+                break;
+            }
+            e2 = e1;
+            e1 = e0;
+            e0 = std::log(e);
+            converges = m_;
+            if (k >= 3) {
+                const double slope = std::min(e0 - e1, 2.0 * (e0 - e1) - (e1 - e2));
+                const double left = e0 - std::log(o.tol * remaining);
+                if (slope < 0.0 && left < -slope * (m_ - k)) converges = k + static_cast<int>(std::ceil(left / -slope));
+            }
+        }
+        if (nrm == 0.0) {                            // e^{zH} 0 = 0
+            if (out != cur) launch_scale_copy<T>(cur, out, n_, 1.0, s_);
+            break;
+        }
+        st.matvecs += k;
+        const TriExp te(k, al.data(), bo.data());
+        if (!te.ok()) fail(SYK_ENUMERIC, "tridiagonal eigensolver failed");
+        te.apply(tau * z, c.data());
+        st.err_est += n2[k] <= 0.0 ? 0.0 : std::sqrt(n2[k]) * std::abs(c[k - 1]);
+        for (int i = 0; i < k; ++i) {
+            // slot i holds u_i = n_i v_i
+            const double ni = std::sqrt(n2[i]);
+            const double sc = ni > 1e-300 ? nrm / ni : 0.0;
+            coef[2 * i] = sc * c[i].real();
+            coef[2 * i + 1] = sc * c[i].imag();
+        }
+        if (k <= kCombineArgs) {
+            launch_combine_args<T>(cur, basis_, vec_stride_, k, coef.data(), out, n_, s_);
+        } else {
+            SYK_HIP(hipMemcpyAsync(coef_, coef.data(), 2 * k * sizeof(double), hipMemcpyHostToDevice, s_));
+            launch_combine<T>(cur, basis_, vec_stride_, k, coef_, out, n_, s_);
+        }
+        st.substeps += 1;
+        remaining -= tau;
+        if (remaining <= 1e-15) break;
+        cur = out;
+    }
+    if (timer_) {
+        SYK_HIP(hipStreamSynchronize(s_));
+        timer_->flush();
+    }
+}
+
+template <typename T>
+void KrylovRun<T>::run_plain(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st) {
     double nrm = norm(v);
-    if (nrm == 0.0 || z == std::complex<double>(0.0, 0.0)) {
+    if (nrm == 0.0) {
         if (out != v) launch_scale_copy<T>(v, out, n_, 1.0, s_);
         return;
     }
@@ -329,7 +604,6 @@ void KrylovRun<T>::run(std::complex<double> z, const T *v, T *out, const syk_kry
             fail(SYK_ENOTCONV, "Krylov propagation exceeded max_substeps");
         launch_scale_copy<T>(cur, vec(0), n_, 1.0 / nrm, s_);
         SYK_HIP(hipMemsetAsync(beta2_, 0, sizeof(double), s_));
-        unnormalised_ = false;
         int k = 0;                 // Lanczos vectors built
         double tau = 0.0;
         bool done = false;
@@ -366,36 +640,21 @@ void KrylovRun<T>::run(std::complex<double> z, const T *v, T *out, const syk_kry
                 done = true;
                 if (breakdown) st.breakdown = 1;
             } else if (k == m_) {
-                // largest fraction f <= remaining with err(f) <= tol f (bisection in log f)
-                double lo = 0.0, hi = remaining;
-                for (int it = 0; it < 200; ++it) {
-                    const double mid = (lo == 0.0) ? hi * 0.5 : std::sqrt(lo * hi);
-                    if (err(mid) <= o.tol * mid)
-                        lo = mid;
-                    else
-                        hi = mid;
-                    if (lo > 0.0 && hi / lo < 1.0 + 1e-3) break;
-                    if (lo == 0.0 && hi < 1e-14 * remaining) break;
-                }
-                if (lo <= 1e-12 * remaining) fail(SYK_ENOTCONV, "Krylov step size underflow (tolerance too strict)");
-                tau = lo;
+                tau = bisect(err, remaining, o.tol);
                 done = true;
             }
             if (done) {
                 te.apply(tau * z, c.data());
                 st.err_est += err(tau);
                 for (int i = 0; i < k; ++i) {
-                    // fused path: slot i >= 1 holds u_i = ||u_i|| v_i
-                    const double ni = std::sqrt(hb[i]);
-                    const double sc = (unnormalised_ && i >= 1) ? (ni > 1e-300 ? nrm / ni : 0.0) : nrm;
-                    coef[2 * i] = sc * c[i].real();
-                    coef[2 * i + 1] = sc * c[i].imag();
+                    coef[2 * i] = nrm * c[i].real();
+                    coef[2 * i + 1] = nrm * c[i].imag();
                 }
             }
         }
         // the combination writes `out`; the start vector already lives in the basis
         SYK_HIP(hipMemcpyAsync(coef_, coef.data(), 2 * k * sizeof(double), hipMemcpyHostToDevice, s_));
-        launch_combine<T>(basis_, vec_stride_, k, coef_, out, n_, s_);
+        launch_combine<T>(vec(0), basis_, vec_stride_, k, coef_, out, n_, s_);
         st.substeps += 1;
         remaining -= tau;
         if (remaining <= 1e-15) break;

@@ -185,14 +185,11 @@ const DeviceTables &Hamiltonian::tables(int blk) {
 }
 
 template <typename T>
-static void apply_gather(Hamiltonian &h, const int (&blks)[2], int nblk, const T *x, T *y, int nvec, uint64_t ld,
-                         hipStream_t s) {
+static int apply_gather(Hamiltonian &h, const int (&blks)[2], int nblk, const T *x, T *y, int nvec, uint64_t ld,
+                        hipStream_t s, const LanczosFuse<T> *lf = nullptr) {
     const uint32_t n = 1u << h.L;
     const DeviceTables *tb[2] = {&h.tables(blks[0]), &h.tables(blks[nblk - 1])};
-    if (tb[0]->head) {
-        launch_apply_dense<T>(tb, nblk, x, y, n, nvec, ld, s);
-        return;
-    }
+    if (tb[0]->head) return launch_apply_dense<T>(tb, nblk, x, y, n, nvec, ld, s, lf);
     GatherTerms<T> g[2];
     for (int b = 0; b < 2; ++b) {
         if constexpr (sizeof(T) == 4)
@@ -202,7 +199,7 @@ static void apply_gather(Hamiltonian &h, const int (&blks)[2], int nblk, const T
         g[b].n_real = tb[b]->n_real;
         g[b].K = tb[b]->K;
     }
-    launch_apply_gather<T>(g, nblk, x, y, n, nvec, ld, s);
+    return launch_apply_gather<T>(g, nblk, x, y, n, nvec, ld, s, lf);
 }
 
 template <>
@@ -316,7 +313,10 @@ template void apply_block<double>(Hamiltonian &, int, int, const double *, doubl
 template <typename T>
 int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s) {
-    if (!h.tiled<T>()) fail(SYK_EDEVICE, "the fused Lanczos step needs a tiled block");
+    if (!h.tiled<T>()) {
+        if (rot != 0) fail(SYK_EDEVICE, "rotated layouts are only planned for tiled blocks");
+        return apply_gather<T>(h, {blk, blk}, 1, x, y, 1, 1ULL << h.L, s, &lf);
+    }
     const ApplyPlan &pl = h.plan<T>(blk, rot, h.variant<T>());
     if (pl.n_wg > lanczos_partials_max(h.L)) fail(SYK_EDEVICE, "partials buffer too small");
     launch_apply_tiled<T>(pl, x, y, 1, 1ULL << h.L, s, &lf);
