@@ -9,7 +9,7 @@
 //    form a coset of Wx, those resident on the whole GPU a coset of Wg (workgroups are
 //    dispatched round-robin over the 8 XCDs).  Partner tiles of two groups g, g' coincide
 //    across resident workgroups iff g ^ g' lies in the subspace, so the subspaces are
-//    grown greedily from the most frequent differences of partner offsets, and groups are
+//    grown greedily from the most frequent differences of partner offsets, and partners are
 //    visited class by class.
 //  * cost model: L2 requests scale with the number of groups D, L2 misses with the number
 //    of classes modulo Wx; the rotation minimising D + 2 * classes_x + classes_g / 2 is
@@ -332,8 +332,16 @@ HostPlan build_host_plan(const std::vector<BlockTerm> &terms, int L, int bt, int
     if (sr != 2) hp.meta.resize(hp.meta.size() + (sr ? 4 : 4 + 2 * (rmask + 1)), 0u);   // padding record (prefetch)
     hp.c.push_back(0.0);
 
-    // partner schedule: class by class modulo Wg, then Wx (both with span(H)), then offset
-    Echelon E5, E8;
+    // partner schedule: class by class modulo Wg, then Wx (both with span(H)), then modulo Wx
+    // alone, then by the terms of the step.  A class modulo Wx + span(H) is 2^w sets of the 2^r
+    // tiles that the resident workgroups of an XCD read in one step (8 MiB in four sets of 2 MiB
+    // for four 64 KiB tiles per workgroup, against 4 MiB of L2): with the steps of a set next to each
+    // other its tiles miss L2 once.  Within a set the step with the most terms comes last: the
+    // copy that runs behind it is the first of the next set, which misses.  N = 56, k = 4,
+    // complex64, variant 10 in standard order: 10.4 -> 8.1 ms (seed 2), 11.6 -> 8.9 ms (seed 56); N = 50: 0.76 -> 0.70 ms;
+    // the heaviest-last rule is 1-2% of it.
+    Echelon E5, E8, Ex;
+    for (uint32_t v : c.wx) Ex.add(v);
     for (uint32_t v : c.H) {
         E5.add(v);
         E8.add(v);
@@ -343,12 +351,20 @@ HostPlan build_host_plan(const std::vector<BlockTerm> &terms, int L, int bt, int
         E8.add(v);
     }
     for (uint32_t v : c.wg) E8.add(v);
-    std::vector<std::tuple<uint32_t, uint32_t, uint32_t>> order;
-    for (uint32_t p : c.Pi) order.push_back(std::make_tuple(E8.reduce(p), E5.reduce(p), p));
-    std::sort(order.begin(), order.end());
     const size_t tpw = hp.hvec.size();
+    auto load_of = [&](uint32_t p) {
+        uint32_t t = 0;
+        for (uint32_t hv : hp.hvec) {
+            const auto it = range.find(p ^ hv);
+            if (it != range.end()) t += it->second[2] - it->second[0];
+        }
+        return t;
+    };
+    std::vector<std::tuple<uint32_t, uint32_t, uint32_t, uint32_t, uint32_t>> order;
+    for (uint32_t p : c.Pi) order.push_back(std::make_tuple(E8.reduce(p), E5.reduce(p), Ex.reduce(p), load_of(p), p));
+    std::sort(order.begin(), order.end());
     for (const auto &o : order) {
-        const uint32_t p = std::get<2>(o);
+        const uint32_t p = std::get<4>(o);
         std::vector<std::array<uint32_t, 3>> rs(tpw);
         uint32_t total = 0;
         for (size_t i = 0; i < tpw; ++i) {
