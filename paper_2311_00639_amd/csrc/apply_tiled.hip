@@ -151,15 +151,32 @@ __device__ __forceinline__ void apply_terms_static(typename V2t<T>::type (&acc)[
 }
 
 // Control-block records (record form 2): a wave holds the current partner step's 64-dword
-// control block in one VGPR (lane l = dword l) and reads a record's four dwords with
+// control block in one VGPR (lane l = dword l) and reads a record's words with
 // readlane into scalar registers, so the term loop issues no scalar memory load (those
 // share the LDS reads' counter and would make every LDS wait also wait for them).
-// Record: (thread bits of x | xr << 24, thread bits of z | sign mask << 24, z >> BT,
-// coefficient: one dword for float, two for double); bit r of the sign mask is the
-// parity of r & zr.
+// Record, as uploaded: LDS byte mask of the partner (thread and register bits of x) | register sign
+// mask << 24, the bits of z below and above the register bits side by side, the coefficient (one
+// dword for float, two for double); bit r of the sign mask is the parity of r & zr.
+// tz: the thread's and its output tile's index bits, laid out as the record's z word; tb8: the
+// thread's LDS byte offset.  Vector operations per term (complex64, 8 registers): 37, 23 without
+// register bits, of which 16 are the products; with separate thread and tile words and the sign
+// mask expanded on the scalar unit it was 42 and 26, and 22 scalar operations more (N = 50, k = 4,
+// variant 10: 0.702 -> 0.625 ms; N = 56: 8.06 -> 7.60 ms; N = 46 complex128: 0.307 -> 0.283 ms).
+template <typename T, int J>
+__device__ __forceinline__ T block_coef(uint32_t cur, int j, uint32_t par) {
+    // the parity goes to the sign bit: adding 2^31 flips it
+    const uint32_t w2 = __builtin_amdgcn_readlane(cur, J * j + 2);
+    if constexpr (sizeof(T) == 4) {
+        return __uint_as_float((par << 31) + w2);
+    } else {
+        const uint32_t w3 = __builtin_amdgcn_readlane(cur, J * j + 3);
+        return __hiloint2double(static_cast<int>((par << 31) + w3), static_cast<int>(w2));
+    }
+}
+
 template <typename T, int BT, int RB, bool IM>
 __device__ __forceinline__ void block_term(typename V2t<T>::type (&acc)[1 << RB], const typename V2t<T>::type *b,
-                                           uint32_t cur, int j, uint32_t tile, uint32_t tid) {
+                                           uint32_t cur, int j, uint32_t tz, uint32_t tb8, uint32_t signbit) {
     using V = typename V2t<T>::type;
     constexpr int R = 1 << RB;
     constexpr int TB = BT - RB;
@@ -167,29 +184,17 @@ __device__ __forceinline__ void block_term(typename V2t<T>::type (&acc)[1 << RB]
     constexpr int RD = sizeof(T) == 4 ? 4 : 5;          // dwords per record
     const uint32_t w0 = __builtin_amdgcn_readlane(cur, RD * j);
     const uint32_t w1 = __builtin_amdgcn_readlane(cur, RD * j + 1);
-    const uint32_t w2 = __builtin_amdgcn_readlane(cur, RD * j + 2);
-    const uint32_t w3 = __builtin_amdgcn_readlane(cur, RD * j + 3);
-    T c;
-    if constexpr (sizeof(T) == 4) {
-        c = __uint_as_float(w3);
-    } else {
-        const uint32_t w4 = __builtin_amdgcn_readlane(cur, RD * j + 4);
-        c = __hiloint2double(static_cast<int>(w4), static_cast<int>(w3));
-    }
-    const uint32_t xt = w0 & 0xffffffu, xr = w0 >> 24;
-    const uint32_t zt = w1 & 0xffffffu, sm = w1 >> 24;
-    const uint32_t par = (__popc(tile & w2) + __popc(tid & zt)) & 1u;
-    const T cl = flip_sign(c, par << 31);
-    const uint32_t base = ((tid ^ xt) << (SH - TB)) | (xr << SH);
+    const T cl = block_coef<T, RD>(cur, j, __popc(tz & w1));
+    const uint32_t base = tb8 ^ (w0 & 0xffffffu);
     const char *bb = reinterpret_cast<const char *>(b);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const V q = *reinterpret_cast<const V *>(bb + (base ^ (static_cast<uint32_t>(r) << SH)));
-        // the register sign stays a scalar operand: one vector XOR per register (output
-        // register 0 never changes sign: r & zr = 0)
-        uint32_t sg = ((sm >> r) & 1u) << 31;
+        // one scalar shift and one vector operation per register sign (output register 0 never
+        // changes sign: r & zr = 0)
+        uint32_t sg = w0 << (7 - r);
         asm("" : "+s"(sg));
-        const T cr = r == 0 ? cl : flip_sign(cl, sg);
+        const T cr = r == 0 ? cl : flip_sign(cl, sg & signbit);
         if (IM) {
             acc[r].x -= cr * q.y;
             acc[r].y += cr * q.x;
@@ -205,26 +210,16 @@ __device__ __forceinline__ void block_term(typename V2t<T>::type (&acc)[1 << RB]
 // register sign.
 template <typename T, int BT, int RB, bool IM>
 __device__ __forceinline__ void block_term_plain(typename V2t<T>::type (&acc)[1 << RB],
-                                                 const typename V2t<T>::type *b, uint32_t cur, int j, uint32_t tile,
-                                                 uint32_t tid) {
+                                                 const typename V2t<T>::type *b, uint32_t cur, int j, uint32_t tz,
+                                                 uint32_t tb8) {
     using V = typename V2t<T>::type;
     constexpr int R = 1 << RB;
     constexpr int TB = BT - RB;
     constexpr int RD = sizeof(T) == 4 ? 4 : 5;          // dwords per record
     const uint32_t w0 = __builtin_amdgcn_readlane(cur, RD * j);
     const uint32_t w1 = __builtin_amdgcn_readlane(cur, RD * j + 1);
-    const uint32_t w2 = __builtin_amdgcn_readlane(cur, RD * j + 2);
-    const uint32_t w3 = __builtin_amdgcn_readlane(cur, RD * j + 3);
-    T c;
-    if constexpr (sizeof(T) == 4) {
-        c = __uint_as_float(w3);
-    } else {
-        const uint32_t w4 = __builtin_amdgcn_readlane(cur, RD * j + 4);
-        c = __hiloint2double(static_cast<int>(w4), static_cast<int>(w3));
-    }
-    const uint32_t par = (__popc(tile & w2) + __popc(tid & (w1 & 0xffffffu))) & 1u;
-    const T cl = flip_sign(c, par << 31);
-    const V *bs = b + (tid ^ (w0 & 0xffffffu));
+    const T cl = block_coef<T, RD>(cur, j, __popc(tz & w1));
+    const V *bs = reinterpret_cast<const V *>(reinterpret_cast<const char *>(b) + (tb8 ^ w0));
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const V q = bs[r << TB];
@@ -396,6 +391,12 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
         static_assert(NBUF == 2 && RB <= 3, "control blocks: 2 buffers, at most 8 registers per thread");
         const uint32_t *blocks = static_cast<const uint32_t *>(recs);
         const uint32_t lane = tid & 63u;
+        const uint32_t tb8 = tid * static_cast<uint32_t>(sizeof(V));
+        uint32_t signbit = 0x80000000u;
+        asm("" : "+v"(signbit));           // in a VGPR: a term's sign operation has one scalar operand
+        uint32_t tz[TPW];
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) tz[i] = tid | ((t0 ^ hs.h[i]) << (BT - RB));
         dma_tile<T, BT, RB>(partner(0), b0, tid);
         uint32_t blk0 = blocks[lane], blk1 = 0;
         auto terms_blk = [&](const V *b, uint32_t cur) __attribute__((always_inline)) {
@@ -404,7 +405,6 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
             int j = 0;
             static_for<0, TPW>([&](auto ic) __attribute__((always_inline)) {
                 constexpr int i = decltype(ic)::value;
-                const uint32_t tile = t0 ^ hs.h[i];
                 const int nre = static_cast<int>((cnt >> (8 * i)) & 15u);
                 const int nim = static_cast<int>((cnt >> (8 * i + 4)) & 15u);
                 const int pre = static_cast<int>((pln >> (8 * i)) & 15u);
@@ -412,10 +412,10 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
                 // a tile without records in this step (common: about 2.8 records per step over
                 // four tiles) costs one test instead of four
                 if (((cnt >> (8 * i)) & 0xffu) == 0u) return;
-                for (const int e = j + pre; j < e; ++j) block_term_plain<T, BT, RB, false>(acc[i], b, cur, j, tile, tid);
-                for (const int e = j + nre - pre; j < e; ++j) block_term<T, BT, RB, false>(acc[i], b, cur, j, tile, tid);
-                for (const int e = j + pim; j < e; ++j) block_term_plain<T, BT, RB, true>(acc[i], b, cur, j, tile, tid);
-                for (const int e = j + nim - pim; j < e; ++j) block_term<T, BT, RB, true>(acc[i], b, cur, j, tile, tid);
+                for (const int e = j + pre; j < e; ++j) block_term_plain<T, BT, RB, false>(acc[i], b, cur, j, tz[i], tb8);
+                for (const int e = j + nre - pre; j < e; ++j) block_term<T, BT, RB, false>(acc[i], b, cur, j, tz[i], tb8, signbit);
+                for (const int e = j + pim; j < e; ++j) block_term_plain<T, BT, RB, true>(acc[i], b, cur, j, tz[i], tb8);
+                for (const int e = j + nim - pim; j < e; ++j) block_term<T, BT, RB, true>(acc[i], b, cur, j, tz[i], tb8, signbit);
             });
         };
         for (int k0 = 0; k0 < n_pi; k0 += 2) {

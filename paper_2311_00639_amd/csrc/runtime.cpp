@@ -252,7 +252,7 @@ const ApplyPlan &Hamiltonian::plan(int blk, int rot, int variant) {
     if (p.pi) return p;
     HostPlan hp = build_host_plan(block_terms[blk], L, tv.bt, tv.rb, tv.nbuf, tv.pf, rot, 2 * sizeof(T),
                                   resident_bits(tv), tv.sr, tv.w);
-    upload_plan(hp, tv.bt, tv.rb, p, slab);
+    upload_plan(hp, tv.bt, tv.rb, p, slab, tv.sr, 2 * sizeof(T));
     p.variant = variant;
     return p;
 }
