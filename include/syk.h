@@ -265,11 +265,12 @@ syk_status syk_green(const syk_ham *h, int n, double beta, const double *t, int 
 /* Many small-N realisations and random vectors in one persistent launch: the OTOC of
  * syk_otoc for every item (W = chi_i, V = chi_j) at a common beta and t grid, nvec Haar
  * vectors each (vector v of item r uses syk_haar_state(N, state_seed, v)), complex64
- * states with double reductions and small exponential.  One workgroup runs one (item,
- * vector) job at a time, entirely on the device (Haar state, Majorana insertions, Lanczos
- * propagators with step control, overlaps), taking jobs from a device counter until none
- * is left.  The launch shape (threads per workgroup, LDS chunk, workgroups per CU) is
- * chosen by timing the eligible shapes on a sample of the batch unless `variant` >= 0.
+ * states with double reductions and small exponential.  A workgroup runs one part of an
+ * (item, vector) job at a time, one parity block's chain over a range of t points, entirely on
+ * the device (Haar state, Majorana insertions, Lanczos propagators with step control,
+ * overlaps), taking parts from a device counter, the most expensive first, until none is left;
+ * results do not depend on the cut.  The launch shape (threads per workgroup, LDS chunk,
+ * workgroups per CU) follows from the block sizes unless `variant` >= 0.
  * Block sizes: 8 <= N/2 - 1 <= 15 (N from 18 to 32) for the shapes that serve them. */
 typedef struct {
     int N;                 /* Majoranas (even) */
@@ -285,15 +286,15 @@ typedef struct {
     double beta;
     int m;                 /* Krylov dimension, 2..60 */
     double tol;            /* per-propagation tolerance (> 0) */
-    int variant;           /* launch shape, -1 = timed choice */
+    int variant;           /* launch shape, -1 = chosen by the block sizes */
     int max_substeps;      /* per job over all its propagations, 0 = 20000 */
 } syk_batch_opts;
 
 typedef struct {
-    long long matvecs;     /* over all jobs */
+    long long matvecs;     /* over all jobs (steps that a cut repeats counted once) */
     int n_jobs, slots, variant;
     double kernel_ms;      /* the persistent launch, HIP events */
-    double tuned_ms[3];    /* sample timings of shapes 0..2 (-1: not timed) */
+    double tuned_ms[3];    /* -1 (shapes are not timed) */
     double seconds;        /* wall time of the call */
 } syk_batch_stats;
 

@@ -1,10 +1,13 @@
 // Host driver of the batched OTOC: term tables and jobs of many realisations, launch-shape
-// choice (timed on a sample of the batch), one persistent launch, per-realisation
+// choice, the cut of the jobs into parts, one persistent launch, per-realisation
 // averaging over vectors and normalisation.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <complex>
+#include <functional>
+#include <map>
+#include <queue>
 #include <vector>
 
 #include "batch.hpp"
@@ -12,15 +15,6 @@
 namespace syk {
 
 namespace {
-
-template <typename U>
-struct DevArray {
-    U *p = nullptr;
-    explicit DevArray(size_t n) { SYK_HIP(hipMalloc(reinterpret_cast<void **>(&p), std::max<size_t>(n, 1) * sizeof(U))); }
-    ~DevArray() { ignore_status(hipFree(p)); }
-    DevArray(const DevArray &) = delete;
-    DevArray &operator=(const DevArray &) = delete;
-};
 
 void majorana_form(int N, int n, uint32_t &x, uint32_t &z, int &w, int &top) {
     if (n == N - 1) {
@@ -33,11 +27,6 @@ void majorana_form(int N, int n, uint32_t &x, uint32_t &z, int &w, int &top) {
     }
 }
 
-struct Launch {
-    const BatchVariant *v;
-    int grid;
-};
-
 int device_cus() {
     int dev = 0, cus = 0;
     SYK_HIP(hipGetDevice(&dev));
@@ -45,38 +34,96 @@ int device_cus() {
     return std::max(cus, 1);
 }
 
-// run jobs [0, n_jobs) of `jobs_d` with variant v; returns kernel milliseconds
-float run_once(const BatchVariant &v, BatchParams p, int n_jobs, int lmax, hipStream_t s, std::vector<char> &hold,
-               float2 *&ws, size_t &ws_cap, unsigned *counter) {
-    const int grid = std::min(n_jobs, device_cus() * v.occ);
-    p.n_jobs = n_jobs;
-    p.vec_stride = std::max<uint64_t>(1ULL << lmax, 64);
-    p.slot_stride = static_cast<uint64_t>(p.m + 5) * p.vec_stride;
-    const size_t need = static_cast<size_t>(grid) * p.slot_stride * sizeof(float2);
-    if (need > ws_cap) {
-        if (ws) SYK_HIP(hipFree(ws));
-        ws = nullptr;
-        ws_cap = 0;
-        SYK_HIP(hipMalloc(reinterpret_cast<void **>(&ws), need));
-        ws_cap = need;
+// Lanczos steps of a propagation over |z| (estimate: the degree of the Chebyshev series of
+// e^{z x} on a spectrum of half width r = 0.05 N)
+double steps_of(double z, int N, double tol) {
+    const double a = z * 0.05 * N / 2.0;
+    double d = 3.0, err = 2.0;
+    while (err > tol && d < 200.0) err *= a / (d++ - 2.0);
+    return d;
+}
+
+// Cuts the jobs into parts for `slots` workgroups, most expensive first.  The makespan cannot fall below
+// the mean load, and a part that takes longer than the mean holds up the end, so parts above a target cost
+// are cut at t points; a cut repeats the incremental propagations before it, so of a few
+// targets the one with the shortest estimated schedule is taken.
+std::vector<BatchPart> make_parts(const std::vector<BatchJob> &jobs, const std::vector<double> &ts, double beta,
+                                  double tol, int slots) {
+    struct Cost {
+        double start;                                   // r0 and r2
+        std::vector<double> inc, full;                  // per t point: advancing r2 and l; r4 and r6
+        double total;
+    };
+    const int nt = static_cast<int>(ts.size());
+    std::map<std::pair<int, int>, Cost> costs;          // by (N, K)
+    double total = 0.0, longest = 0.0;
+    for (const BatchJob &j : jobs) {
+        Cost &c = costs[{j.N, j.K}];
+        if (c.inc.empty()) {
+            // one step: K terms on 2^L amplitudes, vector passes and scalars worth about 12 more terms and
+            // 4096 amplitudes (workgroup barriers, the small exponential)
+            const double step = (j.K + 12.0) * ((1 << j.L) + 4096.0);
+            c.start = step * (steps_of(beta / 8, j.N, tol) + steps_of(beta / 4, j.N, tol));
+            c.total = c.start;
+            for (int k = 0; k < nt; ++k) {
+                const double dt = k ? ts[k] - ts[k - 1] : ts[0];
+                c.inc.push_back(dt > 0.0 ? 2 * step * steps_of(dt, j.N, tol) : 0.0);
+                c.full.push_back(2 * step * steps_of(std::hypot(beta / 4, ts[k]), j.N, tol));
+                c.total += c.inc[k] + c.full[k];
+            }
+        }
+        total += 2 * c.total;
+        longest = std::max(longest, c.total);
     }
-    p.ws = ws;
-    p.counter = counter;
-    SYK_HIP(hipMemsetAsync(counter, 0, sizeof(unsigned), s));
-    hipEvent_t e0, e1;
-    SYK_HIP(hipEventCreate(&e0));
-    SYK_HIP(hipEventCreate(&e1));
-    SYK_HIP(hipEventRecord(e0, s));
-    launch_otoc_batch(v, p, grid, s);
-    SYK_HIP(hipEventRecord(e1, s));
-    SYK_HIP(hipEventSynchronize(e1));
-    float ms = 0.0f;
-    const hipError_t te = hipEventElapsedTime(&ms, e0, e1);
-    ignore_status(hipEventDestroy(e0));
-    ignore_status(hipEventDestroy(e1));
-    SYK_HIP(te);
-    (void)hold;
-    return ms;
+    auto cut = [&](double target) {
+        std::vector<std::pair<double, BatchPart>> parts;
+        for (int ji = 0; ji < static_cast<int>(jobs.size()); ++ji) {
+            const Cost &c = costs.at({jobs[ji].N, jobs[ji].K});
+            double before = c.start;                    // to reach t point k0
+            for (int k0 = 0; k0 < nt;) {
+                double cost = before;
+                int k1 = k0;
+                while (k1 < nt && (k1 == k0 || cost + c.inc[k1] + c.full[k1] <= target)) {
+                    cost += c.inc[k1] + c.full[k1];
+                    before += c.inc[k1++];
+                }
+                for (int A = 0; A < 2; ++A) parts.push_back({cost, BatchPart{ji, A, k0, k1}});
+                k0 = k1;
+            }
+        }
+        std::stable_sort(parts.begin(), parts.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        return parts;
+    };
+    auto makespan = [&](const std::vector<std::pair<double, BatchPart>> &parts) {
+        std::priority_queue<double, std::vector<double>, std::greater<double>> ends;
+        double last = 0.0;
+        for (const auto &p : parts) {
+            double t = p.first;
+            if (static_cast<int>(ends.size()) >= slots) {
+                t += ends.top();
+                ends.pop();
+            }
+            ends.push(t);
+            last = std::max(last, t);
+        }
+        return last;
+    };
+    auto best = cut(1e300);
+    const double mean = total / slots;
+    if (longest > 0.5 * mean) {
+        double span = makespan(best);
+        for (double f : {0.25, 0.35, 0.5, 0.7, 1.0, 1.4, 2.0, 3.0}) {
+            auto p = cut(f * std::max(mean, longest / nt));
+            const double s = makespan(p);
+            if (s < span) {
+                span = s;
+                best = std::move(p);
+            }
+        }
+    }
+    std::vector<BatchPart> out;
+    for (const auto &p : best) out.push_back(p.second);
+    return out;
 }
 
 }  // namespace
@@ -136,77 +183,105 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
     if (o.variant >= 0 && std::find(elig.begin(), elig.end(), o.variant) == elig.end())
         fail(SYK_EINVAL, "requested batch variant does not serve this mix of block sizes");
 
-    DevArray<BatchJob> jobs_d(jobs.size());
-    DevArray<BatchTerm> terms_d(terms.size());
-    DevArray<double> ts_d(ts.size());
-    DevArray<double> F_d(static_cast<size_t>(n_jobs) * ntt * 2);
-    DevArray<unsigned> counter(1);
-    DevArray<int> status_d(jobs.size());
-    DevArray<long long> mv_d(jobs.size());
-    SYK_HIP(hipMemcpy(jobs_d.p, jobs.data(), jobs.size() * sizeof(BatchJob), hipMemcpyHostToDevice));
-    SYK_HIP(hipMemcpy(terms_d.p, terms.data(), terms.size() * sizeof(BatchTerm), hipMemcpyHostToDevice));
-    SYK_HIP(hipMemcpy(ts_d.p, ts.data(), ts.size() * sizeof(double), hipMemcpyHostToDevice));
+    // Launch shape: the widest workgroups (the longest parts end soonest) that still hold four
+    // amplitudes per thread of the largest block; below that the workgroup's fixed costs per step weigh
+    // more than its width.  Kernel times of the eligible shapes (1024, 512, 256 threads), complex64:
+    // 64 realisations x 4 states, N 24-32: 111, 146 ms; N = 28: 32, 33, 59 ms; N = 24: 16.3, 12.9,
+    // 16.0 ms; 256 x 2 at N = 20: -, 11.4, 11.4 ms.
+    int chosen = o.variant;
+    if (chosen < 0) {
+        chosen = elig.back();
+        for (auto v = elig.rbegin(); v != elig.rend(); ++v)
+            if ((1 << lmax) >= 4 * vars[*v].nt) chosen = *v;
+    }
+    const BatchVariant &shape = vars[chosen];
+    const int slots = device_cus() * shape.occ;
+    const std::vector<BatchPart> parts = make_parts(jobs, ts, o.beta, o.tol, slots);
+    const int grid = std::min<int>(static_cast<int>(parts.size()), slots);
 
     BatchParams p{};
-    p.jobs = jobs_d.p;
-    p.terms = terms_d.p;
-    p.ts = ts_d.p;
+    p.n_parts = static_cast<int>(parts.size());
     p.nt = ntt;
     p.m = o.m;
     p.tol = o.tol;
     p.max_substeps = o.max_substeps > 0 ? o.max_substeps : 20000;
-    p.F = F_d.p;
-    p.status = status_d.p;
-    p.matvecs = mv_d.p;
-    float2 *ws = nullptr;
-    size_t ws_cap = 0;
-    std::vector<char> hold;
+    p.vec_stride = std::max<uint64_t>(1ULL << lmax, 64);
+    p.slot_stride = static_cast<uint64_t>(p.m + 5) * p.vec_stride;
+
+    // the thread's cached workspace holds everything (the call synchronises before it returns)
+    DeviceBuffer &ws = thread_workspace(0);
+    size_t need = 0;
+    auto piece = [&](size_t bytes) {
+        const size_t at = need;
+        need += (bytes + 255) & ~static_cast<size_t>(255);
+        return at;
+    };
+    const size_t n_F = static_cast<size_t>(n_jobs) * 2 * ntt * 2;
+    const size_t at_jobs = piece(jobs.size() * sizeof(BatchJob)), at_parts = piece(parts.size() * sizeof(BatchPart));
+    const size_t at_terms = piece(terms.size() * sizeof(BatchTerm)), at_ts = piece(ts.size() * sizeof(double));
+    const size_t at_F = piece(n_F * sizeof(double)), at_res = piece(parts.size() * sizeof(BatchResult));
+    const size_t at_counter = piece(sizeof(unsigned));
+    const size_t at_ws = piece(static_cast<size_t>(grid) * p.slot_stride * sizeof(float2));
+    ws.ensure(need);
+    char *base = ws.ptr();
+    auto put = [&](size_t at, const auto &v) {
+        if (!v.empty())
+            SYK_HIP(hipMemcpyAsync(base + at, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice, s));
+        return base + at;
+    };
+    p.jobs = reinterpret_cast<const BatchJob *>(put(at_jobs, jobs));
+    p.parts = reinterpret_cast<const BatchPart *>(put(at_parts, parts));
+    p.terms = reinterpret_cast<const BatchTerm *>(put(at_terms, terms));
+    p.ts = reinterpret_cast<const double *>(put(at_ts, ts));
+    p.F = reinterpret_cast<double *>(base + at_F);
+    p.results = reinterpret_cast<BatchResult *>(base + at_res);
+    p.counter = reinterpret_cast<unsigned *>(base + at_counter);
+    p.ws = reinterpret_cast<float2 *>(base + at_ws);
+    SYK_HIP(hipMemsetAsync(p.counter, 0, sizeof(unsigned), s));
+    hipEvent_t e0, e1;
+    SYK_HIP(hipEventCreate(&e0));
+    SYK_HIP(hipEventCreate(&e1));
+    std::vector<double> F(n_F);
+    std::vector<BatchResult> res(parts.size());
+    float ms = 0.0f;
     try {
-        int chosen = o.variant >= 0 ? o.variant : elig[0];
-        st.tuned_ms[0] = st.tuned_ms[1] = st.tuned_ms[2] = -1.0;
-        if (o.variant < 0 && elig.size() > 1) {
-            // time each shape on a sample of the batch (its first jobs, the first two t points)
-            BatchParams q = p;
-            q.nt = std::min(ntt, 2);
-            const int sample = std::min(n_jobs, 2 * device_cus());
-            float best = 1e30f;
-            for (int v : elig) {
-                const float ms = run_once(vars[v], q, sample, lmax, s, hold, ws, ws_cap, counter.p);
-                if (v < 3) st.tuned_ms[v] = ms;
-                if (ms < best) {
-                    best = ms;
-                    chosen = v;
-                }
-            }
-        }
-        st.variant = chosen;
-        st.kernel_ms = run_once(vars[chosen], p, n_jobs, lmax, s, hold, ws, ws_cap, counter.p);
-        st.slots = std::min(n_jobs, device_cus() * vars[chosen].occ);
+        SYK_HIP(hipEventRecord(e0, s));
+        launch_otoc_batch(shape, p, grid, s);
+        SYK_HIP(hipEventRecord(e1, s));
+        SYK_HIP(hipEventSynchronize(e1));
+        SYK_HIP(hipEventElapsedTime(&ms, e0, e1));
+        SYK_HIP(hipMemcpyAsync(F.data(), p.F, F.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+        SYK_HIP(hipMemcpyAsync(res.data(), p.results, res.size() * sizeof(BatchResult), hipMemcpyDeviceToHost, s));
+        SYK_HIP(hipStreamSynchronize(s));
     } catch (...) {
-        if (ws) ignore_status(hipFree(ws));
+        ignore_status(hipEventDestroy(e0));
+        ignore_status(hipEventDestroy(e1));
         throw;
     }
-    SYK_HIP(hipFree(ws));
-    std::vector<double> F(static_cast<size_t>(n_jobs) * ntt * 2);
-    std::vector<int> status(jobs.size());
-    std::vector<long long> mv(jobs.size());
-    SYK_HIP(hipMemcpy(F.data(), F_d.p, F.size() * sizeof(double), hipMemcpyDeviceToHost));
-    SYK_HIP(hipMemcpy(status.data(), status_d.p, status.size() * sizeof(int), hipMemcpyDeviceToHost));
-    SYK_HIP(hipMemcpy(mv.data(), mv_d.p, mv.size() * sizeof(long long), hipMemcpyDeviceToHost));
+    ignore_status(hipEventDestroy(e0));
+    ignore_status(hipEventDestroy(e1));
+    st.variant = chosen;
+    st.slots = grid;
+    st.kernel_ms = ms;
+    st.tuned_ms[0] = st.tuned_ms[1] = st.tuned_ms[2] = -1.0;
     st.matvecs = 0;
-    for (int j = 0; j < n_jobs; ++j) {
-        st.matvecs += mv[j];
-        if (status[j] == SYK_ENOTCONV) fail(SYK_ENOTCONV, "batched Krylov propagation did not converge");
-        if (status[j] == SYK_ENUMERIC) fail(SYK_ENUMERIC, "non-finite value in a batched job");
-        if (status[j] != 0) fail(SYK_EUNSUPPORTED, "batched job with an unsupported block size");
+    std::vector<long long> substeps(jobs.size(), 0);
+    for (size_t i = 0; i < parts.size(); ++i) {
+        st.matvecs += res[i].matvecs;
+        substeps[parts[i].job] += res[i].substeps;
+        if (res[i].status == SYK_ENOTCONV || substeps[parts[i].job] > p.max_substeps)
+            fail(SYK_ENOTCONV, "batched Krylov propagation did not converge");
+        if (res[i].status == SYK_ENUMERIC) fail(SYK_ENUMERIC, "non-finite value in a batched job");
+        if (res[i].status != 0) fail(SYK_EUNSUPPORTED, "batched job with an unsupported block size");
     }
     // per realisation: mean over vectors, normalised by t = 0
     const int off = prepend ? 1 : 0;
     for (int r = 0; r < n_items; ++r) {
         std::vector<std::complex<double>> acc(ntt, 0.0);
         for (int v = 0; v < o.nvec; ++v) {
-            const double *f = F.data() + static_cast<size_t>(r * o.nvec + v) * ntt * 2;
-            for (int k = 0; k < ntt; ++k) acc[k] += std::complex<double>(f[2 * k], f[2 * k + 1]);
+            const double *u = F.data() + static_cast<size_t>(r * o.nvec + v) * 2 * ntt * 2, *d = u + 2 * ntt;
+            for (int k = 0; k < ntt; ++k)
+                acc[k] += std::complex<double>(u[2 * k] + d[2 * k], u[2 * k + 1] + d[2 * k + 1]);
         }
         for (auto &a : acc) a /= static_cast<double>(o.nvec);
         const double f0 = acc[0].real();

@@ -1,9 +1,10 @@
 // Batched OTOC: many small-N realisations and random vectors in one persistent launch.
 //
-// A job is one (realisation, Haar vector) pair: both parity-block chains of the OTOC of
-// Eq. (2) over the whole t grid (the random-state estimator of the supplement).  The grid
-// holds one workgroup per resident slot; each workgroup takes jobs from a device counter
-// until none is left and runs a whole job by itself, with no host round trip: Haar state,
+// A job is one (realisation, Haar vector) pair: the two parity-block chains of the OTOC of
+// Eq. (2) over the t grid (the random-state estimator of the supplement).  The host cuts jobs into
+// parts (one block's chain over a range of t points) and sorts them by cost; the grid
+// holds one workgroup per resident slot; each workgroup takes parts from a device counter
+// until none is left and runs a whole part by itself, with no host round trip: Haar state,
 // Majorana insertions, overlaps and every Lanczos propagator (matrix-free apply_H with the
 // vector staged in LDS, Lanczos recurrence with double reductions, small exponential,
 // step control, recombination).  Vectors are complex64 in the standard layout; every
@@ -591,40 +592,45 @@ __device__ void prop(Ctx<NT, CHB> &c, int blk, double zr, double zi, gf2 *v) {
     }
 }
 
-// the OTOC chains of one job (both blocks, all t points) into F (nt complex, accumulated)
+// one part: block A's chain of the job, F at the t points [k0, k1)
 template <int NT, int CHB, int L>
-__device__ __attribute__((noinline)) void run_job(Ctx<NT, CHB> &c, double2 *F) {
+__device__ __attribute__((noinline)) void run_part(Ctx<NT, CHB> &c, int A, int k0, int k1, double2 *F) {
     const BatchJob &jb = c.job;
     const double beta = jb.beta;
     gf2 *l = c.vec[0], *r2 = c.vec[1], *r4 = c.vec[2], *tmp = c.vec[3];
-    for (int A = 0; A < 2; ++A) {
-        const int B = 1 - A;
-        haar<NT, CHB, L>(c, A, l);
-        prop<NT, CHB, L>(c, A, -beta / 8.0, 0.0, l);                              // r0
-        gamma<NT, CHB, L>(c, jb.v_top, jb.vx, jb.vz, jb.vw, A, l, r2);            // V_BA r0
-        prop<NT, CHB, L>(c, B, -beta / 4.0, 0.0, r2);
-        double tprev = 0.0;
-        for (int k = 0; k < c.p.nt; ++k) {
-            const double t = c.p.ts[k];
-            const double dt = t - tprev;
-            if (dt > 0.0) {
-                prop<NT, CHB, L>(c, B, 0.0, -dt, r2);
-                prop<NT, CHB, L>(c, A, 0.0, -dt, l);
-            }
-            tprev = t;
-            gamma<NT, CHB, L>(c, jb.w_top, jb.wx, jb.wz, jb.ww, B, r2, r4);       // W_AB r2
-            prop<NT, CHB, L>(c, A, -beta / 4.0, t, r4);
-            gamma<NT, CHB, L>(c, jb.v_top, jb.vx, jb.vz, jb.vw, A, r4, tmp);      // V_BA r4
-            prop<NT, CHB, L>(c, B, -beta / 4.0, -t, tmp);                         // r6
-            gamma<NT, CHB, L>(c, jb.w_top, jb.wx, jb.wz, jb.ww, B, tmp, r4);      // W_AB r6
-            const double2 d = dot<NT, CHB, L>(c, l, r4);
-            if (c.tid == 0) {
-                F[k].x += 0.25 * d.x;
-                F[k].y += 0.25 * d.y;
-            }
-            if (c.status) return;
+    const int B = 1 - A;
+    haar<NT, CHB, L>(c, A, l);
+    prop<NT, CHB, L>(c, A, -beta / 8.0, 0.0, l);                                  // r0
+    gamma<NT, CHB, L>(c, jb.v_top, jb.vx, jb.vz, jb.vw, A, l, r2);                // V_BA r0
+    prop<NT, CHB, L>(c, B, -beta / 4.0, 0.0, r2);
+    long long before = k0 > 0 ? c.matvecs : 0;                                    // another part's
+    int before_sub = k0 > 0 ? c.substeps : 0;
+    double tprev = 0.0;
+    for (int k = 0; k < k1; ++k) {
+        const double t = c.p.ts[k];
+        const double dt = t - tprev;
+        if (dt > 0.0) {
+            prop<NT, CHB, L>(c, B, 0.0, -dt, r2);
+            prop<NT, CHB, L>(c, A, 0.0, -dt, l);
         }
+        tprev = t;
+        if (c.status) return;
+        if (k < k0) {
+            before = c.matvecs;
+            before_sub = c.substeps;
+            continue;
+        }
+        gamma<NT, CHB, L>(c, jb.w_top, jb.wx, jb.wz, jb.ww, B, r2, r4);           // W_AB r2
+        prop<NT, CHB, L>(c, A, -beta / 4.0, t, r4);
+        gamma<NT, CHB, L>(c, jb.v_top, jb.vx, jb.vz, jb.vw, A, r4, tmp);          // V_BA r4
+        prop<NT, CHB, L>(c, B, -beta / 4.0, -t, tmp);                             // r6
+        gamma<NT, CHB, L>(c, jb.w_top, jb.wx, jb.wz, jb.ww, B, tmp, r4);          // W_AB r6
+        const double2 d = dot<NT, CHB, L>(c, l, r4);
+        if (c.tid == 0) F[k] = double2{0.25 * d.x, 0.25 * d.y};
+        if (c.status) return;
     }
+    c.matvecs -= before;
+    c.substeps -= before_sub;
 }
 
 template <int NT, int CHB, int OCC>
@@ -643,12 +649,11 @@ __global__ void __launch_bounds__(NT, OCC * NT / 256) otoc_batch_kernel(BatchPar
         __syncthreads();
         if (tid == 0) job_sh = static_cast<int>(atomicAdd(p.counter, 1u));
         __syncthreads();
-        const int ji = job_sh;
-        if (ji >= p.n_jobs) break;
-        const BatchJob &jb = p.jobs[ji];
-        double2 *F = reinterpret_cast<double2 *>(p.F) + static_cast<size_t>(ji) * p.nt;
-        if (tid == 0)
-            for (int k = 0; k < p.nt; ++k) F[k] = double2{0.0, 0.0};
+        const int pi = job_sh;
+        if (pi >= p.n_parts) break;
+        const BatchPart part = p.parts[pi];
+        const BatchJob &jb = p.jobs[part.job];
+        double2 *F = reinterpret_cast<double2 *>(p.F) + (static_cast<size_t>(part.job) * 2 + part.A) * p.nt;
         Ctx<NT, CHB> c{p, *(LShared<NT> *)(&sh), (lf2 *)(buf), jb, slot, {slot + static_cast<size_t>(p.m + 1) * p.vec_stride,
                                                slot + static_cast<size_t>(p.m + 2) * p.vec_stride,
                                                slot + static_cast<size_t>(p.m + 3) * p.vec_stride,
@@ -665,7 +670,7 @@ __global__ void __launch_bounds__(NT, OCC * NT / 256) otoc_batch_kernel(BatchPar
         switch (jb.L) {
 #define SYK_BL(LL)                                                       \
     case LL:                                                             \
-        if constexpr ((1 << LL) >= NT && (1 << LL) <= 4 * (1 << CHB)) run_job<NT, CHB, LL>(c, F); \
+        if constexpr ((1 << LL) >= NT && (1 << LL) <= 4 * (1 << CHB)) run_part<NT, CHB, LL>(c, part.A, part.k0, part.k1, F); \
         else c.status = 2;                                               \
         break;
             SYK_BL(8)
@@ -681,8 +686,7 @@ __global__ void __launch_bounds__(NT, OCC * NT / 256) otoc_batch_kernel(BatchPar
                 c.status = 2;
         }
         if (tid == 0) {
-            p.status[ji] = c.status;
-            p.matvecs[ji] = c.matvecs;
+            p.results[pi] = BatchResult{c.matvecs, c.substeps, c.status};
         }
     }
 }

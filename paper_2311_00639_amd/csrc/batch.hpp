@@ -16,7 +16,7 @@ struct BatchTerm {
     uint32_t imag;
 };
 
-// one job: a realisation and one Haar vector, both block chains over the whole t grid
+// one job: a realisation and one Haar vector
 struct BatchJob {
     int L, N, K, pad;
     uint32_t term_off[2];               // first term of block U / D in BatchParams::terms
@@ -32,21 +32,34 @@ struct BatchJob {
     uint16_t pad2[2];
 };
 
+// One part of a job, the unit a workgroup takes: the chain that starts in parity block A, for the
+// t points [k0, k1).  A part with k0 > 0 repeats the incremental propagations up to k0 (in the same
+// steps, so its results do not depend on the split); stats count them in the part that owns them.
+struct BatchPart {
+    int job, A, k0, k1;
+};
+
+// what a part reports
+struct BatchResult {
+    long long matvecs;
+    int substeps, status;               // status: 0, SYK_ENOTCONV, SYK_ENUMERIC, SYK_EUNSUPPORTED
+};
+
 struct BatchParams {
     const BatchJob *jobs;
-    int n_jobs;
+    const BatchPart *parts;
+    int n_parts;
     const BatchTerm *terms;
     const double *ts;                   // t grid (t[0] = 0)
     int nt;
     int m;                              // Krylov dimension
     double tol;
-    int max_substeps;                   // per job, over all propagations
+    int max_substeps;                   // per part, over all propagations
     float2 *ws;                         // per slot: (m + 5) vectors of vec_stride amplitudes
     uint64_t slot_stride, vec_stride;   // in amplitudes
-    double *F;                          // per job: nt complex (re, im)
-    unsigned *counter;                  // next job; zero at launch
-    int *status;                        // per job: 0, SYK_ENOTCONV, SYK_ENUMERIC, SYK_EUNSUPPORTED
-    long long *matvecs;                 // per job
+    double *F;                          // per job and block A: nt complex (re, im)
+    unsigned *counter;                  // next part; zero at launch
+    BatchResult *results;               // per part
 };
 
 // launch shape: threads per workgroup, LDS staging chunk 2^chb amplitudes, workgroups per CU
