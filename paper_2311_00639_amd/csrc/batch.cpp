@@ -34,6 +34,37 @@ int device_cus() {
     return std::max(cus, 1);
 }
 
+// one block's terms as the kernel of `shape` reads them (see BatchTerm), and its run bounds
+void add_block(const std::vector<BlockTerm> &bt, int L, const BatchVariant &shape, std::vector<BatchTerm> &terms,
+               std::vector<uint32_t> &runs) {
+    const int lch = std::min(L, shape.chb), lnt = __builtin_ctz(static_cast<unsigned>(shape.nt));
+    const int rc = (1 << lch) / shape.nt, low = batch_low_bits(rc), n_runs = batch_runs(rc);
+    const uint32_t lmask = (1u << low) - 1u, chmask = (1u << lch) - 1u, rmask = static_cast<uint32_t>(rc) - 1u;
+    std::vector<std::pair<uint32_t, int>> order;        // (chunk, phase, low x bits, low z bits), term
+    for (int a = 0; a < static_cast<int>(bt.size()); ++a) {
+        const uint32_t xl = (bt[a].x >> lnt) & lmask, zl = (bt[a].z >> lnt) & lmask;
+        const uint32_t run = (((bt[a].imag ? 1u : 0u) << low | xl) << low) | zl;
+        order.push_back({(bt[a].x >> lch) * static_cast<uint32_t>(n_runs) + run, a});
+    }
+    std::stable_sort(order.begin(), order.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+    size_t t = 0;
+    for (uint32_t ch = 0; ch < (1u << (L - lch)); ++ch) {
+        runs.push_back(static_cast<uint32_t>(t));
+        for (int run = 0; run < n_runs; ++run) {
+            while (t < order.size() && order[t].first == ch * static_cast<uint32_t>(n_runs) + static_cast<uint32_t>(run)) ++t;
+            runs.push_back(static_cast<uint32_t>(t));
+        }
+    }
+    for (const auto &o : order) {
+        const BlockTerm &b = bt[o.second];
+        const uint32_t zr = (b.z >> lnt) & rmask;
+        uint32_t sg = 0;
+        for (uint32_t h = 0; h <= (rmask >> low); ++h) sg |= (__builtin_popcount(h & (zr >> low)) & 1u) << h;
+        terms.push_back(BatchTerm{(b.x & chmask & ~(lmask << lnt)) * 8u,
+                                  (b.z & ((1u << lnt) - 1u)) | (b.z >> lch) << lnt, static_cast<float>(b.c), sg});
+    }
+}
+
 // Lanczos steps of a propagation over |z| (estimate: the degree of the Chebyshev series of
 // e^{z x} on a spectrum of half width r = 0.05 N)
 double steps_of(double z, int N, double tol) {
@@ -136,41 +167,8 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
     if (prepend) ts.insert(ts.begin(), 0.0);
     const int ntt = static_cast<int>(ts.size());
 
-    // term tables and jobs
-    std::vector<BatchTerm> terms;
-    std::vector<BatchJob> jobs;
     int lmax = 0;
-    for (int r = 0; r < n_items; ++r) {
-        const syk_batch_item &it = items[r];
-        Hamiltonian h;
-        build_hamiltonian(h, it.N, it.k, it.seed, it.ensemble);
-        BatchJob jb{};
-        jb.L = h.L;
-        jb.N = h.N;
-        jb.K = h.K;
-        lmax = std::max(lmax, h.L);
-        for (int blk = 0; blk < 2; ++blk) {
-            jb.term_off[blk] = static_cast<uint32_t>(terms.size());
-            std::vector<BatchTerm> bts;
-            for (const BlockTerm &bt : h.block_terms[blk])
-                bts.push_back(BatchTerm{bt.x, bt.z, static_cast<float>(bt.c), bt.imag ? 1u : 0u});
-            std::stable_sort(bts.begin(), bts.end(), [](const BatchTerm &a, const BatchTerm &b) { return a.x < b.x; });
-            for (uint32_t g = 0, t = 0; g <= 8; ++g) {
-                while (t < bts.size() && (bts[t].x >> 12) < g) ++t;
-                jb.gstart[blk][g] = static_cast<uint16_t>(g == 8 ? bts.size() : t);
-            }
-            terms.insert(terms.end(), bts.begin(), bts.end());
-        }
-        majorana_form(it.N, it.i, jb.wx, jb.wz, jb.ww, jb.w_top);
-        majorana_form(it.N, it.j, jb.vx, jb.vz, jb.vw, jb.v_top);
-        jb.beta = o.beta;
-        for (int v = 0; v < o.nvec; ++v) {
-            jb.base = splitmix_mix(it.state_seed + static_cast<uint64_t>(v + 1) * 0x9E3779B97F4A7C15ULL);
-            jobs.push_back(jb);
-        }
-    }
-    const int n_jobs = static_cast<int>(jobs.size());
-
+    for (int r = 0; r < n_items; ++r) lmax = std::max(lmax, items[r].N / 2 - 1);
     // eligible launch shapes
     std::vector<int> elig;
     const auto &vars = batch_variants();
@@ -195,6 +193,34 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
             if ((1 << lmax) >= 4 * vars[*v].nt) chosen = *v;
     }
     const BatchVariant &shape = vars[chosen];
+
+    // term tables and jobs
+    std::vector<BatchTerm> terms;
+    std::vector<uint32_t> runs;
+    std::vector<BatchJob> jobs;
+    for (int r = 0; r < n_items; ++r) {
+        const syk_batch_item &it = items[r];
+        Hamiltonian h;
+        build_hamiltonian(h, it.N, it.k, it.seed, it.ensemble);
+        BatchJob jb{};
+        jb.L = h.L;
+        jb.N = h.N;
+        jb.K = h.K;
+        for (int blk = 0; blk < 2; ++blk) {
+            jb.term_off[blk] = static_cast<uint32_t>(terms.size());
+            jb.run_off[blk] = static_cast<uint32_t>(runs.size());
+            add_block(h.block_terms[blk], h.L, shape, terms, runs);
+        }
+        majorana_form(it.N, it.i, jb.wx, jb.wz, jb.ww, jb.w_top);
+        majorana_form(it.N, it.j, jb.vx, jb.vz, jb.vw, jb.v_top);
+        jb.beta = o.beta;
+        for (int v = 0; v < o.nvec; ++v) {
+            jb.base = splitmix_mix(it.state_seed + static_cast<uint64_t>(v + 1) * 0x9E3779B97F4A7C15ULL);
+            jobs.push_back(jb);
+        }
+    }
+    const int n_jobs = static_cast<int>(jobs.size());
+
     const int slots = device_cus() * shape.occ;
     const std::vector<BatchPart> parts = make_parts(jobs, ts, o.beta, o.tol, slots);
     const int grid = std::min<int>(static_cast<int>(parts.size()), slots);
@@ -218,6 +244,7 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
     };
     const size_t n_F = static_cast<size_t>(n_jobs) * 2 * ntt * 2;
     const size_t at_jobs = piece(jobs.size() * sizeof(BatchJob)), at_parts = piece(parts.size() * sizeof(BatchPart));
+    const size_t at_runs = piece(runs.size() * sizeof(uint32_t));
     const size_t at_terms = piece(terms.size() * sizeof(BatchTerm)), at_ts = piece(ts.size() * sizeof(double));
     const size_t at_F = piece(n_F * sizeof(double)), at_res = piece(parts.size() * sizeof(BatchResult));
     const size_t at_counter = piece(sizeof(unsigned));
@@ -232,6 +259,7 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
     p.jobs = reinterpret_cast<const BatchJob *>(put(at_jobs, jobs));
     p.parts = reinterpret_cast<const BatchPart *>(put(at_parts, parts));
     p.terms = reinterpret_cast<const BatchTerm *>(put(at_terms, terms));
+    p.runs = reinterpret_cast<const uint32_t *>(put(at_runs, runs));
     p.ts = reinterpret_cast<const double *>(put(at_ts, ts));
     p.F = reinterpret_cast<double *>(base + at_F);
     p.results = reinterpret_cast<BatchResult *>(base + at_res);

@@ -20,6 +20,8 @@
 // matrix function.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "batch.hpp"
 
 namespace syk {
@@ -31,13 +33,12 @@ namespace {
 // one waits on both memory counters.
 typedef __attribute__((address_space(1))) float2 gf2;          // device memory
 typedef __attribute__((address_space(3))) float2 lf2;          // LDS
-typedef __attribute__((address_space(1))) const BatchTerm gterm;
-typedef __attribute__((address_space(3))) const BatchTerm lterm;
+typedef __attribute__((address_space(1))) const uint32_t gword;
+typedef __attribute__((address_space(3))) const uint32_t lword;
 
 // loads and stores through typed pointers use clang's builtin vector types (the HIP vector
 // classes cannot be copied from address-space-qualified objects)
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float2 ld(const gf2 *p) {
     const f32x2 u = *(__attribute__((address_space(1))) const f32x2 *)p;
     return float2{u.x, u.y};
@@ -48,13 +49,6 @@ __device__ __forceinline__ float2 ld(const lf2 *p) {
     return float2{u.x, u.y};
 }
 __device__ __forceinline__ void st(lf2 *p, float2 v) { *(__attribute__((address_space(3))) f32x2 *)p = f32x2{v.x, v.y}; }
-__device__ __forceinline__ BatchTerm ld(gterm *p) {
-    return __builtin_bit_cast(BatchTerm, *(__attribute__((address_space(1))) const u32x4 *)p);
-}
-__device__ __forceinline__ BatchTerm ld(lterm *p) {
-    return __builtin_bit_cast(BatchTerm, *(__attribute__((address_space(3))) const u32x4 *)p);
-}
-
 constexpr int kCheb = 64;               // Chebyshev nodes and series length
 constexpr double kMaxArg = 25.0;        // largest |w| b evaluated
 
@@ -76,8 +70,6 @@ __device__ __forceinline__ double2 bhaar(uint64_t base, uint64_t n) {
     sincos(2.0 * M_PI * u2, &sn, &cs);
     return double2{r * cs, r * sn};
 }
-
-__device__ __forceinline__ float fsign(float c, uint32_t bit) { return __int_as_float(__float_as_int(c) ^ (bit << 31)); }
 
 // LDS written by some lanes of a wavefront, then read by others of the same wavefront
 __device__ __forceinline__ void wave_lds_sync() {
@@ -111,7 +103,7 @@ struct Ctx {
     gf2 *basis;                        // (m + 1) vectors
     gf2 *vec[4];                       // l, r2, r4, tmp
     uint32_t tid;
-    lterm *lterms[2];                  // the job's terms staged in LDS (null: read from memory)
+    lword *lterms[2];                  // the job's terms staged in LDS (null: read from memory)
     long long matvecs = 0;
     int substeps = 0;
     int status = 0;
@@ -155,94 +147,121 @@ __device__ __forceinline__ double bsum1(double a, LShared<NT> &sh, uint32_t tid)
 // ------------------------------------------------------------------ vector kernels
 // Thread tid owns amplitudes r * NT + tid, r < R = 2^L / NT.
 
-// One term on a thread's RC registers.  xr and zr are wave-uniform: the partner register
-// offset (r ^ xr) << LNT and the register sign are scalar values, so each register costs
-// one vector add for its LDS address and one vector XOR for its sign besides the FMAs.
-template <int NT, int RC, bool IM>
-__device__ __forceinline__ void term_regs(float2 (&acc)[RC], const lf2 *buf_lane, float cl, uint32_t xr,
-                                          uint32_t zr) {
-    constexpr int LNT = __builtin_ctz(NT);
+// One term on a thread's RC registers: register 4 h + l (l < 4, or fewer where RC < 4) reads partner
+// register 4 (h ^ xh) + (l ^ XL).  The low bits XL and ZL are compile-time constants of the run, so a group
+// of four registers costs one address (its reads sit at constant offsets, in whatever order) and
+// one sign operation, and the signs inside it are operand modifiers.  cur: 16 records, lane l = word l.
+template <int NT, int RC, int XL, int ZL, bool IM>
+__device__ __forceinline__ void term_regs(float2 (&acc)[RC], lf2 *buf, uint32_t cur, int j, uint32_t tz, uint32_t tb8,
+                                          uint32_t signbit) {
+    constexpr int Q = 1 << batch_low_bits(RC);       // registers per group
+    const uint32_t xb = __builtin_amdgcn_readlane(cur, j), zt = __builtin_amdgcn_readlane(cur, j + 1);
+    const uint32_t cw = __builtin_amdgcn_readlane(cur, j + 2);
+    // the parity goes to the sign bit of the coefficient: adding 2^31 flips it
+    const float cl = __uint_as_float((static_cast<uint32_t>(__popc(tz & zt)) << 31) + cw);
+    const uint32_t base = tb8 ^ xb;
+    float2 q[RC];
 #pragma unroll
-    for (int r = 0; r < RC; ++r) {
-        const float2 q = ld(buf_lane + ((static_cast<uint32_t>(r) ^ xr) << LNT));
-        uint32_t sg = (__popc(static_cast<uint32_t>(r) & zr) & 1u) << 31;
-        asm("" : "+s"(sg));              // keep the register sign a scalar operand
-        const float cr = r == 0 ? cl : __int_as_float(__float_as_int(cl) ^ static_cast<int>(sg));
-        if (IM) {
-            acc[r].x -= cr * q.y;
-            acc[r].y += cr * q.x;
-        } else {
-            acc[r].x += cr * q.x;
-            acc[r].y += cr * q.y;
+    for (int h = 0; h < RC / Q; ++h) {
+        const lf2 *b = (const lf2 *)((__attribute__((address_space(3))) char *)buf + (base ^ (h * Q * NT * 8u)));
+#pragma unroll
+        for (int l = 0; l < Q; ++l) q[Q * h + l] = ld(b + l * NT);
+    }
+    const uint32_t sg = RC > Q ? __builtin_amdgcn_readlane(cur, j + 3) : 0u;
+#pragma unroll
+    for (int h = 0; h < RC / Q; ++h) {
+        uint32_t sh = sg << (31 - h);
+        asm("" : "+s"(sh));                          // one scalar shift, one vector operation
+        const float ch = h == 0 ? cl : __uint_as_float(__float_as_uint(cl) ^ (sh & signbit));
+#pragma unroll
+        for (int l = 0; l < Q; ++l) {
+            const float cr = (__builtin_popcount(l & ZL) & 1) ? -ch : ch;
+            const float2 p = q[Q * h + (l ^ XL)];
+            float2 &a = acc[Q * h + l];
+            if (IM) {
+                a.x -= cr * p.y;
+                a.y += cr * p.x;
+            } else {
+                a.x += cr * p.x;
+                a.y += cr * p.y;
+            }
         }
+    }
+}
+
+// f(integral_constant<int, i>) for i = I .. N - 1
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
     }
 }
 
 // y = H_blk v (v, y: global, standard layout); returns this thread's share of Re <v, y>.
 // The block is cut into NCH chunks of CH amplitudes; output chunk o is accumulated in
 // registers (RC per thread) while every chunk ch of v is staged in LDS in turn, and the
-// terms whose partner offset x >> log2(CH) equals o ^ ch are applied from it.
+// terms whose partner offset x >> log2(CH) equals o ^ ch are applied from it, run by run.
+// Bound by vector issue: with 16 registers a term takes 46 vector operations, 32 of them the
+// products (74 with an address and a sign per register).
 template <int NT, int CHB, int L>
-__device__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v, gf2 *y, float vs) {
+__device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v, gf2 *y, float vs) {
     constexpr int n = 1 << L;
     constexpr int LCH = L < CHB ? L : CHB;
     constexpr int CH = 1 << LCH;
     constexpr int NCH = n / CH;
     constexpr int RC = CH / NT;
     constexpr int LNT = __builtin_ctz(NT);
+    constexpr int LOW = batch_low_bits(RC), RUNS = batch_runs(RC);
     static_assert(NCH >= 1 && NCH <= 4 && RC >= 1 && RC <= 16, "chunking");
-    const uint32_t tid = c.tid;
-    gterm *terms = (gterm *)(c.p.terms + c.job.term_off[blk]);
-    lterm *lterms = c.lterms[blk];
-    const int K = c.job.K;
-    double dre = 0.0;
-    // one term with wave-uniform fields (scalar registers)
-    auto term = [&](auto im, float2 (&acc)[RC], uint32_t tx, uint32_t tz, float tc, int o) __attribute__((always_inline)) {
-        const uint32_t xl = tx & (CH - 1);
-        const uint32_t lane = tid ^ (xl & (NT - 1));
-        const uint32_t xr = xl >> LNT;
-        const uint32_t zr = (tz >> LNT) & (RC - 1);
-        // sign of output m = (o RC + r) NT + tid: thread bits, chunk bits, register bits
-        const uint32_t par = (__popc(tid & tz & (NT - 1)) + __popc((tz >> LCH) & static_cast<uint32_t>(o))) & 1u;
-        const float cl = fsign(tc, par);
-        term_regs<NT, RC, decltype(im)::value>(acc, c.buf + lane, cl, xr, zr);
-    };
-    // the terms of [lo, hi) with the given phase, from LDS or from memory; the two phases
-    // run as separate loops so that each loop body is one straight FMA sequence
+    const uint32_t tid = c.tid, lane = tid & 63u;
+    gword *terms = (gword *)(c.p.terms + c.job.term_off[blk]);
+    lword *lterms = c.lterms[blk];
+    const uint32_t *runs = c.p.runs + c.job.run_off[blk];
     const bool staged = __builtin_amdgcn_readfirstlane(lterms != nullptr ? 1 : 0) != 0;   // uniform
-    auto phase = [&](auto im, float2 (&acc)[RC], int lo, int hi, int o) __attribute__((always_inline)) {
-        auto one = [&](const BatchTerm &tm) __attribute__((always_inline)) {
-            if ((__builtin_amdgcn_readfirstlane(tm.imag) != 0) != decltype(im)::value) return;
-            term(im, acc, __builtin_amdgcn_readfirstlane(tm.x), __builtin_amdgcn_readfirstlane(tm.z),
-                 __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tm.c))), o);
-        };
-        if (staged)
-            for (int t = lo; t < hi; ++t) one(ld(lterms + t));
-        else
-            for (int t = lo; t < hi; ++t) one(ld(terms + t));
+    const uint32_t last = static_cast<uint32_t>(c.job.K) * 4u - 1u;
+    // records 16 i .. 16 i + 15, one word per lane (past the last record: its last word)
+    auto load16 = [&](uint32_t i) __attribute__((always_inline)) {
+        uint32_t w = i * 64u + lane;
+        w = w < last ? w : last;
+        return staged ? lterms[w] : terms[w];
     };
+    const uint32_t tb8 = tid * 8u;
+    uint32_t signbit = 0x80000000u;
+    asm("" : "+v"(signbit));                          // in a VGPR: a sign operation has one scalar operand
+    double dre = 0.0;
+    int in_lds = -1;                                  // chunk of v staged in LDS
     for (int o = 0; o < NCH; ++o) {
         float2 acc[RC];
 #pragma unroll
         for (int r = 0; r < RC; ++r) acc[r] = float2{0.0f, 0.0f};
-        for (int ch = 0; ch < NCH; ++ch) {
-            __syncthreads();                              // earlier readers of buf are done
+        const uint32_t tz = tid | (static_cast<uint32_t>(o) << LNT);
+        for (int i = 0; i < NCH; ++i) {
+            const int ch = (o & 1) ? NCH - 1 - i : i;     // the first chunk is the one staged last
+            if (ch != in_lds) {
+                __syncthreads();                          // earlier readers of buf are done
 #pragma unroll
-            for (int r = 0; r < RC; ++r) {
-                const float2 q = ld(v + (ch * CH + r * NT + tid));
-                st(c.buf + (r * NT + tid), float2{vs * q.x, vs * q.y});
+                for (int r = 0; r < RC; ++r) {
+                    const float2 q = ld(v + (ch * CH + r * NT + tid));
+                    st(c.buf + (r * NT + tid), float2{vs * q.x, vs * q.y});
+                }
+                __syncthreads();
+                in_lds = ch;
             }
-            __syncthreads();
-            // the terms with partner chunk offset x >> LCH == o ^ ch (terms sorted by x)
-            const uint32_t want = static_cast<uint32_t>(o ^ ch);
-            int lo = 0, hi = K;
-            if constexpr (L >= 12) {
-                constexpr int SH = LCH - 12;
-                lo = c.job.gstart[blk][want << SH];
-                hi = c.job.gstart[blk][(want + 1) << SH];
-            }
-            phase(std::false_type{}, acc, lo, hi, o);
-            phase(std::true_type{}, acc, lo, hi, o);
+            // the terms with partner chunk offset x >> LCH == o ^ ch
+            const uint32_t *rb = runs + __builtin_amdgcn_readfirstlane((o ^ ch) * (RUNS + 1));
+            uint32_t t = __builtin_amdgcn_readfirstlane(rb[0]);
+            uint32_t cur = load16(t >> 4);
+            static_for<0, RUNS>([&](auto rc) __attribute__((always_inline)) {
+                constexpr int run = decltype(rc)::value;
+                constexpr int ZL = run & ((1 << LOW) - 1), XL = (run >> LOW) & ((1 << LOW) - 1);
+                constexpr bool IM = (run >> (2 * LOW)) != 0;
+                const uint32_t e = __builtin_amdgcn_readfirstlane(rb[run + 1]);
+                while (t < e) {
+                    term_regs<NT, RC, XL, ZL, IM>(acc, c.buf, cur, static_cast<int>(t & 15u) * 4, tz, tb8, signbit);
+                    if ((++t & 15u) == 0u) cur = load16(t >> 4);
+                }
+            });
         }
 #pragma unroll
         for (int r = 0; r < RC; ++r) {
@@ -351,7 +370,7 @@ __device__ void haar(Ctx<NT, CHB> &c, int A, gf2 *dst) {
 // ------------------------------------------------------------------ Lanczos
 // one Lanczos iteration j: V_{j+1}, alpha_j = sh.al[j], beta_{j+1} = sh.bt[j + 1]
 template <int NT, int CHB, int L>
-__device__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j) {
+__device__ __forceinline__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j) {
     constexpr int R = (1 << L) / NT;
     const gf2 *vj = c.basis + static_cast<size_t>(j) * c.p.vec_stride;
     const gf2 *vp = j > 0 ? c.basis + static_cast<size_t>(j - 1) * c.p.vec_stride : nullptr;
@@ -522,7 +541,7 @@ __device__ void decide(LShared<NT> &sh, int k, int m, double remaining, double z
 // v <- e^{z H_blk} v (in place), Lanczos with restarts and the step control of the
 // single-vector path
 template <int NT, int CHB, int L>
-__device__ void prop(Ctx<NT, CHB> &c, int blk, double zr, double zi, gf2 *v) {
+__device__ __attribute__((noinline)) void prop(Ctx<NT, CHB> &c, int blk, double zr, double zi, gf2 *v) {
     constexpr int R = (1 << L) / NT;
     if (c.status) return;
     double nrm = sqrt(norm2<NT, CHB, L>(c, v));
@@ -663,8 +682,8 @@ __global__ void __launch_bounds__(NT, OCC * NT / 256) otoc_batch_kernel(BatchPar
             for (int blk = 0; blk < 2; ++blk)
                 for (int t = static_cast<int>(tid); t < jb.K; t += NT) tl[blk][t] = p.terms[jb.term_off[blk] + t];
             __syncthreads();
-            c.lterms[0] = (lterm *)(tl[0]);
-            c.lterms[1] = (lterm *)(tl[1]);
+            c.lterms[0] = (lword *)(tl[0]);
+            c.lterms[1] = (lword *)(tl[1]);
         }
         // the block size is a compile-time parameter of the job code
         switch (jb.L) {

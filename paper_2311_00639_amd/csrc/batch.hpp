@@ -9,12 +9,20 @@ namespace syk {
 
 constexpr int kMaxKrylov = 60;          // largest Krylov dimension of the batched path
 
-// one term of a block in kernel form: y[m] += c i^imag (-1)^{popc(m & z)} x[m ^ x]
+// One term of a block as the kernel reads it, for a launch shape of NT threads and LDS chunks of
+// CH amplitudes; thread t holds amplitudes t + NT r of a chunk, r < RC = CH / NT.  The host sorts the
+// terms into runs by partner chunk, phase and the lowest `low` register bits (two, or all where RC
+// < 4) of x and of z, so that each run's registers and signs are known to the compiled code up
+// to the higher register bits, which the record holds.
 struct BatchTerm {
-    uint32_t x, z;
-    float c;
-    uint32_t imag;
+    uint32_t xb;                        // x inside the chunk times 8 bytes, its low register bits cleared
+    uint32_t zt;                        // z: thread bits, then chunk bits
+    float c;                            // coefficient, the parity of x & z folded in
+    uint32_t sg;                        // bit h: sign of the registers with higher bits h
 };
+constexpr int batch_low_bits(int rc) { return rc >= 4 ? 2 : rc >= 2 ? 1 : 0; }
+// runs per partner chunk: (phase, low x bits, low z bits), z fastest; the table holds runs + 1 bounds
+constexpr int batch_runs(int rc) { return 2 << (2 * batch_low_bits(rc)); }
 
 // one job: a realisation and one Haar vector
 struct BatchJob {
@@ -26,10 +34,7 @@ struct BatchJob {
     int vw, v_top;
     uint64_t base;                      // Haar generator base of this vector
     double beta;
-    // each block's terms are sorted by x; gstart[blk][g] = first term with x >> 12 >= g
-    // (g <= 8; gstart[blk][8] = K), so the terms of one partner chunk are contiguous
-    uint16_t gstart[2][9];
-    uint16_t pad2[2];
+    uint32_t run_off[2];                // block U / D in BatchParams::runs: bounds by partner chunk
 };
 
 // One part of a job, the unit a workgroup takes: the chain that starts in parity block A, for the
@@ -50,6 +55,7 @@ struct BatchParams {
     const BatchPart *parts;
     int n_parts;
     const BatchTerm *terms;
+    const uint32_t *runs;               // run bounds, indices into a block's terms
     const double *ts;                   // t grid (t[0] = 0)
     int nt;
     int m;                              // Krylov dimension
