@@ -13,9 +13,11 @@
 // Small exponential.  c = e^{w T} e_1 for the k x k Lanczos tridiagonal T (k <= 64) is
 // evaluated by one wavefront, lane i holding component i: T = a + b Y with [a - b, a + b]
 // the Gershgorin interval, e^{w b y} expanded in Chebyshev polynomials on [-1, 1] with
-// coefficients from 64 Chebyshev nodes (a discrete cosine transform), and the series summed
-// with the three-term recurrence of T_n(Y) e_1.  Accurate to rounding while |w b| <= 25;
-// a larger argument counts as not converged, so the step control shortens the sub-step.
+// coefficients from M Chebyshev nodes (a discrete cosine transform), and the series of M terms summed
+// with the three-term recurrence of T_n(Y) e_1.  M = 16 for |w b| <= 1, 32 for |w b| <= 8, else 64: the
+// truncation, about 2 (|w b| / 2)^M / M!, stays below double rounding.  Accurate to rounding
+// while |w b| <= 25; a larger argument counts as not converged, so the step control shortens the
+// sub-step.
 // The host path (krylov.cpp) uses an eigendecomposition instead; both compute the same
 // matrix function.
 #include <hip/hip_runtime.h>
@@ -49,7 +51,7 @@ __device__ __forceinline__ float2 ld(const lf2 *p) {
     return float2{u.x, u.y};
 }
 __device__ __forceinline__ void st(lf2 *p, float2 v) { *(__attribute__((address_space(3))) f32x2 *)p = f32x2{v.x, v.y}; }
-constexpr int kCheb = 64;               // Chebyshev nodes and series length
+constexpr int kCheb = 64;               // Chebyshev nodes and series length, at most
 constexpr double kMaxArg = 25.0;        // largest |w| b evaluated
 
 __device__ __forceinline__ uint64_t bmix(uint64_t z) {
@@ -198,22 +200,28 @@ __device__ __forceinline__ void static_for(F &&f) {
     }
 }
 
-// y = H_blk v (v, y: global, standard layout); returns this thread's share of Re <v, y>.
-// The block is cut into NCH chunks of CH amplitudes; output chunk o is accumulated in
-// registers (RC per thread) while every chunk ch of v is staged in LDS in turn, and the
-// terms whose partner offset x >> log2(CH) equals o ^ ch are applied from it, run by run.
-// Bound by vector issue: with 16 registers a term takes 46 vector operations, 32 of them the
-// products (74 with an address and a sign per register).
-template <int NT, int CHB, int L>
-__device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v, gf2 *y, float vs) {
+// y = H_blk v (v: global, standard layout, scaled by vs as it is staged); returns this thread's
+// share of Re <v, y>.  The block is cut into NCH chunks of CH amplitudes; output chunk o is
+// accumulated in registers (RC per thread) while every chunk ch of v is staged in LDS in turn, and the
+// terms whose partner offset x >> log2(CH) equals o ^ ch are applied from it, run by run.  Up to two
+// chunks, y stays in registers (y0: chunk 0 of two, acc: the last chunk) and chunk o of v is the
+// last one staged for output chunk o, so its product with y reads LDS and the last chunk of v is still
+// there afterwards; four chunks are written to y.
+// Bound by LDS reads, 8 bytes per term and amplitude: at N = 32 a term costs 0.92 us per 2^15
+// amplitudes, 119 of an assumed 128 bytes a clock (with 16 registers it takes 46 vector operations, 32 of them
+// the products; 74 with an address and a sign per register).  The rest of a step at N = 32, about
+// 85 us on every CU at once, is Lanczos vectors from memory: 127 us when y went through memory and
+// v_j was read again for the products.
+template <int NT, int CHB, int L, int RC>
+__device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v, gf2 *y, float vs, float2 (&y0)[RC],
+                                          float2 (&acc)[RC]) {
     constexpr int n = 1 << L;
     constexpr int LCH = L < CHB ? L : CHB;
     constexpr int CH = 1 << LCH;
     constexpr int NCH = n / CH;
-    constexpr int RC = CH / NT;
     constexpr int LNT = __builtin_ctz(NT);
     constexpr int LOW = batch_low_bits(RC), RUNS = batch_runs(RC);
-    static_assert(NCH >= 1 && NCH <= 4 && RC >= 1 && RC <= 16, "chunking");
+    static_assert(NCH >= 1 && NCH <= 4 && RC == CH / NT && RC >= 1 && RC <= 16, "chunking");
     const uint32_t tid = c.tid, lane = tid & 63u;
     gword *terms = (gword *)(c.p.terms + c.job.term_off[blk]);
     lword *lterms = c.lterms[blk];
@@ -232,19 +240,23 @@ __device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v
     double dre = 0.0;
     int in_lds = -1;                                  // chunk of v staged in LDS
     for (int o = 0; o < NCH; ++o) {
-        float2 acc[RC];
+        if (NCH == 2 && o == 1)
+#pragma unroll
+            for (int r = 0; r < RC; ++r) y0[r] = acc[r];
 #pragma unroll
         for (int r = 0; r < RC; ++r) acc[r] = float2{0.0f, 0.0f};
         const uint32_t tz = tid | (static_cast<uint32_t>(o) << LNT);
         for (int i = 0; i < NCH; ++i) {
-            const int ch = (o & 1) ? NCH - 1 - i : i;     // the first chunk is the one staged last
+            // two chunks: the other one, then its own; four: back and forth; the first chunk of
+            // an output chunk is the one staged last
+            const int ch = NCH <= 2 ? o ^ (NCH - 1 - i) : (o & 1) ? NCH - 1 - i : i;
             if (ch != in_lds) {
                 __syncthreads();                          // earlier readers of buf are done
+                float2 q[RC];
 #pragma unroll
-                for (int r = 0; r < RC; ++r) {
-                    const float2 q = ld(v + (ch * CH + r * NT + tid));
-                    st(c.buf + (r * NT + tid), float2{vs * q.x, vs * q.y});
-                }
+                for (int r = 0; r < RC; ++r) q[r] = ld(v + (ch * CH + r * NT + tid));
+#pragma unroll
+                for (int r = 0; r < RC; ++r) st(c.buf + (r * NT + tid), float2{vs * q[r].x, vs * q[r].y});
                 __syncthreads();
                 in_lds = ch;
             }
@@ -266,9 +278,15 @@ __device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v
 #pragma unroll
         for (int r = 0; r < RC; ++r) {
             const int i = o * CH + r * NT + static_cast<int>(tid);
-            const float2 q = ld(v + i);
-            dre += static_cast<double>(vs * q.x) * acc[r].x + static_cast<double>(vs * q.y) * acc[r].y;
-            st(y + i, acc[r]);
+            float2 q;
+            if (NCH <= 2) {
+                q = ld(c.buf + (r * NT + tid));           // written by this thread
+            } else {
+                const float2 u = ld(v + i);
+                q = float2{vs * u.x, vs * u.y};
+                st(y + i, acc[r]);
+            }
+            dre += static_cast<double>(q.x) * acc[r].x + static_cast<double>(q.y) * acc[r].y;
         }
     }
     return dre;
@@ -299,17 +317,6 @@ __device__ double2 dot(Ctx<NT, CHB> &c, const gf2 *u, const gf2 *v) {
     }
     bsum2<NT>(a, b, c.sh, c.tid);
     return double2{a, b};
-}
-
-template <int NT, int CHB, int L>
-__device__ void scale_copy(Ctx<NT, CHB> &c, const gf2 *src, gf2 *dst, double s) {
-    constexpr int R = (1 << L) / NT;
-#pragma unroll 4
-    for (int r = 0; r < R; ++r) {
-        const float2 q = ld(src + (r * NT + c.tid));
-        st(dst + (r * NT + c.tid), float2{static_cast<float>(s * q.x), static_cast<float>(s * q.y)});
-    }
-    __syncthreads();
 }
 
 // dst = chi block map of Majorana n from block `src_blk` (times sqrt 2: the Pauli string)
@@ -368,35 +375,75 @@ __device__ void haar(Ctx<NT, CHB> &c, int A, gf2 *dst) {
 }
 
 // ------------------------------------------------------------------ Lanczos
-// one Lanczos iteration j: V_{j+1}, alpha_j = sh.al[j], beta_{j+1} = sh.bt[j + 1]
+// one Lanczos iteration j: V_{j+1}, alpha_j = sh.al[j], beta_{j+1} = sh.bt[j + 1].  v0: the start
+// vector, which is basis vector 0 (the others sit in the slot's basis from 1 on)
 template <int NT, int CHB, int L>
-__device__ __forceinline__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j) {
+__device__ __forceinline__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j, const gf2 *v0) {
     constexpr int R = (1 << L) / NT;
-    const gf2 *vj = c.basis + static_cast<size_t>(j) * c.p.vec_stride;
-    const gf2 *vp = j > 0 ? c.basis + static_cast<size_t>(j - 1) * c.p.vec_stride : nullptr;
+    constexpr int RC = L < CHB ? R : (1 << CHB) / NT, NCH = R / RC;
+    const gf2 *vj = j > 0 ? c.basis + static_cast<size_t>(j) * c.p.vec_stride : v0;
+    const gf2 *vp = j > 1 ? c.basis + static_cast<size_t>(j - 1) * c.p.vec_stride : v0;
     gf2 *vn = c.basis + static_cast<size_t>(j + 1) * c.p.vec_stride;
     // basis slots hold v_i / sc[i]; the next slot is left unnormalised (its scale 1/beta_j
     // enters wherever it is read), which saves a normalising pass per step
     const float sj = c.sh.sc[j];
     const float sp = j > 0 ? c.sh.sc[j - 1] : 0.0f;
-    const double alpha = bsum1<NT>(apply_h<NT, CHB, L>(c, blk, vj, vn, sj), c.sh, c.tid);
-    const double bprev = c.sh.bt[j];
-    const float fa = static_cast<float>(alpha) * sj, fb = static_cast<float>(bprev) * sp;
-    double w2 = 0.0;
-#pragma unroll 4
-    for (int r = 0; r < R; ++r) {
-        const int i = r * NT + static_cast<int>(c.tid);
-        const float2 q = ld(vj + i);
-        float2 w = ld(vn + i);
-        w.x -= fa * q.x;
-        w.y -= fa * q.y;
-        if (vp) {
-            const float2 p = ld(vp + i);
-            w.x -= fb * p.x;
-            w.y -= fb * p.y;
+    const float fb = static_cast<float>(c.sh.bt[j]) * sp;   // 0 for j = 0
+    float2 y0[RC], acc[RC];
+    const double dre = apply_h<NT, CHB, L, RC>(c, blk, vj, vn, sj, y0, acc);
+    double w2 = 0.0, alpha;
+    if constexpr (NCH <= 2) {
+        // w = y - alpha v_j - beta_{j-1} v_{j-1} from registers; the last chunk of v_j is still staged
+        float2 p[RC];
+#pragma unroll
+        for (int r = 0; r < RC; ++r)
+            p[r] = j > 0 ? ld(vp + ((NCH - 1) * RC + r) * NT + c.tid) : float2{0.0f, 0.0f};
+        alpha = bsum1<NT>(dre, c.sh, c.tid);
+        const float al = static_cast<float>(alpha), fa = al * sj;
+#pragma unroll
+        for (int r = 0; r < RC; ++r) {
+            const int i = ((NCH - 1) * RC + r) * NT + static_cast<int>(c.tid);
+            const float2 q = ld(c.buf + (r * NT + c.tid));
+            const float2 w = {acc[r].x - al * q.x - fb * p[r].x, acc[r].y - al * q.y - fb * p[r].y};
+            st(vn + i, w);
+            w2 += static_cast<double>(w.x) * w.x + static_cast<double>(w.y) * w.y;
         }
-        st(vn + i, w);
-        w2 += static_cast<double>(w.x) * w.x + static_cast<double>(w.y) * w.y;
+        if constexpr (NCH == 2) {
+            constexpr int G = RC < 8 ? RC : 8;       // loads in flight: 2 G
+#pragma unroll
+            for (int r0 = 0; r0 < RC; r0 += G) {
+                float2 q[G];
+#pragma unroll
+                for (int r = 0; r < G; ++r) {
+                    q[r] = ld(vj + (r0 + r) * NT + c.tid);
+                    p[r] = j > 0 ? ld(vp + (r0 + r) * NT + c.tid) : float2{0.0f, 0.0f};
+                }
+#pragma unroll
+                for (int r = 0; r < G; ++r) {
+                    const float2 w = {y0[r0 + r].x - fa * q[r].x - fb * p[r].x, y0[r0 + r].y - fa * q[r].y - fb * p[r].y};
+                    st(vn + (r0 + r) * NT + c.tid, w);
+                    w2 += static_cast<double>(w.x) * w.x + static_cast<double>(w.y) * w.y;
+                }
+            }
+        }
+    } else {
+        alpha = bsum1<NT>(dre, c.sh, c.tid);
+        const float fa = static_cast<float>(alpha) * sj;
+#pragma unroll 4
+        for (int r = 0; r < R; ++r) {
+            const int i = r * NT + static_cast<int>(c.tid);
+            const float2 q = ld(vj + i);
+            float2 w = ld(vn + i);
+            w.x -= fa * q.x;
+            w.y -= fa * q.y;
+            if (j > 0) {
+                const float2 p = ld(vp + i);
+                w.x -= fb * p.x;
+                w.y -= fb * p.y;
+            }
+            st(vn + i, w);
+            w2 += static_cast<double>(w.x) * w.x + static_cast<double>(w.y) * w.y;
+        }
     }
     const double beta = sqrt(bsum1<NT>(w2, c.sh, c.tid));
     if (c.tid == 0) {
@@ -406,6 +453,15 @@ __device__ __forceinline__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j) {
     }
     __syncthreads();
 }
+
+// lane i's neighbours in the wavefront: the value of lane i - 1 or i + 1, 0 beyond the ends
+template <int CTRL>
+__device__ __forceinline__ double wave_shift(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+constexpr int kFromBelow = 0x138, kFromAbove = 0x130;      // whole-wave shifts by one lane
 
 // Wavefront 0 only.  c = e^{(wr + i wi) T_k} e_1 into sh.cre / sh.cim; returns |c_{k-1}|,
 // or a negative value when the argument exceeds the evaluated range.
@@ -427,10 +483,13 @@ __device__ double small_exp(LShared<NT> &sh, int k, double wr, double wi, uint32
     const double a = 0.5 * (hi + lo);
     const double b = fmax(0.5 * (hi - lo), 1e-300);
     const double ur = wr * b, ui = wi * b;           // argument on [-1, 1]
-    if (sqrt(ur * ur + ui * ui) > kMaxArg) return -1.0;
+    const double arg = sqrt(ur * ur + ui * ui);
+    if (arg > kMaxArg) return -1.0;
+    const int M = __builtin_amdgcn_readfirstlane(arg <= 1.0 ? 16 : arg <= 8.0 ? 32 : kCheb);
+    const int stride = kCheb / M;                    // of the cosine table
     // samples at the Chebyshev nodes y_q = cos(pi (q + 1/2) / M)
-    {
-        const double y = sh.cosb[2 * lane + 1];
+    if (static_cast<int>(lane) < M) {
+        const double y = sh.cosb[(2 * lane + 1) * stride];
         const double er = exp(ur * y);
         double sn, cs;
         sincos(ui * y, &sn, &cs);
@@ -440,13 +499,14 @@ __device__ double small_exp(LShared<NT> &sh, int k, double wr, double wi, uint32
     wave_lds_sync();
     // coefficient n = lane: (2 / M) sum_q f_q cos(pi n (2q + 1) / (2M))
     double cr = 0.0, ci = 0.0;
-    for (int q = 0; q < kCheb; ++q) {
-        const double cs = sh.cosb[(lane * (2 * q + 1)) & (4 * kCheb - 1)];
+#pragma unroll 8
+    for (int q = 0; q < M; ++q) {
+        const double cs = sh.cosb[(lane * (2 * q + 1) * stride) & (4 * kCheb - 1)];
         cr += sh.fre[q] * cs;
         ci += sh.fim[q] * cs;
     }
-    cr *= 2.0 / kCheb;
-    ci *= 2.0 / kCheb;
+    cr *= 2.0 / M;
+    ci *= 2.0 / M;
     if (lane == 0) {
         cr *= 0.5;
         ci *= 0.5;
@@ -461,15 +521,14 @@ __device__ double small_exp(LShared<NT> &sh, int k, double wr, double wi, uint32
     const double lo_off = (in && lane > 0) ? sh.bt[lane] / b : 0.0;                    // to i - 1
     const double up_off = (in && static_cast<int>(lane) + 1 < k) ? sh.bt[lane + 1] / b : 0.0;   // to i + 1
     auto applyY = [&](double u) {
-        const double um = __shfl(u, (lane + 63) & 63, 64);
-        const double up = __shfl(u, (lane + 1) & 63, 64);
-        return in ? d * u + lo_off * um + up_off * up : 0.0;
+        return d * u + lo_off * wave_shift<kFromBelow>(u) + up_off * wave_shift<kFromAbove>(u);
     };
     double u0 = lane == 0 ? 1.0 : 0.0;
     double u1 = applyY(u0);
     double sr = sh.fre[0] * u0 + sh.fre[1] * u1;
     double si = sh.fim[0] * u0 + sh.fim[1] * u1;
-    for (int nn = 2; nn < kCheb; ++nn) {
+#pragma unroll 2
+    for (int nn = 2; nn < M; ++nn) {
         const double u2 = 2.0 * applyY(u1) - u0;
         sr += sh.fre[nn] * u2;
         si += sh.fim[nn] * u2;
@@ -539,38 +598,35 @@ __device__ void decide(LShared<NT> &sh, int k, int m, double remaining, double z
 }
 
 // v <- e^{z H_blk} v (in place), Lanczos with restarts and the step control of the
-// single-vector path
+// single-vector path; nrm = ||v|| on entry, returns the norm of the result
 template <int NT, int CHB, int L>
-__device__ __attribute__((noinline)) void prop(Ctx<NT, CHB> &c, int blk, double zr, double zi, gf2 *v) {
+__device__ __attribute__((noinline)) double prop(Ctx<NT, CHB> &c, int blk, double zr, double zi, gf2 *v, double nrm) {
     constexpr int R = (1 << L) / NT;
-    if (c.status) return;
-    double nrm = sqrt(norm2<NT, CHB, L>(c, v));
-    if (nrm == 0.0 || (zr == 0.0 && zi == 0.0)) return;
+    if (c.status) return nrm;
+    if (nrm == 0.0 || (zr == 0.0 && zi == 0.0)) return nrm;
     if (!(nrm == nrm)) {
         c.status = 6;
-        return;
+        return nrm;
     }
     const int m = c.p.m;
     double remaining = 1.0;
     for (;;) {
         if (++c.substeps > c.p.max_substeps) {
             c.status = 5;
-            return;
+            return nrm;
         }
-        scale_copy<NT, CHB, L>(c, v, c.basis, 1.0 / nrm);
         if (c.tid == 0) {
             c.sh.bt[0] = 0.0;
-            c.sh.sc[0] = 1.0f;
+            c.sh.sc[0] = static_cast<float>(1.0 / nrm);
         }
         __syncthreads();
-        int k = 0, next = 4, done = 0;
+        int k = 0, done = 0;
         double tau = 0.0;
         for (int j = 0; j < m; ++j) {
-            lanczos_step<NT, CHB, L>(c, blk, j);
+            lanczos_step<NT, CHB, L>(c, blk, j, v);
             ++c.matvecs;
             k = j + 1;
-            if (k < next && k < m) continue;
-            next = k + 1;
+            if (k < 4 && k < m) continue;
             if (c.tid < 64) decide<NT>(c.sh, k, m, remaining, zr, zi, c.p.tol, c.tid);
             __syncthreads();
             done = c.sh.ctl_i[0];
@@ -579,34 +635,61 @@ __device__ __attribute__((noinline)) void prop(Ctx<NT, CHB> &c, int blk, double 
             __syncthreads();
             if (fail) {
                 c.status = fail;
-                return;
+                return nrm;
             }
             if (done) break;
         }
         if (!done) {                                  // m == 0 cannot happen; defensive
             c.status = 5;
-            return;
+            return nrm;
         }
-        // v = nrm * sum_i c_i V_i
-#pragma unroll 2
-        for (int r = 0; r < R; ++r) {
-            double sr = 0.0, si = 0.0;
-            for (int i = 0; i < k; ++i) {
-                const float2 q = ld(c.basis + (static_cast<size_t>(i) * c.p.vec_stride + r * NT + c.tid));
+        // v = nrm * sum_i c_i V_i, four vectors of G amplitudes in flight
+        constexpr int G = R < 4 ? R : 4;
+        double n2 = 0.0;
+        for (int r0 = 0; r0 < R; r0 += G) {
+            double sr[G], si[G];
+            auto add = [&](int i, const float2 (&q)[G]) __attribute__((always_inline)) {
                 const double cr = c.sh.cre[i] * c.sh.sc[i], ci = c.sh.cim[i] * c.sh.sc[i];
-                sr += cr * q.x - ci * q.y;
-                si += cr * q.y + ci * q.x;
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    sr[g] += cr * q[g].x - ci * q[g].y;
+                    si[g] += cr * q[g].y + ci * q[g].x;
+                }
+            };
+            auto get = [&](const gf2 *u, float2 (&q)[G]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) q[g] = ld(u + ((r0 + g) * NT + c.tid));
+            };
+#pragma unroll
+            for (int g = 0; g < G; ++g) sr[g] = si[g] = 0.0;
+            float2 q[4][G];
+            get(v, q[0]);
+            add(0, q[0]);
+            int i = 1;
+            for (; i + 4 <= k; i += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) get(c.basis + static_cast<size_t>(i + u) * c.p.vec_stride, q[u]);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) add(i + u, q[u]);
             }
-            st(v + (r * NT + c.tid), float2{static_cast<float>(nrm * sr), static_cast<float>(nrm * si)});
+            for (; i < k; ++i) {
+                get(c.basis + static_cast<size_t>(i) * c.p.vec_stride, q[0]);
+                add(i, q[0]);
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const float2 w = {static_cast<float>(nrm * sr[g]), static_cast<float>(nrm * si[g])};
+                st(v + ((r0 + g) * NT + c.tid), w);
+                n2 += static_cast<double>(w.x) * w.x + static_cast<double>(w.y) * w.y;
+            }
         }
-        __syncthreads();
+        nrm = sqrt(bsum1<NT>(n2, c.sh, c.tid));       // ends with a barrier
         remaining -= tau;
-        if (remaining <= 1e-15) return;
-        nrm = sqrt(norm2<NT, CHB, L>(c, v));
-        if (nrm == 0.0) return;
+        if (remaining <= 1e-15) return nrm;
+        if (nrm == 0.0) return nrm;
         if (!(nrm == nrm)) {
             c.status = 6;
-            return;
+            return nrm;
         }
     }
 }
@@ -619,9 +702,11 @@ __device__ __attribute__((noinline)) void run_part(Ctx<NT, CHB> &c, int A, int k
     gf2 *l = c.vec[0], *r2 = c.vec[1], *r4 = c.vec[2], *tmp = c.vec[3];
     const int B = 1 - A;
     haar<NT, CHB, L>(c, A, l);
-    prop<NT, CHB, L>(c, A, -beta / 8.0, 0.0, l);                                  // r0
+    // norms travel with the vectors: a Majorana string keeps them
+    double nl = sqrt(norm2<NT, CHB, L>(c, l));
+    nl = prop<NT, CHB, L>(c, A, -beta / 8.0, 0.0, l, nl);                         // r0
     gamma<NT, CHB, L>(c, jb.v_top, jb.vx, jb.vz, jb.vw, A, l, r2);                // V_BA r0
-    prop<NT, CHB, L>(c, B, -beta / 4.0, 0.0, r2);
+    double nr = prop<NT, CHB, L>(c, B, -beta / 4.0, 0.0, r2, nl);
     long long before = k0 > 0 ? c.matvecs : 0;                                    // another part's
     int before_sub = k0 > 0 ? c.substeps : 0;
     double tprev = 0.0;
@@ -629,8 +714,8 @@ __device__ __attribute__((noinline)) void run_part(Ctx<NT, CHB> &c, int A, int k
         const double t = c.p.ts[k];
         const double dt = t - tprev;
         if (dt > 0.0) {
-            prop<NT, CHB, L>(c, B, 0.0, -dt, r2);
-            prop<NT, CHB, L>(c, A, 0.0, -dt, l);
+            nr = prop<NT, CHB, L>(c, B, 0.0, -dt, r2, nr);
+            nl = prop<NT, CHB, L>(c, A, 0.0, -dt, l, nl);
         }
         tprev = t;
         if (c.status) return;
@@ -640,9 +725,9 @@ __device__ __attribute__((noinline)) void run_part(Ctx<NT, CHB> &c, int A, int k
             continue;
         }
         gamma<NT, CHB, L>(c, jb.w_top, jb.wx, jb.wz, jb.ww, B, r2, r4);           // W_AB r2
-        prop<NT, CHB, L>(c, A, -beta / 4.0, t, r4);
+        const double n4 = prop<NT, CHB, L>(c, A, -beta / 4.0, t, r4, nr);
         gamma<NT, CHB, L>(c, jb.v_top, jb.vx, jb.vz, jb.vw, A, r4, tmp);          // V_BA r4
-        prop<NT, CHB, L>(c, B, -beta / 4.0, -t, tmp);                             // r6
+        prop<NT, CHB, L>(c, B, -beta / 4.0, -t, tmp, n4);                         // r6
         gamma<NT, CHB, L>(c, jb.w_top, jb.wx, jb.wz, jb.ww, B, tmp, r4);          // W_AB r6
         const double2 d = dot<NT, CHB, L>(c, l, r4);
         if (c.tid == 0) F[k] = double2{0.25 * d.x, 0.25 * d.y};
