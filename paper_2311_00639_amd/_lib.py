@@ -1,5 +1,6 @@
 """ctypes declarations for libsyk and thin wrappers with the C ABI's names."""
 import ctypes as ct
+import functools
 import os
 
 import numpy as np
@@ -200,6 +201,8 @@ def _ptr(a):
 def _stream(stream):
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():      # the current stream's handle, without building its object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         if not torch.cuda.is_available():
             return None          # the library reports the missing device itself
         return torch.cuda.current_stream().cuda_stream
@@ -225,11 +228,13 @@ def _vectors(need: int, **tensors) -> int:
     on a GPU.  Returns the dtype code.  The library sees only raw addresses and sizes, so a
     short, strided or host tensor would otherwise be read or written out of bounds."""
     import torch
+    Tensor, c64, c128 = torch.Tensor, torch.complex64, torch.complex128
     dt = None
     for name, t in tensors.items():
-        if not isinstance(t, torch.Tensor):
+        if not isinstance(t, Tensor):
             raise TypeError(f"{name} must be a torch tensor")
-        d = _dtype_of(t)
+        td = t.dtype
+        d = C64 if td is c64 else C128 if td is c128 else _dtype_of(t)
         if dt is not None and d != dt:
             raise TypeError(f"{name} must have the dtype of the other vectors of the call")
         dt = d
@@ -250,6 +255,11 @@ class Hamiltonian:
         h = _vp()
         _check(_lib.syk_create_hamiltonian_ensemble(N, q, float(k), seed, ensemble, ct.byref(h)))
         self._h = h
+
+    @functools.cached_property
+    def qubits(self) -> int:
+        """L of the handle (2^L amplitudes per block), which never changes."""
+        return self.info()["L"]
 
     @property
     def handle(self):
@@ -295,7 +305,7 @@ def apply_H(ham: Hamiltonian, block: int, x, y, nvec: int = 1, ld: int = None, s
     2^(N/2) space, U block then D block).
 
     With nvec > 1 the tensors hold nvec vectors of leading dimension ld (elements)."""
-    n = (2 if block == FULL else 1) << ham.info()["L"]
+    n = (2 if block == FULL else 1) << ham.qubits
     ld = n if ld is None else ld
     if nvec < 1 or ld < n:
         raise ValueError("nvec must be >= 1 and ld >= the vector length")
@@ -339,7 +349,7 @@ def default_krylov_opts(dtype: int) -> KrylovOpts:
 def krylov_expm(ham: Hamiltonian, block: int, z: complex, v, out, m: int = None, tol: float = None,
                 reorth: int = None, max_substeps: int = None, stream=None) -> dict:
     """out = e^{z H_block} v.  Returns the Krylov statistics as a dict."""
-    n = (2 if block == FULL else 1) << ham.info()["L"]
+    n = (2 if block == FULL else 1) << ham.qubits
     dt = _vectors(n, v=v, out=out)
     o = default_krylov_opts(dt)
     if m is not None:

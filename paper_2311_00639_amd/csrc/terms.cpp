@@ -17,8 +17,8 @@
 // written expression (one IEEE operation at a time).
 #include <algorithm>
 #include <cmath>
-#include <set>
 #include <tuple>
+#include <unordered_set>
 #include <vector>
 
 #include "internal.hpp"
@@ -50,14 +50,24 @@ uint64_t choose(int n, int r) {
     return v;
 }
 
-// idx = C(l,4) + C(k,3) + C(j,2) + C(i,1), l > k > j > i >= 0 (colex rank)
+// C(c, r) for c <= 64, r <= 4
+struct Binomials {
+    uint64_t v[5][65];
+    Binomials() {
+        for (int r = 0; r <= 4; ++r)
+            for (int c = 0; c <= 64; ++c) v[r][c] = choose(c, r);
+    }
+};
+
+// idx = C(l,4) + C(k,3) + C(j,2) + C(i,1), l > k > j > i >= 0 (colex rank), idx < C(64, 4)
 std::tuple<int, int, int, int> unrank4(uint64_t idx) {
+    static const Binomials bin;
     int sub[4];
-    for (int r = 4, pos = 3; r >= 1; --r, --pos) {
-        int c = r - 1;
-        while (choose(c + 1, r) <= idx) ++c;
+    int c = 63;
+    for (int r = 4, pos = 3; r >= 1; --r, --pos, --c) {      // the next element is smaller
+        while (bin.v[r][c] > idx) --c;
         sub[pos] = c;
-        idx -= choose(c, r);
+        idx -= bin.v[r][c];
     }
     return {sub[0], sub[1], sub[2], sub[3]};
 }
@@ -127,13 +137,16 @@ void build_hamiltonian(Hamiltonian &h, int N, double k, uint64_t seed, int ensem
         // 2^64 - (2^64 mod C), computed in 64-bit arithmetic: (0 - C) mod C == 2^64 mod C
         const uint64_t rem = (0ULL - C) % C;
         const uint64_t limit = 0ULL - rem;           // reject r >= limit (rem == 0: never)
-        std::set<std::tuple<int, int, int, int>> set;
-        while (static_cast<int>(set.size()) < Kt) {
+        std::unordered_set<uint64_t> ranks;          // a rank is a subset
+        ranks.reserve(2 * static_cast<size_t>(Kt));
+        while (static_cast<int>(ranks.size()) < Kt) {
             const uint64_t r = rng.next();
             if (rem != 0 && r >= limit) continue;
-            set.insert(unrank4(r % C));
+            ranks.insert(r % C);
         }
-        chosen.assign(set.begin(), set.end());       // std::set iterates in lexicographic order
+        chosen.reserve(Kt);
+        for (uint64_t r : ranks) chosen.push_back(unrank4(r));
+        std::sort(chosen.begin(), chosen.end());     // lexicographic order
         h.p = static_cast<double>(Kt) / static_cast<double>(C);
     }
     const int K = static_cast<int>(chosen.size());
