@@ -473,6 +473,14 @@ void KrylovRun<T>::enqueue(int j, const T *u0) {
         launch_publish_sum2(parts, n_norm_, partials_, beta2_ + j + 1, nh, s_);
 }
 
+// The step after k at which the error estimate is formed: each one for large vectors, where a step
+// in vain costs the most, and ever wider apart below 2^20 amplitudes.
+template <typename T>
+int KrylovRun<T>::next_check(int k) const {
+    if (n_ >= (1ULL << 20)) return std::min(k + 1, m_);
+    return std::min(k == 0 ? 4 : k + std::max(2, k / 4), m_);
+}
+
 template <typename T>
 void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o,
                              syk_krylov_stats &st) {
@@ -494,42 +502,46 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             launch_norm2_partials<T>(cur, n_, partials_, n_part_, s_);
             launch_publish_sum(partials_, n_part_, beta2_, host_.dev(host_.norm2(0)), s_);
         }
-        int k = 0, enq = 0;        // steps checked, enqueued
+        int k = 0, enq = 0;        // steps read back, enqueued
         double tau = 0.0, nrm = 0.0;
-        // log error estimates of the last three checks, newest first: the step at which the
-        // estimate meets the tolerance is extrapolated from them (the decay steepens, so the
-        // last slope and its change are used)
+        int check = next_check(0);               // the error estimate is formed at these steps
+        // log error estimates of the last three checks, newest first, and the steps between them:
+        // the check at which the estimate meets the tolerance is extrapolated from them (the decay
+        // steepens, so the last slope and its change are used)
         double e0 = 0.0, e1 = 0.0, e2 = 0.0;
-        int converges = m_;        // that step, as far as known
+        int d0 = 1, d1 = 1, checks = 0;
+        int converges = m_;        // that check, as far as known
         for (;;) {
-            // Steps are enqueued ahead of the one being checked, so that the GPU does not wait
-            // for the host: two where a step takes microseconds, one for large blocks, none beyond
-            // the step expected to converge (a step enqueued in vain costs its whole time).
-            const int ahead = std::min(k + 1 + (n_ >= kBigBlock ? 1 : 2), std::max(k + 1, converges));
+            // Steps are enqueued ahead of the check, so that the GPU does not wait for the host:
+            // two where a step takes microseconds, one for large blocks, none beyond the check
+            // expected to converge (a step enqueued in vain costs its whole time).
+            const int ahead = std::min(check + (n_ >= kBigBlock ? 1 : 2), std::max(check, converges));
             while (enq < std::min(ahead, m_)) enqueue(enq++, cur);
-            if (direct_ && enq == k + 1)             // no later step to sum this norm
+            if (direct_ && enq == check)             // no later step to sum this norm
                 launch_publish_sum(norms_, n_norm_, beta2_ + enq, host_.dev(host_.norm2(enq)), s_);
             if (k == 0) {
                 n2[0] = host_.wait(host_.norm2(0), s_);
                 if (!std::isfinite(n2[0])) fail(SYK_ENUMERIC, "non-finite norm in Krylov propagation");
                 nrm = std::sqrt(n2[0]);
             }
-            al[k] = host_.wait(host_.alpha(k), s_);
-            n2[k + 1] = host_.wait(host_.norm2(k + 1), s_);
-            ++k;
+            const int step = check - k;
+            for (; k < check; ++k) {
+                al[k] = host_.wait(host_.alpha(k), s_);
+                n2[k + 1] = host_.wait(host_.norm2(k + 1), s_);
+            }
             if (nrm == 0.0) break;
-            double tnorm = 0.0;
+            // beta_k ~ 0 ends the sequence at k, also between two checks
+            double tnorm = 0.0, bk = 0.0;
+            bool breakdown = false;
             for (int i = 0; i < k; ++i) {
                 if (!std::isfinite(al[i])) fail(SYK_ENUMERIC, "non-finite Lanczos alpha");
                 tnorm = std::max(tnorm, std::fabs(al[i]));
+                if (i > 0) tnorm = std::max(tnorm, bo[i - 1]);
+                bo[i] = bk = std::sqrt(n2[i + 1]);
+                if (!std::isfinite(bk)) fail(SYK_ENUMERIC, "non-finite Lanczos beta");
+                breakdown = bk <= 1e-14 * std::max(tnorm, 1e-300);
+                if (breakdown) k = i + 1;
             }
-            for (int i = 0; i + 1 < k; ++i) {
-                bo[i] = std::sqrt(n2[i + 1]);
-                tnorm = std::max(tnorm, bo[i]);
-            }
-            const double bk = std::sqrt(n2[k]);
-            if (!std::isfinite(bk)) fail(SYK_ENUMERIC, "non-finite Lanczos beta");
-            const bool breakdown = bk <= 1e-14 * std::max(tnorm, 1e-300);
             const TriLast tl(k, al.data(), bo.data());
             if (!tl.ok()) fail(SYK_ENUMERIC, "tridiagonal eigensolver failed");
             auto err = [&](double f) { return breakdown ? 0.0 : bk * tl.last(f * z); };
@@ -546,11 +558,17 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             e2 = e1;
             e1 = e0;
             e0 = std::log(e);
+            d1 = d0;
+            d0 = step;
+            check = next_check(k);
             converges = m_;
-            if (k >= 3) {
-                const double slope = std::min(e0 - e1, 2.0 * (e0 - e1) - (e1 - e2));
+            if (++checks >= 3) {
+                const double s0 = (e0 - e1) / d0, slope = std::min(s0, 2.0 * s0 - (e1 - e2) / d1);
                 const double left = e0 - std::log(o.tol * remaining);
-                if (slope < 0.0 && left < -slope * (m_ - k)) converges = k + static_cast<int>(std::ceil(left / -slope));
+                if (slope < 0.0 && left < -slope * (m_ - k)) {
+                    const int at = k + static_cast<int>(std::ceil(left / -slope));
+                    for (converges = check; converges < at && converges < m_;) converges = next_check(converges);
+                }
             }
         }
         if (nrm == 0.0) {                            // e^{zH} 0 = 0
@@ -593,7 +611,6 @@ void KrylovRun<T>::run_plain(std::complex<double> z, const T *v, T *out, const s
         if (out != v) launch_scale_copy<T>(v, out, n_, 1.0, s_);
         return;
     }
-    const bool every = n_ >= (1ULL << 20);        // large vectors: a host check per iteration is cheap
     double remaining = 1.0;
     const T *cur = v;
     std::vector<double> ha(2 * (m_ + 2)), hb(m_ + 2);
@@ -607,13 +624,13 @@ void KrylovRun<T>::run_plain(std::complex<double> z, const T *v, T *out, const s
         int k = 0;                 // Lanczos vectors built
         double tau = 0.0;
         bool done = false;
-        int next_check = every ? 1 : 4;
+        int check = next_check(0);
         for (int j = 0; j < m_ && !done; ++j) {
             if (iterate(j, o.reorth)) st.reorths += 1;
             k = j + 1;
             st.matvecs += 1;
-            if (k < next_check && k < m_) continue;
-            next_check = every ? k + 1 : k + std::max(2, k / 4);
+            if (k < check) continue;
+            check = next_check(k);
             SYK_HIP(hipMemcpyAsync(ha.data(), alpha_, 2 * k * sizeof(double), hipMemcpyDeviceToHost, s_));
             SYK_HIP(hipMemcpyAsync(hb.data(), beta2_, (k + 1) * sizeof(double), hipMemcpyDeviceToHost, s_));
             SYK_HIP(hipStreamSynchronize(s_));

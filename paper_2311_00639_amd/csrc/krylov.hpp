@@ -102,6 +102,7 @@ class KrylovRun {
   private:
     T *vec(int j) { return basis_ + static_cast<size_t>(j) * vec_stride_ * 2; }
     // reorth = 0: fused steps, the host a step or two ahead of the last one it has checked
+    int next_check(int k) const;
     void run_fused(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st);
     void run_plain(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st);
     // enqueue fused Lanczos step j from u_j (slot 0: u0)
