@@ -407,7 +407,7 @@ template <typename T>
 int launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec,
                        uint64_t ld, hipStream_t s, const LanczosFuse<T> *lf) {
     using V = typename V2t<T>::type;
-    if (n < 256) fail(SYK_EDEVICE, "the grouped gather needs 256 amplitudes");
+    if (n < 64) fail(SYK_EDEVICE, "the grouped gather needs 64 amplitudes");
     int g = 0;
     auto go = [&](auto pc, auto tile, auto sc) {
         using P = decltype(pc);

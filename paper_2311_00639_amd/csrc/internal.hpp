@@ -100,10 +100,10 @@ struct DeviceTables {            // per device, per block: the gather kernels' t
     DenseTerm<double> *d64 = nullptr;
 };
 // Blocks whose terms share x masks this often or more (terms per mask) use the grouped form,
-// from one 256-amplitude tile up to 2^22 amplitudes (where the gathers still come from the
+// from one 64-amplitude tile up to 2^22 amplitudes (where the gathers still come from the
 // 256 MB last-level cache; larger dense blocks stay with the tiled kernel, unmeasured).
 constexpr int kDenseTermsPerMask = 4;
-constexpr int kDenseMinL = 8, kDenseMaxL = 22;
+constexpr int kDenseMinL = 6, kDenseMaxL = 22;
 
 // distinct x masks of a block's terms: the groups the gather kernel loads once each
 int gather_groups(const std::vector<BlockTerm> &terms);

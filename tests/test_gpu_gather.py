@@ -47,7 +47,7 @@ def test_sparse_gather(L, K, dt):
 
 
 @pytest.mark.parametrize("dt", [syk.C128, syk.C64])
-@pytest.mark.parametrize("L,masks,per", [(8, 1, 5), (8, 20, 9), (9, 3, 4), (15, 40, 7), (16, 17, 23), (17, 2, 31),
+@pytest.mark.parametrize("L,masks,per", [(6, 7, 8), (7, 33, 6), (8, 1, 5), (8, 20, 9), (9, 3, 4), (15, 40, 7), (16, 17, 23), (17, 2, 31),
                                         (18, 5, 6), (19, 33, 8)])
 def test_grouped_gather(L, masks, per, dt):
     rng = np.random.default_rng(100 * L + masks)
