@@ -516,9 +516,10 @@ syk_status syk_tridiag_expm(int n, const double *alpha, const double *beta, doub
                             double *c_re, double *c_im);
 
 /* Launch plan of the tiled apply_H kernel for one block (host-only; no GPU needed).
- * Blocks of 2^L amplitudes with L >= 18 are served by the tiled kernel (except dense ones, of
- * four or more terms per distinct x mask with L <= 22, which the gather kernel serves unless a
- * tiled variant is pinned by syk_select_variant): output tiles of
+ * Blocks of 2^L amplitudes with L >= 18 have one.  It serves them except where the gather kernels
+ * are faster and no tiled variant is pinned by syk_select_variant: blocks of at most 4 MiB (L = 18,
+ * and L = 19 in complex64), and dense ones (four or more terms per distinct x mask) with L <= 22.
+ * The plan: output tiles of
  * 2^tile_bits amplitudes, terms grouped by partner tile (n_groups groups), tiles mapped
  * to workgroups so that the 2^res_bits tiles resident on one XCD form a coset of a
  * res_bits-dim subspace (classes_xcd = partner-tile classes modulo it, which sets the L2
@@ -529,9 +530,9 @@ syk_status syk_tridiag_expm(int n, const double *alpha, const double *beta, doub
  * for the planner's choice (the layout syk_otoc uses by default), layout >= 0 for that
  * rotation. */
 typedef struct {
-    int tiled;             /* 0: the block is served by the gather kernel; then n_groups is the
-                              number of distinct x masks, each gathered once per amplitude
-                              (about K / 19 for dense SYK, about K for sparse) */
+    int tiled;             /* 0: the block is below the tiled size (L < 18); then n_groups is the
+                              number of distinct x masks (about K / 19 for dense SYK, about K
+                              for sparse) */
     int variant;           /* compiled kernel variant in use (default or tuned) */
     int tile_bits, rot, n_groups, classes_xcd, classes_gpu, res_bits;
     int tiles_per_wg;      /* output tiles a workgroup keeps in registers */

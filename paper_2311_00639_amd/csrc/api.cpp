@@ -759,7 +759,7 @@ syk_status syk_plan_describe(const syk_ham *h, syk_block blk, syk_dtype dt, int 
         require(layout >= -1 && layout < std::max(H.L, 1), "layout must be -1 or a rotation in [0, L)");
         *out = syk_plan_desc{};
         const bool c64 = dt == SYK_C64;
-        out->tiled = c64 ? H.tiled<float>() : H.tiled<double>();
+        out->tiled = H.L >= syk::kTiledMinL;
         if (!out->tiled) {
             out->n_groups = syk::gather_groups(H.block_terms[blk]);
             return;

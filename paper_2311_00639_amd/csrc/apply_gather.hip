@@ -1,8 +1,8 @@
-// apply_H below the tiled size, straight from memory (gfx950).
+// apply_H of small and of dense blocks, straight from memory (gfx950).
 //
 // y[m] = sum_a c_a i^{imag_a} (-1)^{popc(m & z_a)} x[m ^ x_a]   (supplement Algorithm 1, with the
-// sign parity of x_a & z_a folded into c_a).  A parity block of at most 2^17 amplitudes (2 MiB in
-// complex128) sits in every L2, so partners are gathered from there and nothing is staged.
+// sign parity of x_a & z_a folded into c_a).  A parity block of at most 4 MiB sits in every L2, so
+// partners are gathered from there and nothing is staged.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -96,18 +96,39 @@ struct Epilogue {
     }
 };
 
-// One wave owns 64 R consecutive amplitudes (lane l holds base + l + 64 r) and one of S slices
-// of the term list; the S waves of a group are in one workgroup and their sums are added in
+// A 16-byte quad: two adjacent complex64 amplitudes or one complex128.  Rows need the
+// alignment of one amplitude only (an odd leading dimension).
+template <typename T> struct Quad;
+template <> struct Quad<float> {
+    static constexpr int A = 2;
+    typedef float V __attribute__((ext_vector_type(4), aligned(8)));
+};
+template <> struct Quad<double> {
+    static constexpr int A = 1;
+    typedef double V __attribute__((ext_vector_type(2)));
+};
+template <typename T>
+__device__ __forceinline__ typename Quad<T>::V load_quad(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
+    typename Quad<T>::V q;
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+    __builtin_memcpy(&q, &v, 16);
+    return q;
+}
+
+// One wave owns R rows of 64 quads (A amplitudes each: lane l holds base + A (l + 64 r) + e) and one of
+// S slices of the term list; the S waves of a group are in one workgroup and their sums are added in
 // slice order in LDS, so the result does not depend on scheduling.
 //
-// Bound by instruction issue and the latency of the gathers, not by bandwidth.  Hence: the
-// slice is wave-uniform, so term records come through scalar loads; the partner of register r
-// is (lane ^ x) in a VGPR plus a scalar offset ((base ^ x) ^ 64 r), so a gather costs no vector
-// address arithmetic; the sign of the lane and base bits is folded into the coefficient once
-// per term (three vector operations) and the register sign is one XOR; U terms' gathers are
-// in flight at once.  Three complex64 vectors over both blocks at N = 34, k = 4 (5.3e7
-// term-amplitudes): 25 us, against 94 us in two launches of one amplitude per thread with
-// per-lane term loads.
+// Bound by the gathers: an instruction takes 16 clocks of a CU whether its lanes read 8 bytes or 16, in any
+// order and wherever the partner is cached, so every lane reads 16 bytes, which is the 64 bytes
+// a clock of the vector cache.  Two complex64 amplitudes of a quad have their partners in one quad,
+// swapped for odd x masks; the terms are sorted so that the swap is compiled.  The slice is
+// wave-uniform, so term records come through scalar loads; the partner of row r is (lane ^ x) in a
+// VGPR plus a scalar offset, so a gather costs no vector address arithmetic; the sign of the
+// lane and base bits is folded into the coefficient once per term and the sign of the row and the element
+// is one XOR; U terms' gathers are in flight at once.  N = 36, k = 8: complex64 10.6 us against 18.1 us
+// with 8-byte gathers, complex128 18.6 us (K 2^17 16 bytes at 39 TB/s of all vector caches: 15.4 us); 59 / 68 us with
+// one amplitude per thread and per-lane term loads.
 template <typename T, int R, int S, bool FUSE>
 __global__ void __launch_bounds__(64 * S) gather_sparse(GatherTerms<T> t0, GatherTerms<T> t1,
                                                         const typename V2t<T>::type *__restrict__ x,
@@ -115,84 +136,109 @@ __global__ void __launch_bounds__(64 * S) gather_sparse(GatherTerms<T> t0, Gathe
                                                         LanczosFuse<T> lf) {
     static_assert(S >= 4, "the epilogue sums with four waves");
     using V = typename V2t<T>::type;
+    using Q = typename Quad<T>::V;
+    constexpr int A = Quad<T>::A;
     constexpr int SH = sizeof(T) == 4 ? 3 : 4;       // log2 of the bytes per amplitude
     constexpr int U = R >= 4 ? 2 : 4;                // terms in flight
+    constexpr uint32_t ROW = 64u * A;                // amplitudes per row
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t base = blockIdx.x * (64u * R);
+    const uint32_t base = blockIdx.x * (ROW * R);
     __shared__ double sh[S + 4];
     Epilogue<T, S> epi{lf, sh};
     if constexpr (FUSE) epi.load();
     const GatherTerms<T> tb = blockIdx.z == 0 ? t0 : t1;
     const uint64_t vo = static_cast<uint64_t>(blockIdx.y) * ld + static_cast<uint64_t>(blockIdx.z) * n;
-    V acc[R];
+    Q acc[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = V{T(0), T(0)};
+    for (int r = 0; r < R; ++r) acc[r] = Q(T(0));
     {
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<V *>(x + vo), 0, static_cast<int>(n << SH), kBufferWord3);
-        // blocks below 64 amplitudes: the spare lanes compute copies and store nothing
-        const uint32_t lm = lane & (n - 1u);
-        auto terms = [&](auto im, auto uc, uint32_t t) __attribute__((always_inline)) {
+        // blocks below 64 quads: the spare lanes compute copies and store nothing
+        const uint32_t lm = (lane * A) & (n - 1u);
+        const uint32_t at = lm | base;
+        auto terms = [&](auto im, auto odd, auto uc, uint32_t t) __attribute__((always_inline)) {
             constexpr int C = decltype(uc)::value;
-            V q[C][R];
+            Q q[C][R];
             T c[C];
-            uint32_t zm[C];
+            uint32_t zs[C];
 #pragma unroll
             for (int u = 0; u < C; ++u) {
                 const GatherTerm<T> rec = tb.rec[t + u];              // wave-uniform: scalar load
-                const uint32_t voff = (lm ^ (rec.x & 63u)) << SH;
-                const uint32_t so = base ^ (rec.x & ~63u);
+                const uint32_t voff = (lm ^ (rec.x & (ROW - A))) << SH;
+                const uint32_t so = base ^ (rec.x & ~(ROW - 1u));
 #pragma unroll
-                for (int r = 0; r < R; ++r) q[u][r] = load_amp(rs, voff, (so ^ (64u * r)) << SH, T(0));
-                const uint32_t par = __popc(lm & rec.z) + __popc(base & rec.z);
-                c[u] = flip(rec.c, par << 31);
-                zm[u] = rec.z >> 6;
+                for (int r = 0; r < R; ++r) q[u][r] = load_quad<T>(rs, voff, (so ^ (ROW * r)) << SH);
+                c[u] = flip(rec.c, __popc(at & rec.z) << 31);
+                zs[u] = rec.z;
             }
 #pragma unroll
             for (int u = 0; u < C; ++u)
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    uint32_t sg = (__popc(zm[u] & static_cast<uint32_t>(r)) & 1u) << 31;
-                    asm("" : "+s"(sg));                              // keep the register sign scalar
-                    const T cr = r == 0 ? c[u] : flip(c[u], sg);
-                    if (decltype(im)::value) {
-                        acc[r].x -= cr * q[u][r].y;
-                        acc[r].y += cr * q[u][r].x;
-                    } else {
-                        acc[r].x += cr * q[u][r].x;
-                        acc[r].y += cr * q[u][r].y;
-                    }
-                }
-        };
-        auto phase = [&](auto im, uint32_t lo, uint32_t hi) __attribute__((always_inline)) {
-            uint32_t t = lo;
-            for (; t + U <= hi; t += U) terms(im, std::integral_constant<int, U>{}, t);
-            for (; t < hi; ++t) terms(im, std::integral_constant<int, 1>{}, t);
-        };
-        const uint32_t nr = tb.n_real, ni = tb.K - tb.n_real;
-        phase(std::false_type{}, nr * slice / S, nr * (slice + 1) / S);
-        phase(std::true_type{}, nr + ni * slice / S, nr + ni * (slice + 1) / S);
-    }
-    __shared__ V part[S][R][64];
+                for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int r = 0; r < R; ++r) part[slice][r][lane] = acc[r];
+                    for (int e = 0; e < A; ++e) {
+                        uint32_t sg = __popc(zs[u] & static_cast<uint32_t>(ROW * r + e)) << 31;
+                        asm("" : "+s"(sg));                          // keep the sign of row and element scalar
+                        const T cr = r + e == 0 ? c[u] : flip(c[u], sg);
+                        const int f = A == 2 && decltype(odd)::value ? 1 - e : e;
+                        if (decltype(im)::value) {
+                            acc[r][2 * e] -= cr * q[u][r][2 * f + 1];
+                            acc[r][2 * e + 1] += cr * q[u][r][2 * f];
+                        } else {
+                            acc[r][2 * e] += cr * q[u][r][2 * f];
+                            acc[r][2 * e + 1] += cr * q[u][r][2 * f + 1];
+                        }
+                    }
+        };
+        // the slice's share of a run of terms of one phase and swap
+        const uint32_t lo = tb.K * slice / S, hi = tb.K * (slice + 1) / S;
+        auto run = [&](auto im, auto odd, uint32_t first, uint32_t end) __attribute__((always_inline)) {
+            uint32_t t = first > lo ? first : lo;
+            end = end < hi ? end : hi;
+            for (; t + U <= end; t += U) terms(im, odd, std::integral_constant<int, U>{}, t);
+            for (; t < end; ++t) terms(im, odd, std::integral_constant<int, 1>{}, t);
+        };
+        if constexpr (A == 2) {
+            run(std::false_type{}, std::false_type{}, 0, tb.cut[0]);
+            run(std::false_type{}, std::true_type{}, tb.cut[0], tb.cut[1]);
+            run(std::true_type{}, std::false_type{}, tb.cut[1], tb.cut[2]);
+            run(std::true_type{}, std::true_type{}, tb.cut[2], tb.K);
+        } else {
+            run(std::false_type{}, std::false_type{}, 0, tb.cut[1]);
+            run(std::true_type{}, std::false_type{}, tb.cut[1], tb.K);
+        }
+    }
+    __shared__ __attribute__((aligned(16))) T part[S][R][64][2 * A];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int i = 0; i < 2 * A; ++i) part[slice][r][lane][i] = acc[r][i];
     if constexpr (FUSE) epi.share();
     __syncthreads();
     if constexpr (FUSE) epi.scales();
     double dot = 0.0;
     // wave q sums register rows q, q + S, ..., the slices in order
     for (uint32_t r = slice; r < R; r += S) {
-        V s = part[0][r][lane];
+        Q s;
 #pragma unroll
-        for (int k = 1; k < S; ++k) {
-            s.x += part[k][r][lane].x;
-            s.y += part[k][r][lane].y;
-        }
-        const uint32_t m = base + 64u * r + lane;
+        for (int i = 0; i < 2 * A; ++i) s[i] = part[0][r][lane][i];
+#pragma unroll
+        for (int k = 1; k < S; ++k)
+#pragma unroll
+            for (int i = 0; i < 2 * A; ++i) s[i] += part[k][r][lane][i];
+        const uint32_t m = base + ROW * r + A * lane;
         if (m < n) {
-            if constexpr (FUSE) s = epi.row(s, m, dot);
-            y[vo + m] = s;
+            if constexpr (FUSE) {
+#pragma unroll
+                for (int e = 0; e < A; ++e) {
+                    const V w = epi.row(V{s[2 * e], s[2 * e + 1]}, m + e, dot);
+                    s[2 * e] = w.x;
+                    s[2 * e + 1] = w.y;
+                }
+            }
+            *reinterpret_cast<Q *>(y + vo + m) = s;
         }
     }
     if constexpr (FUSE) epi.finish(dot);
@@ -202,7 +248,8 @@ template <typename T, int R, int S>
 int go(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld, hipStream_t s,
        const LanczosFuse<T> *lf) {
     using V = typename V2t<T>::type;
-    const uint32_t g = (n + 64u * R - 1) / (64u * R);
+    constexpr uint32_t rows = 64u * Quad<T>::A * R;
+    const uint32_t g = (n + rows - 1) / rows;
     if (lf)
         hipLaunchKernelGGL((gather_sparse<T, R, S, true>), dim3(g), dim3(64 * S), 0, s, tb[0], tb[0],
                            reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld, *lf);
@@ -384,18 +431,16 @@ template <typename T>
 int launch_apply_gather(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, int nvec, uint64_t ld,
                         hipStream_t s, const LanczosFuse<T> *lf) {
     int g;
-    // Amplitudes per lane R and slices of the term list S, by block size alone (so that a vector's
-    // result does not depend on how many vectors or blocks share the launch): as many amplitudes
-    // per lane as leave about 2048 waves, 8 per CU, with at most 16 slices.  Measured with every
-    // R in {1, 2, 4} and S in {2, 4, 8, 16} from N = 16 to 36: within 10% of each other up to
-    // N = 34, where the call's host time (11 us) hides the kernel, and at N = 36, k = 8 R = 4 with
-    // S = 4 takes 18.8 us (complex64), S = 16 19.1 us, R = 2 with S = 2 19.3 us.
-    const uint32_t groups = (n + 63u) / 64u;
-    if (groups >= 2048u)
-        g = go<T, 4, 4>(tb, nblk, x, y, n, nvec, ld, s, lf);
-    else if (groups >= 1024u)
+    // Rows per wave R and slices of the term list S, by block size alone (so that a vector's
+    // result does not depend on how many vectors or blocks share the launch): as many rows per wave
+    // as leave about 2048 waves, 8 per CU, with at most 16 slices.  Measured with R in {1, 2, 4, 8} and S in
+    // {4, 8, 16} from N = 26 to 44: within 10% of each other below 2^10 rows, where the call's
+    // host time (6 us) hides the kernel; above, k = 8, R = 4 with S = 8 / R = 4 with S = 4 / R = 2 with S = 16:
+    // N = 36 complex64 10.4 / 11.4 / 10.7 us, N = 38 complex128 37.6 / 38.0 / 38.0 us.
+    const uint32_t rows = (n / Quad<T>::A + 63u) / 64u;
+    if (rows >= 1024u)
         g = go<T, 4, 8>(tb, nblk, x, y, n, nvec, ld, s, lf);
-    else if (groups >= 256u)
+    else if (rows >= 256u)
         g = go<T, 2, 16>(tb, nblk, x, y, n, nvec, ld, s, lf);
     else
         g = go<T, 1, 16>(tb, nblk, x, y, n, nvec, ld, s, lf);

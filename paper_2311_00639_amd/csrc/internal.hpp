@@ -49,7 +49,7 @@ struct DeviceSlab {
 };
 
 // One term of the gather kernels (16 bytes in either precision): y[m] += c (-1)^{popc(m & z)}
-// x[m ^ x], times i for the i-phase terms, which follow the n_real real-phase ones.
+// x[m ^ x], times i for the i-phase terms, which follow the real-phase ones.
 template <typename T> struct GatherTerm;
 template <> struct GatherTerm<float> {
     uint32_t x, z;
@@ -63,7 +63,8 @@ template <> struct GatherTerm<double> {
 template <typename T>
 struct GatherTerms {
     const GatherTerm<T> *rec = nullptr;
-    uint32_t n_real = 0, K = 0;
+    uint32_t K = 0;
+    uint32_t cut[3] = {0, 0, 0};             // ends of (real, even x), (real, odd x), (i-phase, even x)
 };
 
 // Terms of the grouped gather kernel: groups of equal x mask, cut into steps of four terms of
@@ -93,7 +94,7 @@ struct DeviceTables {            // per device, per block: the gather kernels' t
     bool in_slab = false;        // carved from a DeviceSlab: not freed by the library
     GatherTerm<float> *r32 = nullptr;
     GatherTerm<double> *r64 = nullptr;
-    uint32_t n_real = 0, K = 0;
+    uint32_t K = 0, cut[3] = {0, 0, 0};
     // the grouped form, for blocks that use it (null otherwise)
     uint32_t *head = nullptr;
     DenseTerm<float> *d32 = nullptr;
@@ -127,8 +128,13 @@ const std::vector<TiledVariant> &tiled_variants();
 // variant used before (or without) autotuning, for blocks of 2^L amplitudes
 template <typename T>
 int default_variant(int L);
-// smallest block (in qubits) served by the tiled kernel
+// smallest block (in qubits) that the tiled kernel can serve
 constexpr int kTiledMinL = 18;
+// Blocks that fit the 4 MiB L2 of one XCD are gathered straight from there.  Gather against tiled
+// apply at k = 4: 2^18 amplitudes 11.1 / 26 us in complex64 and 20 / 32 us in complex128 (4 MiB), 2^19
+// amplitudes 21.5 / 34 us in complex64 (4 MiB) and 47 / 43 us in complex128 (8 MiB), 2^20 amplitudes
+// 50 / 48 us in complex64 (8 MiB).
+constexpr uint64_t kGatherBytes = 4ULL << 20;
 
 // bit rotations within L bits: layout rotation s stores qubit (b + s) mod L at index bit b
 uint32_t rotr_bits(uint32_t v, int s, int L);
@@ -196,8 +202,8 @@ struct Hamiltonian {
     std::map<std::pair<int, int>, int> tuned;                   // (double?, device) -> variant
     std::set<std::pair<int, int>> pinned;                       // those of them chosen by syk_select_variant
     // whether the tiled kernel serves the block on the current device: blocks of at least
-    // 2^kTiledMinL amplitudes, except dense ones that the grouped gather kernel serves (unless
-    // a tiled variant is pinned)
+    // 2^kTiledMinL amplitudes, except, unless a tiled variant is pinned, those that fit an L2
+    // (kGatherBytes) and dense ones that the grouped gather kernel serves
     template <typename T>
     bool tiled();
     bool grouped();                       // the terms share x masks often enough for the grouped form
@@ -253,8 +259,8 @@ template <typename T>
 int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s);
 // upper bound on the partials apply_block_lanczos writes for a block of 2^L amplitudes (tiled:
-// one per tile of 2^10 or more; gather: at most 512 workgroups below the tiled size, and one
-// per 256 amplitudes for a dense block above it)
+// one per tile of 2^10 or more; gather: at most 512 workgroups below the tiled size, and at
+// most one per 256 amplitudes above it)
 inline uint64_t lanczos_partials_max(int L) {
     return L >= kTiledMinL ? 1ULL << (L > kDenseMaxL ? L - 10 : L - 8) : 512;
 }

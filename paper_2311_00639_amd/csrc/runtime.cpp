@@ -70,7 +70,7 @@ bool Hamiltonian::grouped() {
 template <typename T>
 bool Hamiltonian::tiled() {
     if (L < kTiledMinL) return false;
-    if (!grouped()) return true;
+    if ((2ULL * sizeof(T) << L) > kGatherBytes && !grouped()) return true;
     int d = 0;
     if (hipGetDevice(&d) != hipSuccess) d = 0;       // host-only queries: plans of device 0
     std::lock_guard<std::mutex> g(dev_mu);
@@ -150,7 +150,6 @@ const DeviceTables &Hamiltonian::tables(int blk) {
     const auto &bt = block_terms[blk];
     DeviceTables nt;
     nt.in_slab = slab != nullptr;
-    nt.n_real = static_cast<uint32_t>(n_real[blk]);
     nt.K = static_cast<uint32_t>(K);
     try {
         if (dense) {
@@ -169,9 +168,16 @@ const DeviceTables &Hamiltonian::tables(int blk) {
         } else {
             std::vector<GatherTerm<float>> r32(K);
             std::vector<GatherTerm<double>> r64(K);
-            for (int i = 0; i < K; ++i) {
-                r32[i] = {bt[i].x, bt[i].z, static_cast<float>(bt[i].c), 0u};
-                r64[i] = {bt[i].x, bt[i].z, bt[i].c};
+            // by phase, then by the lowest bit of the x mask, otherwise in the terms' order
+            uint32_t i = 0;
+            for (uint32_t kind = 0; kind < 4; ++kind) {
+                for (const BlockTerm &b : bt) {
+                    if ((b.imag ? 2u : 0u) + (b.x & 1u) != kind) continue;
+                    r32[i] = {b.x, b.z, static_cast<float>(b.c), 0u};
+                    r64[i] = {b.x, b.z, b.c};
+                    ++i;
+                }
+                if (kind < 3) nt.cut[kind] = i;
             }
             upload_vec(nt.r32, r32, slab);
             upload_vec(nt.r64, r64, slab);
@@ -196,8 +202,8 @@ static int apply_gather(Hamiltonian &h, const int (&blks)[2], int nblk, const T 
             g[b].rec = tb[b]->r32;
         else
             g[b].rec = tb[b]->r64;
-        g[b].n_real = tb[b]->n_real;
         g[b].K = tb[b]->K;
+        for (int i = 0; i < 3; ++i) g[b].cut[i] = tb[b]->cut[i];
     }
     return launch_apply_gather<T>(g, nblk, x, y, n, nvec, ld, s, lf);
 }
