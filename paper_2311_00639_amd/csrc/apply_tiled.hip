@@ -495,7 +495,27 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
     // Lanczos epilogue: w = H v_j - beta_{j-1} v_{j-1} and this workgroup's share of
     // Re <v_j, w> in double, with the scales of the unnormalised basis (see LanczosFuse; a zero
     // vector after an exact breakdown stays zero)
-    const double nj = sqrt(lf.norm2[lf.j]);
+    __shared__ double red[NT / 64];
+    double n2;
+    if (lf.n_parts > 0) {
+        // n_j^2 from the partials of the pass before (at most 1024, one line per wave out of L2): about
+        // 1 us at the end of the apply, where a launch of its own between the passes takes 6
+        double a = 0.0;
+        for (int p = tid; p < lf.n_parts; p += NT) a += lf.norm_parts[p];
+        for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
+        if ((tid & 63) == 0) red[tid >> 6] = a;
+        __syncthreads();
+        n2 = 0.0;
+        for (int w = 0; w < NT / 64; ++w) n2 += red[w];
+        __syncthreads();                              // red is written again below
+        if (blockIdx.x == 0 && tid == 0) {
+            lf.norm2[lf.j] = n2;
+            __hip_atomic_store(lf.norm2_host, n2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    } else {
+        n2 = lf.norm2[lf.j];
+    }
+    const double nj = sqrt(n2);
     const double njm = lf.j >= 1 ? sqrt(lf.norm2[lf.j - 1]) : 0.0;
     const T sc = nj > 1e-300 ? static_cast<T>(1.0 / nj) : T(0);
     const T bp = (lf.vprev && njm > 1e-300) ? static_cast<T>(nj / njm) : T(0);
@@ -532,7 +552,6 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
         epilogue(std::true_type{});
     else
         epilogue(std::false_type{});
-    __shared__ double red[NT / 64];
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
     if ((tid & 63) == 0) red[tid >> 6] = sum;
     __syncthreads();

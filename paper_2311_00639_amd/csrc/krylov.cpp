@@ -220,9 +220,8 @@ KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, cha
     p += up(static_cast<size_t>(8 * (m + 4)) * sizeof(double));
     fused_ = reinterpret_cast<double *>(p);
     norms_ = fused_ + fused_partials(n);
-    direct_ = !h_.tiled<T>();
-    big_ = n > kBigBlock;
-    n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ && !direct_ ? n / 256 : kNormParts));
+    big_ = n > kBigBlock && h_.tiled<T>();
+    n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ ? n / 256 : kNormParts));
 }
 
 template <typename T>
@@ -437,8 +436,7 @@ void KrylovRun<T>::run(std::complex<double> z, const T *v, T *out, const syk_kry
 // One fused Lanczos step: the apply, whose epilogue forms y = H v_j - beta_{j-1} v_{j-1} and the partial
 // sums of alpha_j, and one pass that writes u_{j+1} = y - alpha_j v_j unnormalised with the
 // partial sums of its norm (the scales 1 / n_i enter wherever a slot is read).  Who adds the partials up:
-//   gather kernels: each reader, behind its own loads (two launches a step);
-//   tiled, up to 2^21 amplitudes: alpha the residual pass, the norm a one-workgroup launch;
+//   gather kernels and, up to 2^21 amplitudes, the tiled ones: each reader (two launches a step);
 //   larger: launches of their own (too many partials for every workgroup to add).
 // Measured with the host following through pinned scalars instead of copies and stream waits:
 // N = 26, complex128 (12 steps) 582 -> 158 us a propagation, N = 40, complex128 (27 steps) 2187 ->
@@ -454,23 +452,19 @@ void KrylovRun<T>::enqueue(int j, const T *u0) {
     lf.j = j;
     lf.partials = fused_;
     lf.norm_parts = norms_;
-    lf.n_parts = n_norm_;
+    lf.n_parts = big_ ? 0 : n_norm_;
     lf.norm2_host = host_.dev(host_.norm2(j));
     pending_ = true;
     if (timer_) timer_->begin(s_);
     const int np = apply_block_lanczos<T>(h_, blk_, rot_, u, w, lf, s_);
     if (timer_) timer_->end(s_);
     double *al = alpha_ + j, *al_host = host_.dev(host_.alpha(j));
-    const bool reduce = n_norm_ <= kNormParts && np <= kNormParts;
+    const bool reduce = !big_ && np <= kNormParts;
     if (!reduce) launch_publish_sum(fused_, np, al, al_host, s_);
-    double *parts = n_norm_ <= kNormParts ? norms_ : fused_;      // fused_ is free once alpha_j is formed
+    double *parts = big_ ? fused_ : norms_;                      // fused_ is free once alpha_j is formed
     launch_lanczos_residual<T>(w, u, al, al_host, fused_, reduce ? np : 0, beta2_, j, n_, parts, n_norm_, s_);
-    if (direct_) return;                                             // the next apply sums the norm
-    double *nh = host_.dev(host_.norm2(j + 1));
-    if (n_norm_ <= kNormParts)
-        launch_publish_sum(parts, n_norm_, beta2_ + j + 1, nh, s_);
-    else
-        launch_publish_sum2(parts, n_norm_, partials_, beta2_ + j + 1, nh, s_);
+    if (big_) launch_publish_sum2(parts, n_norm_, partials_, beta2_ + j + 1, host_.dev(host_.norm2(j + 1)), s_);
+    // otherwise the next apply sums the norm
 }
 
 // The step after k at which the error estimate is formed: each one for large vectors, where a step
@@ -485,7 +479,7 @@ template <typename T>
 void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o,
                              syk_krylov_stats &st) {
     // the two-stage sum of large blocks stages 512 doubles in partials_
-    if (n_norm_ > kNormParts && static_cast<size_t>(n_part_) * 2 * (m_ + 2) < 512)
+    if (big_ && static_cast<size_t>(n_part_) * 2 * (m_ + 2) < 512)
         fail(SYK_EDEVICE, "partials buffer too small");
     double remaining = 1.0;
     const T *cur = v;
@@ -496,7 +490,7 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             fail(SYK_ENOTCONV, "Krylov propagation exceeded max_substeps");
         host_.next();
         pending_ = true;
-        if (direct_) {
+        if (!big_) {
             launch_norm2_partials<T>(cur, n_, norms_, n_norm_, s_);
         } else {
             launch_norm2_partials<T>(cur, n_, partials_, n_part_, s_);
@@ -515,9 +509,9 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             // Steps are enqueued ahead of the check, so that the GPU does not wait for the host:
             // two where a step takes microseconds, one for large blocks, none beyond the check
             // expected to converge (a step enqueued in vain costs its whole time).
-            const int ahead = std::min(check + (n_ >= kBigBlock ? 1 : 2), std::max(check, converges));
+            const int ahead = std::min(check + (big_ ? 1 : 2), std::max(check, converges));
             while (enq < std::min(ahead, m_)) enqueue(enq++, cur);
-            if (direct_ && enq == check)             // no later step to sum this norm
+            if (!big_ && enq == check)             // no later step to sum this norm
                 launch_publish_sum(norms_, n_norm_, beta2_ + enq, host_.dev(host_.norm2(enq)), s_);
             if (k == 0) {
                 n2[0] = host_.wait(host_.norm2(0), s_);

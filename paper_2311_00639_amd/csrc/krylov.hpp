@@ -125,7 +125,7 @@ class KrylovRun {
     T *basis_ = nullptr;
     double *partials_ = nullptr, *alpha_ = nullptr, *beta2_ = nullptr, *coef_ = nullptr, *scratch_ = nullptr;
     double *fused_ = nullptr, *norms_ = nullptr;
-    bool direct_ = false, big_ = false;   // gather kernels; more than 2^21 amplitudes
+    bool big_ = false;                    // tiled, more than 2^21 amplitudes
     int n_norm_ = 0;                      // partials of ||u||^2
     HostScalars host_;
     bool pending_ = false;                // the stream may hold steps that store to host_
