@@ -333,9 +333,9 @@ template int apply_block_lanczos<float>(Hamiltonian &, int, int, const float *, 
 template int apply_block_lanczos<double>(Hamiltonian &, int, int, const double *, double *,
                                          const LanczosFuse<double> &, hipStream_t);
 
-// Time every compiled variant of the tiled kernel on this Hamiltonian (block U, each in
-// its own planned layout) and keep the fastest for the current device.  x, y: scratch
-// device vectors of 2^L amplitudes.
+// Time the compiled variants of the tiled kernel on this Hamiltonian (block U, each in
+// its own planned layout; force: every one, also if the handle is tuned already) and keep the
+// fastest for the current device.  x, y: scratch device vectors of 2^L amplitudes.
 template <typename T>
 int autotune(Hamiltonian &h, T *x, T *y, hipStream_t s, bool force, std::vector<float> *times) {
     if (h.L < kTiledMinL) return -1;
@@ -347,6 +347,13 @@ int autotune(Hamiltonian &h, T *x, T *y, hipStream_t s, bool force, std::vector<
         if (it != h.tuned.end()) return it->second;
     }
     const auto &vars = tiled_variants<T>();
+    // On the way to an OTOC only the variants that can win are planned and timed: those with control
+    // blocks whose workgroup holds the most amplitudes that still leave 512 workgroups, or more (or within
+    // a factor two of the widest).  Of all 17, the fastest was one of these at every N from 40 to 56, k = 2, 4
+    // and 8; at N = 52, complex64, that is 4 variants and 0.13 s against 0.36 s.
+    int widest = 0;
+    for (const TiledVariant &tv : vars) widest = std::max(widest, tv.bt + tv.w);
+    widest = std::min(widest - 1, h.L - 9);
     const uint64_t n = 1ULL << h.L;
     const int np = reduction_blocks(n);
     double *part = nullptr;
@@ -361,6 +368,7 @@ int autotune(Hamiltonian &h, T *x, T *y, hipStream_t s, bool force, std::vector<
         launch_haar_raw<T>(1, 0, h.L - 1, 0, x, x + n, part, np, s);     // any finite data
         for (int v = 0; v < static_cast<int>(vars.size()); ++v) {
             if (vars[v].bt + vars[v].w + 3 > h.L) continue;              // needs >= 8 workgroups
+            if (!force && (vars[v].sr != 2 || vars[v].bt + vars[v].w < widest)) continue;
             const ApplyPlan &pl = h.plan<T>(0, h.internal_rotation<T>(v), v);
             launch_apply_tiled<T>(pl, x, y, 1, n, s);                    // warm-up
             SYK_HIP(hipEventRecord(e0, s));
