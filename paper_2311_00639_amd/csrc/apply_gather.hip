@@ -338,6 +338,7 @@ __global__ void __launch_bounds__(64 * S) gather_dense(DenseTerms<P> t0, DenseTe
     constexpr int R = Tile::R;
     constexpr int SH = sizeof(T) == 4 ? 3 : 4;
     constexpr int PER = kDenseSlices / S;                 // table slices per wave
+    constexpr int B = 4;                                  // steps whose operands are built together
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t base = blockIdx.x * (64u * R);
@@ -367,36 +368,43 @@ __global__ void __launch_bounds__(64 * S) gather_dense(DenseTerms<P> t0, DenseTe
     if (s0 < s1) {
         gather(tb.head[kDenseSlices + 1 + wave * PER]);
         M dre{}, dim{};
-        DenseTerm<P> nrec = tb.rec[static_cast<size_t>(s0) * 4 + lane];
+        // records as plain words (a struct copied whole would be kept in LDS)
+        using Raw = std::conditional_t<sizeof(P) == 4, u32x2, u32x4>;
+        static_assert(sizeof(Raw) == sizeof(DenseTerm<P>), "record words");
+        const Raw *recs = reinterpret_cast<const Raw *>(tb.rec);
+        Raw nrec = recs[static_cast<size_t>(s0) * 4 + lane];
         uint32_t nhdr = hdrs[s0 + (lane & 15u)];
         for (uint32_t st = s0; st < s1; st += kDenseChunk) {
             // the wave's reads of the chunk before are done: the products took their results
-            stage[lane] = nrec;
+            reinterpret_cast<Raw *>(stage)[lane] = nrec;
             const uint32_t hdr = nhdr;
             const uint32_t nx = st + kDenseChunk < s1 ? st + kDenseChunk : s0;
-            nrec = tb.rec[static_cast<size_t>(nx) * 4 + lane];
+            nrec = recs[static_cast<size_t>(nx) * 4 + lane];
             nhdr = hdrs[nx + (lane & 15u)];
             __builtin_amdgcn_wave_barrier();
-#pragma unroll 4
-            for (int u = 0; u < kDenseChunk; ++u) {
-                const uint32_t h = __builtin_amdgcn_readlane(hdr, u);
-                const DenseTerm<P> rec = stage[4 * u + kq];
-                P a, b;
-                signed_pair(__popc(am & rec.z), __popc(bm & rec.z), rec.c, a, b);
-                if (h & (1u << 30))
-                    dim = Tile::mma(a, b, dim);
-                else
-                    dre = Tile::mma(a, b, dre);
-                if (h & (1u << 31)) {
+            for (int u0 = 0; u0 < kDenseChunk; u0 += B) {
+                P a[B], b[B];
 #pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        const T cr = static_cast<T>(dre[r]), ci = static_cast<T>(dim[r]);
-                        acc[r].x += cr * q[r].x - ci * q[r].y;
-                        acc[r].y += cr * q[r].y + ci * q[r].x;
+                for (int u = 0; u < B; ++u) {
+                    const DenseTerm<P> rec = stage[4 * (u0 + u) + kq];
+                    signed_pair(__popc(am & rec.z), __popc(bm & rec.z), rec.c, a[u], b[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < B; u += 2) {
+                    const uint32_t h = __builtin_amdgcn_readlane(hdr, u0 + u);
+                    dre = Tile::mma(a[u], b[u], dre);
+                    dim = Tile::mma(a[u + 1], b[u + 1], dim);
+                    if (h & kDenseEnd) {
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            const T cr = static_cast<T>(dre[r]), ci = static_cast<T>(dim[r]);
+                            acc[r].x += cr * q[r].x - ci * q[r].y;
+                            acc[r].y += cr * q[r].y + ci * q[r].x;
+                        }
+                        dre = M{};
+                        dim = M{};
+                        gather(h & 0x0fffffffu);
                     }
-                    dre = M{};
-                    dim = M{};
-                    gather(h & 0x0fffffffu);
                 }
             }
             __builtin_amdgcn_wave_barrier();

@@ -43,12 +43,12 @@ uint64_t align_up(uint64_t b, uint64_t a) { return (b + a - 1) / a * a; }
 
 // Upper bound of the device bytes of one block's gather tables (runtime.cpp), each piece
 // 256-byte aligned in a slab: 32 bytes per term in the plain form; in the grouped form, used
-// from kDenseTermsPerMask = 4 terms per x mask on, each mask's two phases are padded to
-// multiples of four terms (at most 6 more per mask) and each of 16 slices to a multiple of
-// 16 steps of four terms, 25 bytes per padded term (a quarter of a header word included).
+// from kDenseTermsPerMask = 4 terms per x mask on, each mask's two phases are padded to the
+// same multiple of four terms (at most twice the mask's terms and 6 more) and each of 16 slices to a
+// multiple of 16 steps of four terms, 25 bytes per padded term (a quarter of a header word included).
 uint64_t tables_bound(uint64_t K) {
     static_assert(kDenseTermsPerMask >= 4, "padding bound");
-    const uint64_t padded = K + (6 * K + 3) / 4 + kDenseSlices * kDenseChunk * 4;
+    const uint64_t padded = 2 * K + (6 * K + 3) / 4 + kDenseSlices * kDenseChunk * 4;
     return std::max<uint64_t>(32 * (K + 1), 25 * padded + 4 * kDenseHead) + 5 * 256;
 }
 

@@ -68,13 +68,15 @@ struct GatherTerms {
 };
 
 // Terms of the grouped gather kernel: groups of equal x mask, cut into steps of four terms of
-// one phase (the last step of a phase padded with zero coefficients).  hdr[s] of step s: bit 30
-// i-phase, bit 31 the group ends here, and on such a step bits 0..27 the next group's x mask.
+// one phase, a real and an i-phase step in turn (padded with zero coefficients).  hdr[s] of the
+// real step s is zero but for the last pair of a group: kDenseEnd and in bits 0..27 the next
+// group's x mask.
 // The steps are dealt to kDenseSlices slices of whole groups, slice q holding steps
 // [cut[q], cut[q + 1]), a multiple of kDenseChunk (padded with empty steps); first[q] is the
 // x mask of its first group.  The header table starts with cut (kDenseSlices + 1 words) and
 // first (kDenseSlices), the step headers follow at word kDenseHead.
 constexpr int kDenseSlices = 16, kDenseChunk = 16, kDenseHead = 64;
+constexpr uint32_t kDenseEnd = 1u << 31;
 template <typename T> struct DenseTerm;
 template <> struct DenseTerm<float> {
     uint32_t z;

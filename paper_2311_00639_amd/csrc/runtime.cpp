@@ -93,7 +93,7 @@ static void dense_steps(const std::vector<BlockTerm> &bt, std::vector<uint32_t> 
     });
     struct Group {
         size_t lo, mid, hi;
-        size_t steps() const { return (mid - lo + 3) / 4 + (hi - mid + 3) / 4; }
+        size_t steps() const { return 2 * ((std::max(mid - lo, hi - mid) + 3) / 4); }
     };
     std::vector<Group> groups;
     size_t total = 0;
@@ -116,17 +116,16 @@ static void dense_steps(const std::vector<BlockTerm> &bt, std::vector<uint32_t> 
         while (gi < groups.size() && (done < until || q == kDenseSlices - 1)) {
             const Group &g = groups[gi++];
             done += g.steps();
-            for (int ph = 0; ph < 2; ++ph) {
-                const size_t lo = ph ? g.mid : g.lo, hi = ph ? g.hi : g.mid;
-                for (size_t t = lo; t < hi; t += 4) {
-                    hdr.push_back(ph ? 1u << 30 : 0u);
-                    for (size_t u = t; u < t + 4; ++u) {
+            for (size_t p = 0; p < g.steps(); p += 2)
+                for (int ph = 0; ph < 2; ++ph) {
+                    const size_t lo = (ph ? g.mid : g.lo) + 2 * p, hi = ph ? g.hi : g.mid;
+                    hdr.push_back(0u);
+                    for (size_t u = lo; u < lo + 4; ++u) {
                         z.push_back(u < hi ? bt[order[u]].z : 0u);
                         c.push_back(u < hi ? bt[order[u]].c : 0.0);
                     }
                 }
-            }
-            hdr.back() |= (1u << 31) | (gi < groups.size() ? bt[order[groups[gi].lo]].x : 0u);
+            hdr[hdr.size() - 2] = kDenseEnd | (gi < groups.size() ? bt[order[groups[gi].lo]].x : 0u);
         }
         while ((hdr.size() - cut[q]) % kDenseChunk != 0) {
             hdr.push_back(0u);
