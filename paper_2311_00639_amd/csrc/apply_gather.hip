@@ -267,13 +267,15 @@ int go(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, in
 // (about 19 in dense SYK).  D is a matrix product: over a tile of 256 amplitudes m = 16 i + j the
 // sign splits into (row, term) and (term, column) factors, D = A B with A[i][t] = c_t s_t(base + 16 i)
 // and B[t][j] = s_t(j) = +-1, and four terms are one 16 x 16 x 4 matrix instruction (products by
-// +-1 are exact, sums are in the vectors' precision or better).  Building A and B costs six vector
-// operations per step of four terms and wave, whatever the tile; summed on the vector unit it
-// was about six per term and amplitude.  Bound by issue (readlane, two uniform branches and the
-// operand building of every step): about 95 clocks per step and SIMD, where the instruction itself
-// takes 16 to 64.  One apply, complex64 / complex128: N = 30 (K = 27405) 84 / 87 us, against
-// 278 / 391 us summed on the vector unit; N = 38 (K = 73815) 0.80 / 1.24 ms and N = 42 (K = 111930)
-// 4.2 / 6.9 ms, against 9.1 ms (N = 38, complex64) and 26 ms (N = 42) term by term in the tiled kernel.
+// +-1 are exact, sums are in the vectors' precision or better).  Summed on the vector unit it was
+// about six operations per term and amplitude.  Bound by issue: matrix and vector instructions
+// of a SIMD add up here, 32 clocks (16 x 16 x 4, 32-bit) and about 16 vector operations per step,
+// six to build A and B and the rest the complex product of a group of 16 terms.  Hence the table
+// pairs a real with an i-phase step, so that a step needs no phase branch and two sums run
+// independently, and the operands of four steps are built before their products, which hides the
+// LDS reads: N = 30 86 -> 59 us (complex128), N = 38 0.82 -> 0.64 / 1.29 -> 1.05 ms (complex64 /
+// complex128).  Term by term on the vector unit N = 30 took 278 / 391 us, in the tiled kernel N = 38 9.1 ms
+// (complex64).
 //
 // The matrix instruction of a wave's tile, in the precision P of the sums.  rows(l): the amplitude
 // offset of the row of A that lane l supplies, cols(l): that of the column of B; both supply
@@ -483,15 +485,18 @@ int launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x,
                                d[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld,
                                LanczosFuse<T>{});
     };
-    // Small blocks take 64-amplitude tiles to reach more CUs (N = 30: 84 us against 95 us in
-    // complex64 and 87 us against 140 us in complex128 with 256-amplitude tiles), larger ones 256
-    // (four times the amplitudes per step; N = 34: 153 / 243 us).  Sixteen waves share a tile up
-    // to 2^17 amplitudes, eight above (N = 38, complex128: 1.24 ms against 1.42 ms).
-    if (n <= 1u << 15)
+    // Small blocks take 64-amplitude tiles to reach more CUs (N = 30: 56 us against 70 us in
+    // complex64 and 59 us against 106 us in complex128 with 256-amplitude tiles), larger ones 256
+    // (four times the amplitudes per step; N = 32, complex64: 92 us against 129 us; N = 32, complex128: 136 us
+    // against 134 us).  Sixteen waves share a tile while the tiles are few, and in complex64 always, as its sums
+    // are then shorter (N = 38: 635 us against 650 us, error 3.1e-7 against 4.2e-7); complex128 takes eight
+    // from 2^17 amplitudes (N = 38: 1.05 ms against 1.13 ms).
+    constexpr bool f32 = sizeof(T) == 4;
+    if (n <= (f32 ? 1u << 14 : 1u << 15))
         go(double(0), MfmaRow{}, std::integral_constant<int, 16>{});
-    else if (n <= 1u << 17)
+    else if (f32 || n <= 1u << 16)
         go(T(0), MfmaTile<T>{}, std::integral_constant<int, 16>{});
-    else
+    else if constexpr (!f32)
         go(T(0), MfmaTile<T>{}, std::integral_constant<int, 8>{});
     SYK_HIP(hipGetLastError());
     return g;
