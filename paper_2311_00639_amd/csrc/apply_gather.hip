@@ -492,7 +492,7 @@ int launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x,
     // are then shorter (N = 38: 635 us against 650 us, error 3.1e-7 against 4.2e-7); complex128 takes eight
     // from 2^17 amplitudes (N = 38: 1.05 ms against 1.13 ms).
     constexpr bool f32 = sizeof(T) == 4;
-    if (n <= (f32 ? 1u << 14 : 1u << 15))
+    if (n <= (f32 ? 1u << kDenseRowL32 : 1u << (kDenseRowL32 + 1)))
         go(double(0), MfmaRow{}, std::integral_constant<int, 16>{});
     else if (f32 || n <= 1u << 16)
         go(T(0), MfmaTile<T>{}, std::integral_constant<int, 16>{});

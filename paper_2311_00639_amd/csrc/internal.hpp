@@ -94,6 +94,7 @@ struct DenseTerms {
 
 struct DeviceTables {            // per device, per block: the gather kernels' term tables
     bool in_slab = false;        // carved from a DeviceSlab: not freed by the library
+    char *mem = nullptr;         // holds what the pointers below point into
     GatherTerm<float> *r32 = nullptr;
     GatherTerm<double> *r64 = nullptr;
     uint32_t K = 0, cut[3] = {0, 0, 0};
@@ -107,6 +108,8 @@ struct DeviceTables {            // per device, per block: the gather kernels' t
 // 256 MB last-level cache; larger dense blocks stay with the tiled kernel, unmeasured).
 constexpr int kDenseTermsPerMask = 4;
 constexpr int kDenseMinL = 6, kDenseMaxL = 22;
+// complex64 blocks up to this size take 64-amplitude tiles (complex128: one more)
+constexpr int kDenseRowL32 = 14;
 
 // distinct x masks of a block's terms: the groups the gather kernel loads once each
 int gather_groups(const std::vector<BlockTerm> &terms);

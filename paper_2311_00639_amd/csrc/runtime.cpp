@@ -33,31 +33,75 @@ static void free_tables(DeviceTables &t) {
         t = DeviceTables{};
         return;
     }
-    ignore_status(hipFree(t.r32));
-    ignore_status(hipFree(t.r64));
-    ignore_status(hipFree(t.head));
-    ignore_status(hipFree(t.d32));
-    ignore_status(hipFree(t.d64));
+    ignore_status(hipFree(t.mem));
     t = DeviceTables{};
 }
 
 int gather_groups(const std::vector<BlockTerm> &terms) {
-    std::vector<uint32_t> xs;
-    xs.reserve(terms.size());
-    for (const BlockTerm &t : terms) xs.push_back(t.x);
-    std::sort(xs.begin(), xs.end());
-    return static_cast<int>(std::unique(xs.begin(), xs.end()) - xs.begin());
+    if (terms.size() < 1024) {               // few: cheaper than a bit per mask
+        std::vector<uint32_t> xs;
+        for (const BlockTerm &t : terms) xs.push_back(t.x);
+        std::sort(xs.begin(), xs.end());
+        return static_cast<int>(std::unique(xs.begin(), xs.end()) - xs.begin());
+    }
+    uint32_t top = 0;
+    for (const BlockTerm &t : terms) top |= t.x;
+    std::vector<uint64_t> seen((static_cast<size_t>(top) >> 6) + 1, 0);
+    int n = 0;
+    for (const BlockTerm &t : terms) {
+        const uint64_t bit = 1ULL << (t.x & 63u);
+        n += (seen[t.x >> 6] & bit) == 0;
+        seen[t.x >> 6] |= bit;
+    }
+    return n;
 }
 
-template <typename U>
-static void upload_vec(U *&d, const std::vector<U> &h, DeviceSlab *slab) {
-    const size_t bytes = std::max<size_t>(h.size(), 1) * sizeof(U);
-    if (slab)
-        d = static_cast<U *>(slab->take(bytes, "term tables"));
-    else
-        SYK_HIP(hipMalloc(reinterpret_cast<void **>(&d), bytes));
-    if (!h.empty()) SYK_HIP(hipMemcpy(d, h.data(), h.size() * sizeof(U), hipMemcpyHostToDevice));
+// the terms' indices by x mask, then phase (real first), otherwise in the terms' order: a radix
+// sort, as comparing 27405 terms took most of the first apply at N = 30
+static std::vector<int> order_by_mask(const std::vector<BlockTerm> &bt) {
+    std::vector<int> a(bt.size()), b(bt.size());
+    uint32_t top = 0;
+    for (size_t i = 0; i < bt.size(); ++i) {
+        a[i] = static_cast<int>(i);
+        top |= bt[i].x;
+    }
+    auto key = [&](int i) { return (static_cast<uint64_t>(bt[i].x) << 1) | (bt[i].imag ? 1u : 0u); };
+    constexpr int kBits = 8;
+    for (int sh = 0; sh == 0 || ((static_cast<uint64_t>(top) << 1) >> sh) != 0; sh += kBits) {
+        size_t at[(1 << kBits) + 1] = {};
+        for (int i : a) ++at[((key(i) >> sh) & ((1 << kBits) - 1)) + 1];
+        for (int k = 0; k < 1 << kBits; ++k) at[k + 1] += at[k];
+        for (int i : a) b[at[(key(i) >> sh) & ((1 << kBits) - 1)]++] = i;
+        a.swap(b);
+    }
+    return a;
 }
+
+// One allocation and one copy for the pieces of a block's tables (each 256-byte aligned): three
+// of each were most of the first apply of a dense block.
+namespace {
+class TableImage {
+  public:
+    template <typename U>
+    size_t add(const std::vector<U> &v) {
+        const size_t at = bytes_.size();
+        bytes_.resize((at + std::max<size_t>(v.size(), 1) * sizeof(U) + 255) & ~static_cast<size_t>(255));
+        if (!v.empty()) std::memcpy(bytes_.data() + at, v.data(), v.size() * sizeof(U));
+        return at;
+    }
+    char *upload(DeviceTables &t, DeviceSlab *slab) {
+        if (slab)
+            t.mem = static_cast<char *>(slab->take(bytes_.size(), "term tables"));
+        else
+            SYK_HIP(hipMalloc(reinterpret_cast<void **>(&t.mem), bytes_.size()));
+        SYK_HIP(hipMemcpy(t.mem, bytes_.data(), bytes_.size(), hipMemcpyHostToDevice));
+        return t.mem;
+    }
+
+  private:
+    std::vector<char> bytes_;
+};
+}  // namespace
 
 bool Hamiltonian::grouped() {
     std::lock_guard<std::mutex> g(dev_mu);
@@ -86,11 +130,7 @@ static void dense_steps(const std::vector<BlockTerm> &bt, std::vector<uint32_t> 
     head.assign(kDenseHead, 0u);
     uint32_t *cut = head.data(), *first = head.data() + kDenseSlices + 1;
     static_assert(2 * kDenseSlices + 1 <= kDenseHead, "table head");
-    std::vector<int> order(bt.size());
-    for (size_t a = 0; a < order.size(); ++a) order[a] = static_cast<int>(a);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-        return bt[a].x != bt[b].x ? bt[a].x < bt[b].x : (!bt[a].imag && bt[b].imag);
-    });
+    const std::vector<int> order = order_by_mask(bt);
     struct Group {
         size_t lo, mid, hi;
         size_t steps() const { return 2 * ((std::max(mid - lo, hi - mid) + 3) / 4); }
@@ -150,20 +190,22 @@ const DeviceTables &Hamiltonian::tables(int blk) {
     DeviceTables nt;
     nt.in_slab = slab != nullptr;
     nt.K = static_cast<uint32_t>(K);
+    TableImage img;
     try {
         if (dense) {
             std::vector<uint32_t> head, z;
             std::vector<double> c;
             dense_steps(bt, head, z, c);
-            std::vector<DenseTerm<float>> d32(z.size());
+            // the 64-amplitude tiles of small blocks sum in 64 bits, whatever the vectors' type
+            std::vector<DenseTerm<float>> d32(L > kDenseRowL32 ? z.size() : 0);
             std::vector<DenseTerm<double>> d64(z.size());
-            for (size_t i = 0; i < z.size(); ++i) {
-                d32[i] = {z[i], static_cast<float>(c[i])};
-                d64[i] = {z[i], 0u, c[i]};
-            }
-            upload_vec(nt.head, head, slab);
-            upload_vec(nt.d32, d32, slab);
-            upload_vec(nt.d64, d64, slab);
+            for (size_t i = 0; i < d32.size(); ++i) d32[i] = {z[i], static_cast<float>(c[i])};
+            for (size_t i = 0; i < z.size(); ++i) d64[i] = {z[i], 0u, c[i]};
+            const size_t oh = img.add(head), o32 = img.add(d32), o64 = img.add(d64);
+            char *m = img.upload(nt, slab);
+            nt.head = reinterpret_cast<uint32_t *>(m + oh);
+            nt.d32 = reinterpret_cast<DenseTerm<float> *>(m + o32);
+            nt.d64 = reinterpret_cast<DenseTerm<double> *>(m + o64);
         } else {
             std::vector<GatherTerm<float>> r32(K);
             std::vector<GatherTerm<double>> r64(K);
@@ -178,8 +220,10 @@ const DeviceTables &Hamiltonian::tables(int blk) {
                 }
                 if (kind < 3) nt.cut[kind] = i;
             }
-            upload_vec(nt.r32, r32, slab);
-            upload_vec(nt.r64, r64, slab);
+            const size_t o32 = img.add(r32), o64 = img.add(r64);
+            char *m = img.upload(nt, slab);
+            nt.r32 = reinterpret_cast<GatherTerm<float> *>(m + o32);
+            nt.r64 = reinterpret_cast<GatherTerm<double> *>(m + o64);
         }
     } catch (...) {
         free_tables(nt);
