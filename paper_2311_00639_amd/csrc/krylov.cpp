@@ -439,8 +439,8 @@ void KrylovRun<T>::run(std::complex<double> z, const T *v, T *out, const syk_kry
 //   gather kernels and, up to 2^21 amplitudes, the tiled ones: each reader (two launches a step);
 //   larger: launches of their own (too many partials for every workgroup to add).
 // Measured with the host following through pinned scalars instead of copies and stream waits:
-// N = 26, complex128 (12 steps) 582 -> 158 us a propagation, N = 40, complex128 (27 steps) 2187 ->
-// 1433 us; from N = 50 on the apply is nearly all of it (17.9 -> 17.2 ms).
+// N = 26, complex128 (12 steps) 582 -> 152 us a propagation, N = 40, complex128 (27 steps) 2187 ->
+// 1383 us; from N = 50 on the apply is nearly all of it (17.9 -> 17.2 ms).
 template <typename T>
 void KrylovRun<T>::enqueue(int j, const T *u0) {
     const T *u = j == 0 ? u0 : vec(j);

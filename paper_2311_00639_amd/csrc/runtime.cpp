@@ -271,14 +271,15 @@ const std::vector<TiledVariant> &tiled_variants<double>() {
                                                 {11, 1, 2, 1, 2, 2, 2}, {10, 1, 2, 1, 4, 2, 2}};
     return v;
 }
-// Before (or without) autotuning: the first of a preference order (control-block records
-// with four, two, one tile per workgroup, then the same tile counts with per-term records;
-// the fastest at N = 56 when measured) whose grid still has >= 256 workgroups, else the
-// variant with the most workgroups.
+// Before (or without) autotuning: the first of a preference order (control-block records, four, two,
+// one tile per workgroup, then the next smaller tile at two workgroups per CU) whose grid still
+// has >= 256 workgroups, else the variant with the most workgroups.  All variants at k = 2, 4, 8: the
+// choice is within 6% of the fastest from N = 40 to 48; the smaller tile (2^11) against the smallest (2^10) at
+// N = 42, complex64, k = 4: 46.8 / 49.0 us.
 template <typename T>
 int default_variant(int L) {
     const auto &v = tiled_variants<T>();
-    for (int pref : {10, 9, 8, 6, 5, 0}) {
+    for (int pref : {10, 9, 8, 11}) {
         const TiledVariant &tv = v.at(pref);
         if (L >= tv.bt + tv.w + 8) return pref;
     }
