@@ -260,6 +260,220 @@ int go(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, in
     return static_cast<int>(g);
 }
 
+// ------------------------------------------------------------------ one launch per Lanczos step
+// u_j = a g - b u_{j-2} - c u_{j-1} with the scales of the unnormalised basis (a zero vector after an exact
+// breakdown stays zero): w = g / n_{j-1} - (n_{j-1} / n_{j-2}) u_{j-2} and u_j = w - (alpha_{j-1} / n_{j-1}) u_{j-1},
+// alpha_{j-1} = Re <v_{j-1}, w>.  Every wave adds up the sums of the step before in the same order.
+template <typename T>
+struct StepScales {
+    T a, b, c;
+    __device__ __forceinline__ StepScales(const LanczosStep<T> &st, uint32_t lane, bool publish) {
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        for (int p = lane; p < st.np; p += 64) {
+            s0 += st.parts[3 * p];
+            s1 += st.parts[3 * p + 1];
+            s2 += st.parts[3 * p + 2];
+        }
+        const double n2 = st.j >= 2 ? sqrt(st.norm2[st.j - 2]) : 0.0;
+        for (int off = 32; off > 0; off >>= 1) {
+            s0 += __shfl_xor(s0, off, 64);
+            s1 += __shfl_xor(s1, off, 64);
+            s2 += __shfl_xor(s2, off, 64);
+        }
+        const double n1 = sqrt(s0), inv = n1 > 1e-300 ? 1.0 / n1 : 0.0, inv2 = n2 > 1e-300 ? 1.0 / n2 : 0.0;
+        const double al = (s0 > 1e-300 ? s1 / s0 : 0.0) - s2 * inv2;
+        a = static_cast<T>(inv);
+        b = static_cast<T>(n1 * inv2);
+        c = static_cast<T>(al * inv);
+        if (publish) {
+            st.norm2[st.j - 1] = s0;
+            st.alpha[st.j - 1] = al;
+            __hip_atomic_store(st.norm2_host, s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(st.alpha_host, al, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+    __device__ __forceinline__ T operator()(T g, T u2, T u1) const {
+        const T w = a * g - b * u2;
+        return w - c * u1;
+    }
+};
+
+// gather_sparse with u_j formed from three quads at every partner.  A small propagation is bound by the
+// time from one dependent launch to the next (4 to 5 us) and not by what the kernels do: with two
+// launches a step it took 120 us from N = 20 to 32.  Now the chain of one kernel bounds it: the sums of the
+// step before, then a slice's terms, four at a time.
+template <typename T, int S, bool FIRST>
+__global__ void __launch_bounds__(64 * S) lanczos_step(GatherTerms<T> tb, LanczosStep<T> st, uint32_t n) {
+    using Q = typename Quad<T>::V;
+    constexpr int A = Quad<T>::A;
+    constexpr int SH = sizeof(T) == 4 ? 3 : 4;
+    constexpr int R = 1, U = 4;                      // rows per wave, terms in flight
+    constexpr uint32_t ROW = 64u * A;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t slice = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t base = blockIdx.x * (ROW * R);
+    auto vector = [&](const T *v) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(v), 0, static_cast<int>(n << SH), kBufferWord3);
+    };
+    const bool two = !FIRST && st.j >= 2;
+    // constant memory: the loads stay scalar behind this kernel's stores
+    using Rec = const __attribute__((address_space(4))) GatherTerm<T>;
+    Rec *recs = (Rec *)reinterpret_cast<uintptr_t>(tb.rec);
+    const __amdgpu_buffer_rsrc_t rg = vector(st.g), r1 = vector(FIRST ? st.g : st.u1),
+                                 r2 = vector(two ? st.u2 : st.g);
+    const uint32_t lm = (lane * A) & (n - 1u), at = lm | base;
+    // this wave's own row
+    const uint32_t mine = base + ROW * slice + A * lane;
+    const bool writes = slice < R && mine < n;
+    const uint32_t own = (mine & (n - 1u)) << SH;
+    Q ug = load_quad<T>(rg, own, 0), u1{}, u2{};
+    if constexpr (!FIRST) u1 = load_quad<T>(r1, own, 0);
+    if (two) u2 = load_quad<T>(r2, own, 0);
+    T ca = T(1), cb = T(0), cc = T(0);
+    if constexpr (!FIRST) {
+        const StepScales<T> sc(st, lane, threadIdx.x == 0 && blockIdx.x == 0);
+        ca = sc.a, cb = sc.b, cc = sc.c;
+    }
+    auto form = [&](Q g, Q p2, Q p1) __attribute__((always_inline)) {
+        if constexpr (!FIRST) {
+#pragma unroll
+            for (int i = 0; i < 2 * A; ++i) {
+                const T w = ca * g[i] - cb * p2[i];
+                g[i] = w - cc * p1[i];
+            }
+        }
+        return g;
+    };
+    const Q u = form(ug, u2, u1);
+    if (!FIRST && writes) *reinterpret_cast<Q *>(st.u + 2 * static_cast<uint64_t>(mine)) = u;
+    Q acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = Q(T(0));
+    auto terms = [&](auto im, auto odd, auto uc, uint32_t t) __attribute__((always_inline)) {
+        constexpr int C = decltype(uc)::value;
+        Q q[C][R], q1[C][R], q2[C][R];
+        T c[C];
+        uint32_t zs[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+            const uint32_t x = recs[t + k].x, z = recs[t + k].z;
+            const uint32_t voff = (lm ^ (x & (ROW - A))) << SH;
+            const uint32_t so = base ^ (x & ~(ROW - 1u));
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint32_t off = (so ^ (ROW * r)) << SH;
+                q[k][r] = load_quad<T>(rg, voff, off);
+                if constexpr (!FIRST) {
+                    q1[k][r] = load_quad<T>(r1, voff, off);
+                    q2[k][r] = two ? load_quad<T>(r2, voff, off) : Q(T(0));
+                }
+            }
+            c[k] = flip(static_cast<T>(recs[t + k].c), __popc(at & z) << 31);
+            zs[k] = z;
+        }
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const Q v = FIRST ? q[k][r] : form(q[k][r], q2[k][r], q1[k][r]);
+#pragma unroll
+                for (int e = 0; e < A; ++e) {
+                    uint32_t sg = __popc(zs[k] & static_cast<uint32_t>(ROW * r + e)) << 31;
+                    asm("" : "+s"(sg));                              // keep the sign of row and element scalar
+                    const T cr = r + e == 0 ? c[k] : flip(c[k], sg);
+                    const int f = A == 2 && decltype(odd)::value ? 1 - e : e;
+                    if (decltype(im)::value) {
+                        acc[r][2 * e] -= cr * v[2 * f + 1];
+                        acc[r][2 * e + 1] += cr * v[2 * f];
+                    } else {
+                        acc[r][2 * e] += cr * v[2 * f];
+                        acc[r][2 * e + 1] += cr * v[2 * f + 1];
+                    }
+                }
+            }
+    };
+    const uint32_t lo = tb.K * slice / S, hi = tb.K * (slice + 1) / S;
+    auto run = [&](auto im, auto odd, uint32_t first, uint32_t end) __attribute__((always_inline)) {
+        uint32_t t = first > lo ? first : lo;
+        end = end < hi ? end : hi;
+        for (; t + U <= end; t += U) terms(im, odd, std::integral_constant<int, U>{}, t);
+        for (; t < end; ++t) terms(im, odd, std::integral_constant<int, 1>{}, t);
+    };
+    if constexpr (A == 2) {
+        run(std::false_type{}, std::false_type{}, 0, tb.cut[0]);
+        run(std::false_type{}, std::true_type{}, tb.cut[0], tb.cut[1]);
+        run(std::true_type{}, std::false_type{}, tb.cut[1], tb.cut[2]);
+        run(std::true_type{}, std::true_type{}, tb.cut[2], tb.K);
+    } else {
+        run(std::false_type{}, std::false_type{}, 0, tb.cut[1]);
+        run(std::true_type{}, std::false_type{}, tb.cut[1], tb.K);
+    }
+    __shared__ __attribute__((aligned(16))) T part[S][R][64][2 * A];
+    __shared__ double sh[R][3];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int i = 0; i < 2 * A; ++i) part[slice][r][lane][i] = acc[r][i];
+    __syncthreads();
+    if (slice < R) {
+        double d0 = 0.0, d1 = 0.0, d2 = 0.0;
+        if (writes) {
+            Q s;
+#pragma unroll
+            for (int i = 0; i < 2 * A; ++i) s[i] = part[0][slice][lane][i];
+#pragma unroll
+            for (int k = 1; k < S; ++k)
+#pragma unroll
+                for (int i = 0; i < 2 * A; ++i) s[i] += part[k][slice][lane][i];
+            *reinterpret_cast<Q *>(st.gout + 2 * static_cast<uint64_t>(mine)) = s;
+#pragma unroll
+            for (int i = 0; i < 2 * A; ++i) {
+                d0 += static_cast<double>(u[i]) * u[i];
+                d1 += static_cast<double>(u[i]) * s[i];
+                if constexpr (!FIRST) d2 += static_cast<double>(u[i]) * u1[i];
+            }
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            d0 += __shfl_down(d0, off, 64);
+            d1 += __shfl_down(d1, off, 64);
+            d2 += __shfl_down(d2, off, 64);
+        }
+        if (lane == 0) {
+            sh[slice][0] = d0;
+            sh[slice][1] = d1;
+            sh[slice][2] = d2;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double v = 0.0;
+        for (int r = 0; r < R; ++r) v += sh[r][threadIdx.x];
+        st.out[3 * blockIdx.x + threadIdx.x] = v;
+    }
+}
+
+// the end of the sequence: alpha_{j-1} and ||u_j||^2 without H u_j, in one workgroup
+template <typename T>
+__global__ void __launch_bounds__(1024) lanczos_close(LanczosStep<T> st, uint32_t n) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const StepScales<T> sc(st, lane, threadIdx.x == 0);
+    const bool two = st.j >= 2;
+    double sum = 0.0;
+    for (uint32_t i = threadIdx.x; i < 2 * n; i += 1024) {
+        const T v = sc(st.g[i], two ? st.u2[i] : T(0), st.u1[i]);
+        sum += static_cast<double>(v) * v;
+    }
+    __shared__ double sh[16];
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+    if (lane == 0) sh[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double v = 0.0;
+        for (int k = 0; k < 16; ++k) v += sh[k];
+        __hip_atomic_store(st.next_host, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // ------------------------------------------------------------------ grouped by x mask
 // Terms that share an x mask act on the partner x[m ^ x] as one complex diagonal
 //   D(m) = sum_t c_t (-1)^popc(m & z_t)   (real-phase terms in Re D, i-phase terms in Im D),
@@ -502,7 +716,28 @@ int launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x,
     return g;
 }
 
+template <typename T>
+int launch_lanczos_step(const GatherTerms<T> &tb, const LanczosStep<T> &st, uint32_t n, hipStream_t s) {
+    // at most 2^13 amplitudes, so one row per wave and at most 128 workgroups
+    constexpr uint32_t row = 64u * Quad<T>::A;
+    const int g = static_cast<int>((n + row - 1) / row);
+    if (st.j == 0)
+        hipLaunchKernelGGL((lanczos_step<T, 16, true>), dim3(g), dim3(1024), 0, s, tb, st, n);
+    else
+        hipLaunchKernelGGL((lanczos_step<T, 16, false>), dim3(g), dim3(1024), 0, s, tb, st, n);
+    SYK_HIP(hipGetLastError());
+    return g;
+}
+
+template <typename T>
+void launch_lanczos_close(const LanczosStep<T> &st, uint32_t n, hipStream_t s) {
+    hipLaunchKernelGGL(lanczos_close<T>, dim3(1), dim3(1024), 0, s, st, n);
+    SYK_HIP(hipGetLastError());
+}
+
 #define SYK_INST(T)                                                                                                 \
+    template int launch_lanczos_step<T>(const GatherTerms<T> &, const LanczosStep<T> &, uint32_t, hipStream_t);     \
+    template void launch_lanczos_close<T>(const LanczosStep<T> &, uint32_t, hipStream_t);                           \
     template int launch_apply_dense<T>(const DeviceTables *const (&)[2], int, const T *, T *, uint32_t, int,        \
                                        uint64_t, hipStream_t, const LanczosFuse<T> *);                              \
     template int launch_apply_gather<T>(const GatherTerms<T> (&)[2], int, const T *, T *, uint32_t, int, uint64_t,  \

@@ -180,6 +180,22 @@ struct LanczosFuse {
     double *norm2_host = nullptr;      // pinned host memory, the slot of n_j^2
 };
 
+// One launch per Lanczos step (small sparse blocks).  Step j forms u_j wherever it reads it, from
+// g = H u_{j-1}, u1 = u_{j-1}, u2 = u_{j-2} and the sums over them that step j - 1 left (three per workgroup:
+// ||u_{j-1}||^2, Re <u_{j-1}, g>, Re <u_{j-1}, u_{j-2}>), writes u_j (j >= 1) and H u_j, and leaves its own sums.
+// Step 0 reads u_0 as g.
+template <typename T>
+struct LanczosStep {
+    const T *g = nullptr, *u1 = nullptr, *u2 = nullptr;
+    T *u = nullptr, *gout = nullptr;
+    const double *parts = nullptr;
+    int np = 0, j = 0;
+    double *out = nullptr;                            // 3 per workgroup
+    double *norm2 = nullptr, *alpha = nullptr;        // device, indexed by step
+    double *norm2_host = nullptr, *alpha_host = nullptr;   // pinned slots of step j - 1
+    double *next_host = nullptr;                      // close: the slot of ||u_j||^2
+};
+
 // ------------------------------------------------------------------ host-side model
 uint64_t splitmix_mix(uint64_t z);
 
@@ -263,6 +279,16 @@ void apply_full(Hamiltonian &h, const T *x, T *y, int nvec, uint64_t ld, hipStre
 template <typename T>
 int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s);
+// whether one launch per Lanczos step serves the block (apply_step)
+template <typename T>
+bool one_launch_steps(Hamiltonian &h);
+// Lanczos step st.j of a block; returns the number of workgroups (triples of sums in st.out)
+template <typename T>
+int apply_step(Hamiltonian &h, int blk, const LanczosStep<T> &st, hipStream_t s);
+template <typename T>
+void launch_lanczos_close(const LanczosStep<T> &st, uint32_t n, hipStream_t s);
+template <typename T>
+int launch_lanczos_step(const GatherTerms<T> &tb, const LanczosStep<T> &st, uint32_t n, hipStream_t s);
 // upper bound on the partials apply_block_lanczos writes for a block of 2^L amplitudes (tiled:
 // one per tile of 2^10 or more; gather: at most 512 workgroups below the tiled size, and at
 // most one per 256 amplitudes above it)

@@ -193,6 +193,8 @@ static size_t fused_partials(uint64_t n) {
 // workgroups (and partial sums) of a residual pass up to 2^21 amplitudes, at most: every workgroup
 // of the next pass may add them up
 constexpr int kNormParts = 1024;
+// workgroups of a one-launch step at most: two sets of three sums each fit the partials' space
+constexpr int kStepGroups = 256;
 
 size_t krylov_workspace_bytes(uint64_t n, int m, size_t elem_bytes) {
     const size_t vec = basis_stride_bytes(n, elem_bytes);
@@ -221,6 +223,7 @@ KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, cha
     fused_ = reinterpret_cast<double *>(p);
     norms_ = fused_ + fused_partials(n);
     big_ = n > kBigBlock && h_.tiled<T>();
+    one_ = one_launch_steps<T>(h_);
     n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ ? n / 256 : kNormParts));
 }
 
@@ -467,6 +470,47 @@ void KrylovRun<T>::enqueue(int j, const T *u0) {
     // otherwise the next apply sums the norm
 }
 
+// One launch per step: H u_j alternates between slot 0 and slot m, which hold no basis vector while the
+// steps run, and the sums between two halves of the partials' space.
+template <typename T>
+LanczosStep<T> KrylovRun<T>::step_of(int j, const T *u0) {
+    LanczosStep<T> st;
+    T *g[2] = {basis_, vec(m_)};
+    double *sums[2] = {fused_, fused_ + 3 * kStepGroups};
+    st.j = j;
+    st.g = j == 0 ? u0 : g[(j - 1) & 1];
+    st.u1 = j == 0 ? nullptr : j == 1 ? u0 : vec(j - 1);
+    st.u2 = j < 2 ? nullptr : j == 2 ? u0 : vec(j - 2);
+    st.u = j == 0 ? nullptr : vec(j);
+    st.gout = g[j & 1];
+    st.parts = sums[(j - 1) & 1];
+    st.np = n_step_;
+    st.out = sums[j & 1];
+    st.norm2 = beta2_;
+    st.alpha = alpha_;
+    if (j > 0) {
+        st.norm2_host = host_.dev(host_.norm2(j - 1));
+        st.alpha_host = host_.dev(host_.alpha(j - 1));
+    }
+    return st;
+}
+
+template <typename T>
+void KrylovRun<T>::enqueue_one(int j, const T *u0) {
+    pending_ = true;
+    if (timer_) timer_->begin(s_);
+    n_step_ = apply_step<T>(h_, blk_, step_of(j, u0), s_);
+    if (timer_) timer_->end(s_);
+}
+
+// alpha_{j-1} and the norm of u_j, with no step j enqueued
+template <typename T>
+void KrylovRun<T>::close(int j, const T *u0) {
+    LanczosStep<T> st = step_of(j, u0);
+    st.next_host = host_.dev(host_.norm2(j));
+    launch_lanczos_close<T>(st, static_cast<uint32_t>(n_), s_);
+}
+
 // The step after k at which the error estimate is formed: each one for large vectors, where a step
 // in vain costs the most, and ever wider apart below 2^20 amplitudes.
 template <typename T>
@@ -490,7 +534,9 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             fail(SYK_ENOTCONV, "Krylov propagation exceeded max_substeps");
         host_.next();
         pending_ = true;
-        if (!big_) {
+        if (one_) {
+            // step 0 sums the norm
+        } else if (!big_) {
             launch_norm2_partials<T>(cur, n_, norms_, n_norm_, s_);
         } else {
             launch_norm2_partials<T>(cur, n_, partials_, n_part_, s_);
@@ -509,10 +555,17 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             // Steps are enqueued ahead of the check, so that the GPU does not wait for the host:
             // two where a step takes microseconds, one for large blocks, none beyond the check
             // expected to converge (a step enqueued in vain costs its whole time).
-            const int ahead = std::min(check + (big_ ? 1 : 2), std::max(check, converges));
-            while (enq < std::min(ahead, m_)) enqueue(enq++, cur);
-            if (!big_ && enq == check)             // no later step to sum this norm
-                launch_publish_sum(norms_, n_norm_, beta2_ + enq, host_.dev(host_.norm2(enq)), s_);
+            // With one launch per step the norm that the check needs comes with the second step after it.
+            if (one_) {
+                const int ahead = converges <= check || check + 2 > m_ ? check : check + 2;
+                while (enq < ahead) enqueue_one(enq++, cur);
+                if (enq == check) close(check, cur);
+            } else {
+                const int ahead = std::min(check + (big_ ? 1 : 2), std::max(check, converges));
+                while (enq < std::min(ahead, m_)) enqueue(enq++, cur);
+                if (!big_ && enq == check)           // no later step to sum this norm
+                    launch_publish_sum(norms_, n_norm_, beta2_ + enq, host_.dev(host_.norm2(enq)), s_);
+            }
             if (k == 0) {
                 n2[0] = host_.wait(host_.norm2(0), s_);
                 if (!std::isfinite(n2[0])) fail(SYK_ENUMERIC, "non-finite norm in Krylov propagation");

@@ -103,6 +103,9 @@ class KrylovRun {
     T *vec(int j) { return basis_ + static_cast<size_t>(j) * vec_stride_ * 2; }
     // reorth = 0: fused steps, the host a step or two ahead of the last one it has checked
     int next_check(int k) const;
+    LanczosStep<T> step_of(int j, const T *u0);
+    void enqueue_one(int j, const T *u0);
+    void close(int j, const T *u0);
     void run_fused(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st);
     void run_plain(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st);
     // enqueue fused Lanczos step j from u_j (slot 0: u0)
@@ -125,6 +128,8 @@ class KrylovRun {
     T *basis_ = nullptr;
     double *partials_ = nullptr, *alpha_ = nullptr, *beta2_ = nullptr, *coef_ = nullptr, *scratch_ = nullptr;
     double *fused_ = nullptr, *norms_ = nullptr;
+    bool one_ = false;                    // one launch per step
+    int n_step_ = 0;                      // its workgroups
     bool big_ = false;                    // tiled, more than 2^21 amplitudes
     int n_norm_ = 0;                      // partials of ||u||^2
     HostScalars host_;

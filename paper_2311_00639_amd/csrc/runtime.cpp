@@ -234,20 +234,24 @@ const DeviceTables &Hamiltonian::tables(int blk) {
 }
 
 template <typename T>
+static GatherTerms<T> gather_terms(const DeviceTables &t) {
+    GatherTerms<T> g;
+    if constexpr (sizeof(T) == 4)
+        g.rec = t.r32;
+    else
+        g.rec = t.r64;
+    g.K = t.K;
+    for (int i = 0; i < 3; ++i) g.cut[i] = t.cut[i];
+    return g;
+}
+
+template <typename T>
 static int apply_gather(Hamiltonian &h, const int (&blks)[2], int nblk, const T *x, T *y, int nvec, uint64_t ld,
                         hipStream_t s, const LanczosFuse<T> *lf = nullptr) {
     const uint32_t n = 1u << h.L;
     const DeviceTables *tb[2] = {&h.tables(blks[0]), &h.tables(blks[nblk - 1])};
     if (tb[0]->head) return launch_apply_dense<T>(tb, nblk, x, y, n, nvec, ld, s, lf);
-    GatherTerms<T> g[2];
-    for (int b = 0; b < 2; ++b) {
-        if constexpr (sizeof(T) == 4)
-            g[b].rec = tb[b]->r32;
-        else
-            g[b].rec = tb[b]->r64;
-        g[b].K = tb[b]->K;
-        for (int i = 0; i < 3; ++i) g[b].cut[i] = tb[b]->cut[i];
-    }
+    const GatherTerms<T> g[2] = {gather_terms<T>(*tb[0]), gather_terms<T>(*tb[1])};
     return launch_apply_gather<T>(g, nblk, x, y, n, nvec, ld, s, lf);
 }
 
@@ -376,6 +380,25 @@ template int apply_block_lanczos<float>(Hamiltonian &, int, int, const float *, 
                                         const LanczosFuse<float> &, hipStream_t);
 template int apply_block_lanczos<double>(Hamiltonian &, int, int, const double *, double *,
                                          const LanczosFuse<double> &, hipStream_t);
+
+// Step j of one launch reads three vectors per term where two launches read one, and adds up three sums
+// before its first term.  That costs less than a launch (about 4 us from one dependent launch to the
+// next) while the further reads stay below 16 MB.  A propagation of 12 steps at k = 4, two launches / one: N = 16
+// 135 / 111 us, N = 26 153 / 139 us (14 MB), N = 30 165 / 179 us (63 MB) in complex128; N = 20 118 / 96 us, N = 28
+// 120 / 103 us (15 MB) in complex64.
+template <typename T>
+bool one_launch_steps(Hamiltonian &h) {
+    return h.L <= 13 && !h.grouped() && 2.0 * h.K * static_cast<double>(1u << h.L) * 2 * sizeof(T) <= 16e6;
+}
+template bool one_launch_steps<float>(Hamiltonian &);
+template bool one_launch_steps<double>(Hamiltonian &);
+
+template <typename T>
+int apply_step(Hamiltonian &h, int blk, const LanczosStep<T> &st, hipStream_t s) {
+    return launch_lanczos_step<T>(gather_terms<T>(h.tables(blk)), st, 1u << h.L, s);
+}
+template int apply_step<float>(Hamiltonian &, int, const LanczosStep<float> &, hipStream_t);
+template int apply_step<double>(Hamiltonian &, int, const LanczosStep<double> &, hipStream_t);
 
 // Time the compiled variants of the tiled kernel on this Hamiltonian (block U, each in
 // its own planned layout; force: every one, also if the handle is tuned already) and keep the

@@ -109,3 +109,25 @@ def test_threads_and_streams_share_nothing():
         t.join()
     for o, a in zip(outs, alone):
         assert all(torch.equal(v, a) for v in o)
+
+
+@pytest.mark.parametrize("dt", [syk.C128, syk.C64])
+@pytest.mark.parametrize("N,m", [(8, 2), (16, 2), (16, 3), (16, 5), (24, 7), (28, 4)])
+def test_small_krylov_dimensions(N, m, dt):
+    """The dimension ends the steps before the next error check, with one launch per step (N <= 28 here)
+    and its two spare slots: the accepted errors sum to at most tol, and each sub-step rounds its applies and
+    its result (8 units).  With m = 2 the estimate falls only linearly with the sub-step, so that no sub-step
+    meets a tolerance proportional to it: refused on every path."""
+    h = _ham(N, 2 if N == 8 else 4)
+    x = _state(1 << (N // 2 - 1), dt, 7)
+    out, ref = torch.empty_like(x), torch.empty_like(x)
+    if m == 2:
+        for reorth in (0, 2):
+            with pytest.raises(syk.SykError) as e:
+                syk.krylov_expm(h, 0, 0.02j, x, out, m=m, tol=1e-5, reorth=reorth)
+            assert e.value.status == 5
+        return
+    st = syk.krylov_expm(h, 0, 0.02j, x, out, m=m, tol=1e-5)
+    syk.krylov_expm(h, 0, 0.02j, x, ref, m=40, reorth=2)
+    assert st["matvecs"] <= m * st["substeps"]
+    assert float(torch.linalg.vector_norm(out - ref)) <= 1e-5 + st["substeps"] * 8 * (2.0 ** -24 if dt == syk.C64 else 2.0 ** -53)
