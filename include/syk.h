@@ -188,7 +188,8 @@ void syk_krylov_default_opts(syk_dtype dt, syk_krylov_opts *o);
  * estimate ||v|| beta_j |[e^{tau z T_j} e_1]_j|; a step ends early once the estimate
  * meets the tolerance for the remaining tau, else the largest tau that meets it is taken
  * and the propagation restarts from the result.  beta_j ~ 0 is an invariant subspace
- * (exact result).  v, out: device, n_amps = 2^L, 16-byte aligned; out == v allowed.
+ * (exact result).  v, out: device, n_amps = 2^L, 16-byte aligned; out == v allowed, and so is
+ * any overlap (v is then copied before it is overwritten).
  * stats may be NULL.
  * SYK_FULL (n_amps = 2^(L+1)): the two halves are propagated separately (e^{zH} is block
  * diagonal), each to the tolerance relative to its own norm; the statistics are summed

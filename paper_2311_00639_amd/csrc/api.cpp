@@ -393,7 +393,11 @@ syk_status syk_krylov_expm(const syk_ham *h, syk_block blk, syk_dtype dt, double
         const std::complex<double> z(z_re, z_im);
         // one block, or both halves of the full space (U first), each its own Lanczos run
         const int nblk = blk == SYK_FULL ? 2 : 1;
-        for (int q = 0; q < nblk; ++q) {
+        // where out overlaps v in part, the half of out written first must not reach into the
+        // other half of v: U first if out lies below v, D first if above
+        const bool d_first = blk == SYK_FULL && reinterpret_cast<uintptr_t>(out) > reinterpret_cast<uintptr_t>(v);
+        for (int p = 0; p < nblk; ++p) {
+            const int q = d_first ? 1 - p : p;
             const int b = blk == SYK_FULL ? q : blk;
             const uint64_t off = static_cast<uint64_t>(q) * 2 * nb;   // in scalars
             syk_krylov_stats sq{};

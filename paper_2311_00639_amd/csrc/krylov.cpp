@@ -424,11 +424,27 @@ double KrylovRun<T>::bisect(const E &err, double remaining, double tol) {
     return lo;
 }
 
+// whether two vectors share some of their amplitudes, but are not the same vector
+template <typename T>
+static bool overlap_in_part(const T *a, const T *b, uint64_t n) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa != pb && (pa > pb ? pa - pb : pb - pa) < n * 2 * sizeof(T);
+}
+
+// out = v; through slot 0 where they overlap in part, as the copy's threads run in no order
+template <typename T>
+void KrylovRun<T>::copy(const T *v, T *out) {
+    if (out == v) return;
+    const bool via = overlap_in_part(v, out, n_);
+    if (via) launch_scale_copy<T>(v, vec(0), n_, 1.0, s_);
+    launch_scale_copy<T>(via ? vec(0) : v, out, n_, 1.0, s_);
+}
+
 template <typename T>
 void KrylovRun<T>::run(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st) {
     if (z == std::complex<double>(0.0, 0.0)) {
         norm(v);                                   // refuses a non-finite vector
-        if (out != v) launch_scale_copy<T>(v, out, n_, 1.0, s_);
+        copy(v, out);
     } else if (o.reorth == 0) {
         run_fused(z, v, out, o, st);
     } else {
@@ -527,19 +543,36 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
         fail(SYK_EDEVICE, "partials buffer too small");
     double remaining = 1.0;
     const T *cur = v;
+    // Vector 0 of the recombination is `cur` itself, read and written by the same thread where it is
+    // `out`.  Where the two overlap in part a thread would write amplitudes that another has yet to
+    // read: the sub-step then starts from a normalised copy in slot 0, which only one-launch
+    // steps use otherwise.
+    bool staged = overlap_in_part(v, static_cast<const T *>(out), n_);
     std::vector<double> al(m_ + 1), n2(m_ + 2), bo(m_ + 1), coef(2 * (m_ + 1));
     std::vector<std::complex<double>> c(m_ + 1);
     while (remaining > 0.0) {
         if (o.max_substeps > 0 && st.substeps >= o.max_substeps)
             fail(SYK_ENOTCONV, "Krylov propagation exceeded max_substeps");
+        const T *u0 = cur;
+        double unit = 1.0;                       // cur = unit u0
+        if (staged) {
+            unit = norm(cur);
+            if (unit == 0.0) {
+                copy(cur, out);
+                break;
+            }
+            launch_scale_copy<T>(cur, vec(0), n_, 1.0 / unit, s_);
+            u0 = vec(0);
+        }
+        const bool one = one_ && !staged;
         host_.next();
         pending_ = true;
-        if (one_) {
+        if (one) {
             // step 0 sums the norm
         } else if (!big_) {
-            launch_norm2_partials<T>(cur, n_, norms_, n_norm_, s_);
+            launch_norm2_partials<T>(u0, n_, norms_, n_norm_, s_);
         } else {
-            launch_norm2_partials<T>(cur, n_, partials_, n_part_, s_);
+            launch_norm2_partials<T>(u0, n_, partials_, n_part_, s_);
             launch_publish_sum(partials_, n_part_, beta2_, host_.dev(host_.norm2(0)), s_);
         }
         int k = 0, enq = 0;        // steps read back, enqueued
@@ -556,13 +589,13 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             // two where a step takes microseconds, one for large blocks, none beyond the check
             // expected to converge (a step enqueued in vain costs its whole time).
             // With one launch per step the norm that the check needs comes with the second step after it.
-            if (one_) {
+            if (one) {
                 const int ahead = converges <= check || check + 2 > m_ ? check : check + 2;
-                while (enq < ahead) enqueue_one(enq++, cur);
-                if (enq == check) close(check, cur);
+                while (enq < ahead) enqueue_one(enq++, u0);
+                if (enq == check) close(check, u0);
             } else {
                 const int ahead = std::min(check + (big_ ? 1 : 2), std::max(check, converges));
-                while (enq < std::min(ahead, m_)) enqueue(enq++, cur);
+                while (enq < std::min(ahead, m_)) enqueue(enq++, u0);
                 if (!big_ && enq == check)           // no later step to sum this norm
                     launch_publish_sum(norms_, n_norm_, beta2_ + enq, host_.dev(host_.norm2(enq)), s_);
             }
@@ -619,7 +652,7 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             }
         }
         if (nrm == 0.0) {                            // e^{zH} 0 = 0
-            if (out != cur) launch_scale_copy<T>(cur, out, n_, 1.0, s_);
+            copy(cur, out);
             break;
         }
         st.matvecs += k;
@@ -630,20 +663,21 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
         for (int i = 0; i < k; ++i) {
             // slot i holds u_i = n_i v_i
             const double ni = std::sqrt(n2[i]);
-            const double sc = ni > 1e-300 ? nrm / ni : 0.0;
+            const double sc = ni > 1e-300 ? unit * nrm / ni : 0.0;
             coef[2 * i] = sc * c[i].real();
             coef[2 * i + 1] = sc * c[i].imag();
         }
         if (k <= kCombineArgs) {
-            launch_combine_args<T>(cur, basis_, vec_stride_, k, coef.data(), out, n_, s_);
+            launch_combine_args<T>(u0, basis_, vec_stride_, k, coef.data(), out, n_, s_);
         } else {
             SYK_HIP(hipMemcpyAsync(coef_, coef.data(), 2 * k * sizeof(double), hipMemcpyHostToDevice, s_));
-            launch_combine<T>(cur, basis_, vec_stride_, k, coef_, out, n_, s_);
+            launch_combine<T>(u0, basis_, vec_stride_, k, coef_, out, n_, s_);
         }
         st.substeps += 1;
         remaining -= tau;
         if (remaining <= 1e-15) break;
         cur = out;
+        staged = false;
     }
     if (timer_) {
         SYK_HIP(hipStreamSynchronize(s_));
@@ -655,7 +689,7 @@ template <typename T>
 void KrylovRun<T>::run_plain(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st) {
     double nrm = norm(v);
     if (nrm == 0.0) {
-        if (out != v) launch_scale_copy<T>(v, out, n_, 1.0, s_);
+        copy(v, out);
         return;
     }
     double remaining = 1.0;

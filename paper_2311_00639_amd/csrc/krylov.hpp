@@ -91,7 +91,7 @@ class KrylovRun {
     // rot: layout rotation of the vectors (0 = standard index order)
     KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, char *ws, hipStream_t s);
     ~KrylovRun();                               // waits for the stream where work may be left on it
-    // out = e^{z H} v (out may equal v); accumulates into st.  The result is enqueued, not waited for.
+    // out = e^{z H} v (out may be v, or overlap it); accumulates into st.  The result is enqueued, not waited for.
     void run(std::complex<double> z, const T *v, T *out, const syk_krylov_opts &o, syk_krylov_stats &st);
     double norm(const T *v);
     void set_timer(ApplyTimer *t) { timer_ = t; }
@@ -101,6 +101,7 @@ class KrylovRun {
 
   private:
     T *vec(int j) { return basis_ + static_cast<size_t>(j) * vec_stride_ * 2; }
+    void copy(const T *v, T *out);
     // reorth = 0: fused steps, the host a step or two ahead of the last one it has checked
     int next_check(int k) const;
     LanczosStep<T> step_of(int j, const T *u0);

@@ -1,0 +1,48 @@
+"""Vectors that krylov_expm is given: in and out that overlap in part.
+
+Bounds: the Krylov bounds of the parity tests, 1e-10 in complex128 and 1e-5 in complex64.
+"""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_2311_00639_amd as syk  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _cd(dt):
+    return torch.complex64 if dt == syk.C64 else torch.complex128
+
+
+def _state(n, dt, seed):
+    x = torch.randn(n, dtype=_cd(dt), device="cuda", generator=torch.Generator(device="cuda").manual_seed(seed))
+    return x / torch.linalg.vector_norm(x)
+
+
+def _tol(dt):
+    return 1e-10 if dt == syk.C128 else 1e-5
+
+
+@pytest.mark.parametrize("dt", [syk.C128, syk.C64])
+@pytest.mark.parametrize("shift", [2, -2, 514, -514])
+@pytest.mark.parametrize("N,blk", [(16, 0), (16, syk.FULL), (30, 1), (30, syk.FULL), (40, 0), (46, 1)])
+def test_in_and_out_overlap_in_part(N, blk, shift, dt):
+    """One launch a step (N = 16), two (N = 30), the tiled kernel with the norm summed in the next apply
+    (N = 40) and by launches of its own (N = 46): the propagated vector is that of a separate `out`, also over
+    several sub-steps, with reorthogonalisation, and at z = 0 (where `out` is v, bit for bit)."""
+    h = syk.create_hamiltonian(N, 4, 2, 3)
+    n = (2 if blk == syk.FULL else 1) << (N // 2 - 1)
+    a, b = max(0, -shift), max(0, shift)
+    x, ref = _state(n, dt, N), torch.empty(n, dtype=_cd(dt), device="cuda")
+    modes = [dict(), dict(m=8)] + ([dict(reorth=2)] if N == 16 else [])
+    for z, opts in [(-0.2 + 0.5j, o) for o in modes] + [(0.0, dict())]:
+        syk.krylov_expm(h, blk, z, x, ref, **opts)
+        buf = torch.full((n + abs(shift),), 7.0, dtype=_cd(dt), device="cuda")
+        buf[a:a + n] = x
+        syk.krylov_expm(h, blk, z, buf[a:a + n], buf[b:b + n], **opts)
+        got = buf[b:b + n]
+        if z == 0.0:
+            assert torch.equal(got, x)
+        else:
+            assert float(torch.linalg.vector_norm(got - ref)) <= _tol(dt)
