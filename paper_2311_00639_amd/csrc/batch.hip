@@ -84,7 +84,10 @@ struct Shared {
     double red[4][NT / 64];
     double al[kMaxKrylov + 2];
     double bt[kMaxKrylov + 2];
-    float sc[kMaxKrylov + 2];          // basis vector i is stored as beta_{i-1} v_i: v_i = sc[i] * stored
+    // v_i = sc[i] * stored: basis vector i >= 1 is stored as beta_{i-1} v_i and sc[i] is a float; vector 0 is
+    // the caller's, scaled in 64 bits and rounded once per element, as a rounded scale would
+    // enter the whole result
+    double sc[kMaxKrylov + 2];
     double cre[kMaxKrylov + 2], cim[kMaxKrylov + 2];
     double fre[kCheb], fim[kCheb];
     double cosb[4 * kCheb];            // cos(pi j / (2 kCheb)), j < 4 kCheb
@@ -200,7 +203,7 @@ __device__ __forceinline__ void static_for(F &&f) {
     }
 }
 
-// y = H_blk v (v: global, standard layout, scaled by vs as it is staged); returns this thread's
+// y = H_blk v (v: global, standard layout, scaled by vs + vlo as it is staged); returns this thread's
 // share of Re <v, y>.  The block is cut into NCH chunks of CH amplitudes; output chunk o is
 // accumulated in registers (RC per thread) while every chunk ch of v is staged in LDS in turn, and the
 // terms whose partner offset x >> log2(CH) equals o ^ ch are applied from it, run by run.  Up to two
@@ -213,8 +216,8 @@ __device__ __forceinline__ void static_for(F &&f) {
 // 85 us on every CU at once, is Lanczos vectors from memory: 127 us when y went through memory and
 // v_j was read again for the products.
 template <int NT, int CHB, int L, int RC>
-__device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v, gf2 *y, float vs, float2 (&y0)[RC],
-                                          float2 (&acc)[RC]) {
+__device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v, gf2 *y, float vs, float vlo,
+                                          float2 (&y0)[RC], float2 (&acc)[RC]) {
     constexpr int n = 1 << L;
     constexpr int LCH = L < CHB ? L : CHB;
     constexpr int CH = 1 << LCH;
@@ -233,6 +236,9 @@ __device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v
         uint32_t w = i * 64u + lane;
         w = w < last ? w : last;
         return staged ? lterms[w] : terms[w];
+    };
+    auto scaled = [&](float2 q) __attribute__((always_inline)) {
+        return float2{fmaf(vs, q.x, vlo * q.x), fmaf(vs, q.y, vlo * q.y)};
     };
     const uint32_t tb8 = tid * 8u;
     uint32_t signbit = 0x80000000u;
@@ -256,7 +262,7 @@ __device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v
 #pragma unroll
                 for (int r = 0; r < RC; ++r) q[r] = ld(v + (ch * CH + r * NT + tid));
 #pragma unroll
-                for (int r = 0; r < RC; ++r) st(c.buf + (r * NT + tid), float2{vs * q[r].x, vs * q[r].y});
+                for (int r = 0; r < RC; ++r) st(c.buf + (r * NT + tid), scaled(q[r]));
                 __syncthreads();
                 in_lds = ch;
             }
@@ -282,8 +288,7 @@ __device__ __forceinline__ double apply_h(Ctx<NT, CHB> &c, int blk, const gf2 *v
             if (NCH <= 2) {
                 q = ld(c.buf + (r * NT + tid));           // written by this thread
             } else {
-                const float2 u = ld(v + i);
-                q = float2{vs * u.x, vs * u.y};
+                q = scaled(ld(v + i));
                 st(y + i, acc[r]);
             }
             dre += static_cast<double>(q.x) * acc[r].x + static_cast<double>(q.y) * acc[r].y;
@@ -386,11 +391,11 @@ __device__ __forceinline__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j, co
     gf2 *vn = c.basis + static_cast<size_t>(j + 1) * c.p.vec_stride;
     // basis slots hold v_i / sc[i]; the next slot is left unnormalised (its scale 1/beta_j
     // enters wherever it is read), which saves a normalising pass per step
-    const float sj = c.sh.sc[j];
-    const float sp = j > 0 ? c.sh.sc[j - 1] : 0.0f;
-    const float fb = static_cast<float>(c.sh.bt[j]) * sp;   // 0 for j = 0
+    const double sj = c.sh.sc[j];
+    const float shi = static_cast<float>(sj), slo = static_cast<float>(sj - shi);   // slo = 0 for j > 0
+    const float fb = j > 0 ? static_cast<float>(c.sh.bt[j] * c.sh.sc[j - 1]) : 0.0f;
     float2 y0[RC], acc[RC];
-    const double dre = apply_h<NT, CHB, L, RC>(c, blk, vj, vn, sj, y0, acc);
+    const double dre = apply_h<NT, CHB, L, RC>(c, blk, vj, vn, shi, slo, y0, acc);
     double w2 = 0.0, alpha;
     if constexpr (NCH <= 2) {
         // w = y - alpha v_j - beta_{j-1} v_{j-1} from registers; the last chunk of v_j is still staged
@@ -399,7 +404,7 @@ __device__ __forceinline__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j, co
         for (int r = 0; r < RC; ++r)
             p[r] = j > 0 ? ld(vp + ((NCH - 1) * RC + r) * NT + c.tid) : float2{0.0f, 0.0f};
         alpha = bsum1<NT>(dre, c.sh, c.tid);
-        const float al = static_cast<float>(alpha), fa = al * sj;
+        const float al = static_cast<float>(alpha), fa = static_cast<float>(alpha * sj);
 #pragma unroll
         for (int r = 0; r < RC; ++r) {
             const int i = ((NCH - 1) * RC + r) * NT + static_cast<int>(c.tid);
@@ -428,7 +433,7 @@ __device__ __forceinline__ void lanczos_step(Ctx<NT, CHB> &c, int blk, int j, co
         }
     } else {
         alpha = bsum1<NT>(dre, c.sh, c.tid);
-        const float fa = static_cast<float>(alpha) * sj;
+        const float fa = static_cast<float>(alpha * sj);
 #pragma unroll 4
         for (int r = 0; r < R; ++r) {
             const int i = r * NT + static_cast<int>(c.tid);
@@ -617,7 +622,7 @@ __device__ __attribute__((noinline)) double prop(Ctx<NT, CHB> &c, int blk, doubl
         }
         if (c.tid == 0) {
             c.sh.bt[0] = 0.0;
-            c.sh.sc[0] = static_cast<float>(1.0 / nrm);
+            c.sh.sc[0] = 1.0 / nrm;
         }
         __syncthreads();
         int k = 0, done = 0;
