@@ -7,6 +7,7 @@
 
 #include <type_traits>
 
+#include "device.hpp"
 #include "internal.hpp"
 
 namespace syk {
@@ -46,7 +47,8 @@ struct Epilogue {
     const LanczosFuse<T> &lf;
     double *sh;                               // S + 4 doubles of LDS: norm shares, then row shares
     double norm = 0.0;
-    T sc = 0, bp = 0;
+    Scale<T> sc;
+    T bp = 0;
     __device__ __forceinline__ void load() {
         if (threadIdx.x < 256)
             for (int p = threadIdx.x; p < lf.n_parts; p += 256) norm += lf.norm_parts[p];
@@ -67,19 +69,19 @@ struct Epilogue {
         }
         const double nj = sqrt(n2);
         const double njm = lf.j >= 1 ? sqrt(lf.norm2[lf.j - 1]) : 0.0;
-        sc = nj > 1e-300 ? static_cast<T>(1.0 / nj) : T(0);
+        sc = Scale<T>(nj > 1e-300 ? 1.0 / nj : 0.0);
         bp = njm > 1e-300 ? static_cast<T>(nj / njm) : T(0);
     }
     // w = H v_j - beta_{j-1} v_{j-1} of amplitude m from s = (H u_j)[m]; adds to Re <v_j, w>
     __device__ __forceinline__ V row(V s, uint32_t m, double &sum) {
-        V w{sc * s.x, sc * s.y};
+        V w{sc(s.x), sc(s.y)};
         if (lf.vprev) {
             const V p = reinterpret_cast<const V *>(lf.vprev)[m];
             w.x -= bp * p.x;
             w.y -= bp * p.y;
         }
         const V u = reinterpret_cast<const V *>(lf.vcur)[m];
-        const V c{sc * u.x, sc * u.y};
+        const V c{sc(u.x), sc(u.y)};
         sum += static_cast<double>(c.x) * w.x + static_cast<double>(c.y) * w.y;
         return w;
     }
@@ -266,7 +268,8 @@ int go(const GatherTerms<T> (&tb)[2], int nblk, const T *x, T *y, uint32_t n, in
 // alpha_{j-1} = Re <v_{j-1}, w>.  Every wave adds up the sums of the step before in the same order.
 template <typename T>
 struct StepScales {
-    T a, b, c;
+    Scale<T> a;
+    T b, c;
     __device__ __forceinline__ StepScales(const LanczosStep<T> &st, uint32_t lane, bool publish) {
         double s0 = 0.0, s1 = 0.0, s2 = 0.0;
         for (int p = lane; p < st.np; p += 64) {
@@ -282,7 +285,7 @@ struct StepScales {
         }
         const double n1 = sqrt(s0), inv = n1 > 1e-300 ? 1.0 / n1 : 0.0, inv2 = n2 > 1e-300 ? 1.0 / n2 : 0.0;
         const double al = (s0 > 1e-300 ? s1 / s0 : 0.0) - s2 * inv2;
-        a = static_cast<T>(inv);
+        a = Scale<T>(inv);
         b = static_cast<T>(n1 * inv2);
         c = static_cast<T>(al * inv);
         if (publish) {
@@ -293,7 +296,7 @@ struct StepScales {
         }
     }
     __device__ __forceinline__ T operator()(T g, T u2, T u1) const {
-        const T w = a * g - b * u2;
+        const T w = a(g) - b * u2;
         return w - c * u1;
     }
 };
@@ -329,7 +332,8 @@ __global__ void __launch_bounds__(64 * S) lanczos_step(GatherTerms<T> tb, Lanczo
     Q ug = load_quad<T>(rg, own, 0), u1{}, u2{};
     if constexpr (!FIRST) u1 = load_quad<T>(r1, own, 0);
     if (two) u2 = load_quad<T>(r2, own, 0);
-    T ca = T(1), cb = T(0), cc = T(0);
+    Scale<T> ca;
+    T cb = T(0), cc = T(0);
     if constexpr (!FIRST) {
         const StepScales<T> sc(st, lane, threadIdx.x == 0 && blockIdx.x == 0);
         ca = sc.a, cb = sc.b, cc = sc.c;
@@ -338,7 +342,7 @@ __global__ void __launch_bounds__(64 * S) lanczos_step(GatherTerms<T> tb, Lanczo
         if constexpr (!FIRST) {
 #pragma unroll
             for (int i = 0; i < 2 * A; ++i) {
-                const T w = ca * g[i] - cb * p2[i];
+                const T w = ca(g[i]) - cb * p2[i];
                 g[i] = w - cc * p1[i];
             }
         }

@@ -25,6 +25,7 @@
 
 #include <type_traits>
 
+#include "device.hpp"
 #include "internal.hpp"
 #include "apply_plan.hpp"
 
@@ -517,11 +518,16 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
     }
     const double nj = sqrt(n2);
     const double njm = lf.j >= 1 ? sqrt(lf.norm2[lf.j - 1]) : 0.0;
-    const T sc = nj > 1e-300 ? static_cast<T>(1.0 / nj) : T(0);
+    const Scale<T> sc(nj > 1e-300 ? 1.0 / nj : 0.0);
     const T bp = (lf.vprev && njm > 1e-300) ? static_cast<T>(nj / njm) : T(0);
     double sum = 0.0;
     auto epi_tile = [&](auto has_prev, auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
+        // the caller's vector (j = 0) is scaled in 64 bits; the later ones by a T, which their
+        // coefficients in the recombination undo (both for all j: N = 50, complex64 14.6 -> 15.3 ms)
+        auto scaled = [&](T v) __attribute__((always_inline)) {
+            return decltype(has_prev)::value ? sc.hi * v : sc(v);
+        };
         {
             const uint64_t base = static_cast<uint64_t>(t0 ^ hs.h[i]) << BT;
             V *dst = yv + base;
@@ -530,13 +536,13 @@ __global__ void __launch_bounds__(1 << (BT - RB), OCC * (1 << (BT - RB)) / 256) 
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int m = r * NT + tid;
-                V w = V{sc * acc[i][r].x, sc * acc[i][r].y};
+                V w = V{scaled(acc[i][r].x), scaled(acc[i][r].y)};
                 if constexpr (decltype(has_prev)::value) {
                     const V p = vp[m];
                     w.x -= bp * p.x;
                     w.y -= bp * p.y;
                 }
-                const V c = V{sc * vc[m].x, sc * vc[m].y};
+                const V c = V{scaled(vc[m].x), scaled(vc[m].y)};
                 dst[m] = w;
                 sum += static_cast<double>(c.x) * w.x + static_cast<double>(c.y) * w.y;
                 // bound the loads in flight: with several workgroups per CU the register

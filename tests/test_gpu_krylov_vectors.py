@@ -1,4 +1,4 @@
-"""Vectors that krylov_expm is given: in and out that overlap in part.
+"""Vectors that krylov_expm is given: in and out that overlap in part, and norms whose inverse rounds badly.
 
 Bounds: the Krylov bounds of the parity tests, 1e-10 in complex128 and 1e-5 in complex64.
 """
@@ -46,3 +46,26 @@ def test_in_and_out_overlap_in_part(N, blk, shift, dt):
             assert torch.equal(got, x)
         else:
             assert float(torch.linalg.vector_norm(got - ref)) <= _tol(dt)
+
+
+@pytest.mark.parametrize("N,k", [(26, 4), (28, 4), (30, 4), (32, "dense"), (36, 4), (42, 2), (46, 2)])
+def test_start_vector_scale_is_not_rounded_to_32_bits(N, k):
+    """complex64: the factor 1 / ||v|| that turns H v into the first Lanczos step is 0.87 u (u = 2^-24) off
+    if it is rounded to 32 bits, at the norm chosen here, and the first-order term z H v of the
+    result with it.  Otherwise the part of the error along H v is at most 0.4 u of z H v: the rounding
+    of the result (0.3 u / (|z| E sqrt(2 n)) per standard deviation, E = ||H v|| >= 0.5 ||v||: 0.05 u at
+    n = 2^12, of which six) and the later coefficients, each within u at second order in |z| E <= 0.1.
+    One launch a step up to N = 28, two from there, dense blocks, the tiled kernel from N = 42."""
+    dense = k == "dense"
+    h = syk.create_hamiltonian(N, 4, (N - 1) * (N - 2) * (N - 3) / 24.0 if dense else k, 3,
+                               syk.BERNOULLI if dense else syk.EXACT_K)
+    n, z, u = 1 << (N // 2 - 1), 0.1j, 2.0 ** -24
+    inv = 1.0 + 311171 * 2.0 ** -23 + 0.45 * 2.0 ** -23       # between two floats
+    x = (_state(n, syk.C128, N) / inv).to(torch.complex64)
+    xd = x.to(torch.complex128)
+    hx, out, ref = torch.empty_like(xd), torch.empty_like(x), torch.empty_like(xd)
+    syk.apply_H(h, 0, xd, hx)
+    syk.krylov_expm(h, 0, z, x, out, tol=1e-9)
+    syk.krylov_expm(h, 0, z, xd, ref)
+    along = torch.vdot(hx, out.to(torch.complex128) - ref) / (z * torch.vdot(hx, hx))
+    assert abs(float(along.real)) <= 0.4 * u
