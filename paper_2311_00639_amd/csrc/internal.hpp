@@ -202,6 +202,7 @@ uint64_t splitmix_mix(uint64_t z);
 struct Hamiltonian {
     int N = 0, L = 0, K = 0;
     double k = 0, p = 0, sigma = 0, sum_J2 = 0;
+    double c_max = 0;                  // largest |c| of the block terms
     uint64_t seed = 0;
     int ensemble = 0;                  // -1: a general operator (syk_op_to_hamiltonian)
     bool hermitian = true;

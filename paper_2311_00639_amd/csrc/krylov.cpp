@@ -205,6 +205,16 @@ size_t krylov_workspace_bytes(uint64_t n, int m, size_t elem_bytes) {
     return static_cast<size_t>(m + 1) * up(vec) + up(part) + up(scal) + up(fused);
 }
 
+// The fused steps read v and the later basis vectors unnormalised, so that H u_j is formed at about c_max
+// times the norm of u_j, which is ||v|| for j = 0 and of the order of c_max else (sums over u_j and H u_j
+// at its third power).  Within these bounds on ||v|| and c_max nothing of that leaves the range
+// of T, nor the sums that of a double.
+template <typename T>
+static bool fused_range(double s) {
+    const int e = sizeof(T) == 4 ? 40 : 300;
+    return s >= std::ldexp(1.0, -e) && s <= std::ldexp(1.0, e);
+}
+
 template <typename T>
 KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, char *ws, hipStream_t s)
     : h_(h), blk_(blk), rot_(rot), n_(n), m_(m), s_(s) {
@@ -223,6 +233,7 @@ KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, cha
     fused_ = reinterpret_cast<double *>(p);
     norms_ = fused_ + fused_partials(n);
     big_ = n > kBigBlock && h_.tiled<T>();
+    plain_ = !h_.tiled<T>() && !fused_range<T>(h_.c_max);
     one_ = one_launch_steps<T>(h_);
     n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ ? n / 256 : kNormParts));
 }
@@ -445,7 +456,7 @@ void KrylovRun<T>::run(std::complex<double> z, const T *v, T *out, const syk_kry
     if (z == std::complex<double>(0.0, 0.0)) {
         norm(v);                                   // refuses a non-finite vector
         copy(v, out);
-    } else if (o.reorth == 0) {
+    } else if (o.reorth == 0 && !plain_) {
         run_fused(z, v, out, o, st);
     } else {
         run_plain(z, v, out, o, st);
@@ -546,7 +557,7 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
     // Vector 0 of the recombination is `cur` itself, read and written by the same thread where it is
     // `out`.  Where the two overlap in part a thread would write amplitudes that another has yet to
     // read: the sub-step then starts from a normalised copy in slot 0, which only one-launch
-    // steps use otherwise.
+    // steps use otherwise.  So does one from a vector outside the range of the fused steps.
     bool staged = overlap_in_part(v, static_cast<const T *>(out), n_);
     std::vector<double> al(m_ + 1), n2(m_ + 2), bo(m_ + 1), coef(2 * (m_ + 1));
     std::vector<std::complex<double>> c(m_ + 1);
@@ -576,6 +587,7 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
             launch_publish_sum(partials_, n_part_, beta2_, host_.dev(host_.norm2(0)), s_);
         }
         int k = 0, enq = 0;        // steps read back, enqueued
+        bool again = false;
         double tau = 0.0, nrm = 0.0;
         int check = next_check(0);               // the error estimate is formed at these steps
         // log error estimates of the last three checks, newest first, and the steps between them:
@@ -603,6 +615,8 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
                 n2[0] = host_.wait(host_.norm2(0), s_);
                 if (!std::isfinite(n2[0])) fail(SYK_ENUMERIC, "non-finite norm in Krylov propagation");
                 nrm = std::sqrt(n2[0]);
+                again = !staged && nrm > 0.0 && !fused_range<T>(nrm);
+                if (again) break;
             }
             const int step = check - k;
             for (; k < check; ++k) {
@@ -650,6 +664,10 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
                     for (converges = check; converges < at && converges < m_;) converges = next_check(converges);
                 }
             }
+        }
+        if (again) {
+            staged = true;
+            continue;
         }
         if (nrm == 0.0) {                            // e^{zH} 0 = 0
             copy(cur, out);

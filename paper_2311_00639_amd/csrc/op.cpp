@@ -82,6 +82,7 @@ void build_operator_hamiltonian(Hamiltonian &h, const Operator &op) {
     h.ensemble = -1;
     h.hermitian = op_is_hermitian(op, 1e-13);
     h.sum_J2 = 0.0;
+    h.c_max = 0.0;
     h.ijkl.clear();
     h.J.clear();
     h.xmask.clear();
@@ -95,6 +96,7 @@ void build_operator_hamiltonian(Hamiltonian &h, const Operator &op) {
         for (int q = 0; q < 4; ++q) h.ijkl.push_back(-1);
         h.J.push_back(J);
         h.sum_J2 += J * J;
+        h.c_max = std::max(h.c_max, std::fabs(J));
         h.xmask.push_back(x);
         h.zmask.push_back(z);
         h.phase[0].push_back(static_cast<int8_t>(p));

@@ -171,6 +171,7 @@ void build_hamiltonian(Hamiltonian &h, int N, double k, uint64_t seed, int ensem
     h.phase[0].clear();
     h.phase[1].clear();
     h.sum_J2 = 0.0;
+    h.c_max = 0.0;
     for (const auto &t : chosen) {
         h.ijkl.push_back(std::get<0>(t));
         h.ijkl.push_back(std::get<1>(t));
@@ -184,6 +185,7 @@ void build_hamiltonian(Hamiltonian &h, int N, double k, uint64_t seed, int ensem
         const double Ja = h.sigma * r * std::cos(two_pi * u2);
         h.J.push_back(Ja);
         h.sum_J2 += Ja * Ja;
+        h.c_max = std::max(h.c_max, 0.25 * std::fabs(Ja));
     }
 
     // block forms of gamma_i gamma_j gamma_k gamma_l

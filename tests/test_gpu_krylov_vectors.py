@@ -1,7 +1,9 @@
-"""Vectors that krylov_expm is given: in and out that overlap in part, and norms whose inverse rounds badly.
+"""Vectors that krylov_expm is given: in and out that overlap in part, norms whose inverse rounds badly,
+and vectors and operators near the ends of the type's range.
 
 Bounds: the Krylov bounds of the parity tests, 1e-10 in complex128 and 1e-5 in complex64.
 """
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -69,3 +71,54 @@ def test_start_vector_scale_is_not_rounded_to_32_bits(N, k):
     syk.krylov_expm(h, 0, z, xd, ref)
     along = torch.vdot(hx, out.to(torch.complex128) - ref) / (z * torch.vdot(hx, hx))
     assert abs(float(along.real)) <= 0.4 * u
+
+
+def _scaled(n, dt, exp, seed):
+    """Integers below 100 times a power of two, ||x|| of the order of 2^exp: scaling by a power of two is exact."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    re, im = (torch.randint(-99, 100, (n,), device="cuda", generator=g).to(torch.float64) for _ in range(2))
+    s = 2.0 ** (exp - 6 - n.bit_length() // 2)
+    return torch.complex(re * s, im * s).to(_cd(dt))
+
+
+@pytest.mark.parametrize("dt", [syk.C128, syk.C64])
+@pytest.mark.parametrize("N,k", [(16, 4), (30, 4), (32, "dense"), (42, 2)])
+def test_vectors_near_the_ends_of_the_range(N, k, dt):
+    """A vector scaled by a power of two gives the scaled result: between two scales outside the range of
+    the fused steps up to the smallest denormal, against the unscaled vector within the Krylov bound."""
+    dense = k == "dense"
+    h = syk.create_hamiltonian(N, 4, (N - 1) * (N - 2) * (N - 3) / 24.0 if dense else k, 3,
+                               syk.BERNOULLI if dense else syk.EXACT_K)
+    n, z = 1 << (N // 2 - 1), -0.4 + 0.9j
+    outs = {}
+    pairs = ((-112, -80), (110, 80)) if dt == syk.C64 else ((-480, -400), (480, 400))
+    for e in (0,) + pairs[0] + pairs[1]:
+        x = _scaled(n, dt, e, N)
+        out = torch.empty_like(x)
+        syk.krylov_expm(h, 1, z, x, out)
+        outs[e] = out.to(torch.complex128) * 2.0 ** -e
+        assert float(torch.linalg.vector_norm(outs[e] - outs[0])) <= _tol(dt) * float(torch.linalg.vector_norm(outs[0]))
+    for a, b in pairs:
+        assert float((outs[a] - outs[b]).abs().max()) <= 2 * (2.0 ** (-149 - min(a, b)) if dt == syk.C64 else 0.0)
+
+
+@pytest.mark.parametrize("dt", [syk.C128, syk.C64])
+@pytest.mark.parametrize("L", [7, 14, 17])
+def test_operators_near_the_ends_of_the_range(L, dt):
+    """e^{zH} depends on z H: an operator scaled by a power of two, with z and the tolerance (which is on
+    beta_k times the last component) scaled against it."""
+    rng = np.random.default_rng(L)
+    x, p = rng.integers(0, 1 << L, 30).astype(np.uint64), rng.integers(0, 1 << L, 30).astype(np.uint64)
+    odd = np.array([bin(int(a & b)).count("1") & 1 for a, b in zip(x, p)])
+    c = rng.standard_normal(30) / 6.0 * np.where(odd, 1j, 1.0)                 # Hermitian strings
+    v = _state(1 << L, dt, L)
+    tol = 1e-12 if dt == syk.C128 else 1e-7
+    outs = {}
+    pairs = ((-70, -50), (60, 50)) if dt == syk.C64 else ((-400, -320), (400, 320))
+    for e in (0,) + pairs[0] + pairs[1]:
+        h = syk.Operator(L, x, p, c * 2.0 ** e).to_hamiltonian()
+        outs[e] = torch.empty_like(v)
+        syk.krylov_expm(h, 0, (-0.4 + 0.9j) * 2.0 ** -e, v, outs[e], tol=tol * 2.0 ** e)
+        assert float(torch.linalg.vector_norm(outs[e] - outs[0])) <= _tol(dt) * float(torch.linalg.vector_norm(outs[0]))
+    for a, b in pairs:
+        assert torch.equal(outs[a], outs[b])
