@@ -263,7 +263,11 @@ HostScalars::HostScalars() {
             pin_pool()->pop_back();
         }
     }
-    if (!p_) SYK_HIP(hipHostMalloc(reinterpret_cast<void **>(&p_), 2 * kSlots * sizeof(double), hipHostMallocPortable));
+    // coherent: a running kernel's store has to reach a polling host (any other flag alone leaves that
+    // to the environment, HIP_HOST_COHERENT)
+    if (!p_)
+        SYK_HIP(hipHostMalloc(reinterpret_cast<void **>(&p_), 2 * kSlots * sizeof(double),
+                              hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
     void *d = nullptr;
     const hipError_t e = hipHostGetDevicePointer(&d, p_, 0);
     if (e != hipSuccess) {

@@ -59,7 +59,8 @@ class ApplyTimer {
 };
 
 // Scalars that kernels store to pinned host memory and the host polls for, so that it can follow a
-// Lanczos run without waiting for the stream.  Blocks come from a pool shared by all threads (one
+// Lanczos run without waiting for the stream: coherent memory, written with system-scope atomic
+// stores, one 8-byte value per slot, so that no order between slots is needed.  Blocks come from a pool shared by all threads (one
 // per run in progress), which syk_release_workspace empties.
 class HostScalars {
   public:
