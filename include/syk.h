@@ -517,10 +517,8 @@ syk_status syk_tridiag_expm(int n, const double *alpha, const double *beta, doub
                             double *c_re, double *c_im);
 
 /* Launch plan of the tiled apply_H kernel for one block (host-only; no GPU needed).
- * Blocks of 2^L amplitudes with L >= 18 have one.  It serves them except where the gather kernels
- * are faster and no tiled variant is pinned by syk_select_variant: blocks of at most 4 MiB (L = 18,
- * and L = 19 in complex64), and dense ones (four or more terms per distinct x mask) with L <= 22.
- * The plan: output tiles of
+ * Blocks of 2^L amplitudes with L >= 18 have one, whichever kernel serves them (syk_apply_kernel
+ * tells).  The plan: output tiles of
  * 2^tile_bits amplitudes, terms grouped by partner tile (n_groups groups), tiles mapped
  * to workgroups so that the 2^res_bits tiles resident on one XCD form a coset of a
  * res_bits-dim subspace (classes_xcd = partner-tile classes modulo it, which sets the L2
@@ -531,7 +529,8 @@ syk_status syk_tridiag_expm(int n, const double *alpha, const double *beta, doub
  * for the planner's choice (the layout syk_otoc uses by default), layout >= 0 for that
  * rotation. */
 typedef struct {
-    int tiled;             /* 0: the block is below the tiled size (L < 18); then n_groups is the
+    int tiled;             /* 1: the block has a plan of the tiled kernel (described here whether or not that
+                              kernel serves the block by default); 0: it is below the tiled size (L < 18); then n_groups is the
                               number of distinct x masks (about K / 19 for dense SYK, about K
                               for sparse) */
     int variant;           /* compiled kernel variant in use (default or tuned) */
@@ -541,6 +540,15 @@ typedef struct {
     uint64_t n_tiles;
 } syk_plan_desc;
 syk_status syk_plan_describe(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, syk_plan_desc *out);
+
+/* Kernel that syk_apply_H, and what is built on it in the standard layout, uses for a block of `h` in
+ * precision dt on the current device (device 0 without one; host-only).  Blocks of 2^L amplitudes are
+ * served by the tiled kernel from L = 18 up, except where a gather kernel is faster and no
+ * variant is pinned by syk_select_variant: blocks of at most 4 MiB (L = 18, and L = 19 in
+ * complex64), and dense ones (four or more terms per distinct x mask) with 6 <= L <= 22, which
+ * the grouped gather kernel serves.  Errors: EINVAL. */
+typedef enum { SYK_KERNEL_GATHER = 0, SYK_KERNEL_GROUPED = 1, SYK_KERNEL_TILED = 2 } syk_kernel;
+syk_status syk_apply_kernel(const syk_ham *h, syk_dtype dt, int *kernel);
 
 /* Control blocks of that plan (host-only; for inspection and tests), when the variant in use
  * has record form 2: one 64-word block per partner step plus one for the last prefetch.  In
@@ -559,8 +567,8 @@ syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int la
 
 /* Schedule autotuner: time each compiled variant of the tiled apply_H kernel (tile size,
  * LDS buffering, prefetch depth; each in its planned layout) on this Hamiltonian and keep
- * the fastest for the current device and precision (a dense block that the gather kernel
- * serves stays with it; see syk_plan_describe).  *variant receives the choice (-1 if
+ * the fastest for the current device and precision (a block that a gather kernel
+ * serves stays with it; see syk_apply_kernel).  *variant receives the choice (-1 if
  * L < 18); ms[v] (host, cap entries, may be NULL) the mean time of one
  * apply with variant v (-1 where skipped).  Uses a library-owned workspace of two vectors.
  * Errors: EINVAL, ENOMEM, EDEVICE. */

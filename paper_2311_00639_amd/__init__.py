@@ -20,6 +20,9 @@ from ._lib import (  # noqa: F401
     EAGAIN,
     FIT_GLOBAL,
     FIT_SLOPE,
+    KERNEL_GATHER,
+    KERNEL_GROUPED,
+    KERNEL_TILED,
     Engine,
     BLOCK_U,
     BLOCK_D,
@@ -29,6 +32,7 @@ from ._lib import (  # noqa: F401
     Operator,
     KrylovOpts,
     apply_H,
+    apply_kernel,
     apply_majorana,
     autotune,
     create_hamiltonian,

@@ -126,6 +126,7 @@ class FitResult(ct.Structure):
 
 
 FIT_SLOPE, FIT_GLOBAL = 0, 1
+KERNEL_GATHER, KERNEL_GROUPED, KERNEL_TILED = 0, 1, 2
 
 _vp, _u64, _i, _d = ct.c_void_p, ct.c_uint64, ct.c_int, ct.c_double
 _dp = ct.POINTER(ct.c_double)
@@ -145,6 +146,7 @@ _SIGS = {
     "syk_tridiag_expm": [_i, _dp, _dp, _d, _d, _dp, _dp],
     "syk_release_workspace": [],
     "syk_plan_describe": [_vp, _i, _i, _i, ct.POINTER(PlanDesc)],
+    "syk_apply_kernel": [_vp, _i, ct.POINTER(_i)],
     "syk_plan_blocks": [_vp, _i, _i, _i, ct.c_void_p, ct.c_size_t, ct.POINTER(ct.c_size_t)],
     "syk_autotune": [_vp, _i, ct.POINTER(_i), ct.POINTER(ct.c_float), _i, _vp],
     "syk_select_variant": [_vp, _i, _i],
@@ -549,6 +551,13 @@ def plan_describe(ham: Hamiltonian, block: int, dtype: int, layout: int = -1) ->
     d = PlanDesc()
     _check(_lib.syk_plan_describe(ham.handle, block, dtype, layout, ct.byref(d)))
     return {f: getattr(d, f) for f, _ in PlanDesc._fields_}
+
+
+def apply_kernel(ham: Hamiltonian, dtype: int) -> int:
+    """The kernel that serves a block of the handle: KERNEL_GATHER, KERNEL_GROUPED or KERNEL_TILED."""
+    k = ct.c_int(-1)
+    _check(_lib.syk_apply_kernel(ham.handle, dtype, ct.byref(k)))
+    return k.value
 
 
 def plan_blocks(ham: Hamiltonian, block: int, dtype: int, layout: int = -1):

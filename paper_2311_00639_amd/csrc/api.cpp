@@ -754,6 +754,16 @@ syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int la
     });
 }
 
+syk_status syk_apply_kernel(const syk_ham *h, syk_dtype dt, int *kernel) {
+    return guarded([&] {
+        require(h && kernel, "NULL argument");
+        require(dt == SYK_C64 || dt == SYK_C128, "invalid dtype");
+        auto &H = const_cast<syk::Hamiltonian &>(h->h);
+        const bool tiled = dt == SYK_C64 ? H.tiled<float>() : H.tiled<double>();
+        *kernel = tiled ? SYK_KERNEL_TILED : H.grouped() ? SYK_KERNEL_GROUPED : SYK_KERNEL_GATHER;
+    });
+}
+
 syk_status syk_plan_describe(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, syk_plan_desc *out) {
     return guarded([&] {
         require(h && out, "NULL argument");
