@@ -567,8 +567,8 @@ syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int la
 
 /* Schedule autotuner: time each compiled variant of the tiled apply_H kernel (tile size,
  * LDS buffering, prefetch depth; each in its planned layout) on this Hamiltonian and keep
- * the fastest for the current device and precision (a block that a gather kernel
- * serves stays with it; see syk_apply_kernel).  *variant receives the choice (-1 if
+ * the fastest for the current device and precision.  A variant pinned by syk_select_variant is
+ * forgotten; a block that a gather kernel serves without one goes (back) to it (syk_apply_kernel).  *variant receives the choice (-1 if
  * L < 18); ms[v] (host, cap entries, may be NULL) the mean time of one
  * apply with variant v (-1 where skipped).  Uses a library-owned workspace of two vectors.
  * Errors: EINVAL, ENOMEM, EDEVICE. */
@@ -576,7 +576,7 @@ syk_status syk_autotune(const syk_ham *h, syk_dtype dt, int *variant, float *ms,
 
 /* Pin the tiled apply_H variant (0 <= variant < the number of entries syk_autotune
  * reports) for this handle, precision and the current device, in place of the default or
- * tuned one: for tests of every variant and for reproducible timings.  Host-only (without
+ * tuned one (and of the gather kernels, from L = 18 up), until syk_autotune: for tests of every variant and for reproducible timings.  Host-only (without
  * a device it applies to device 0, e.g. for syk_plan_describe).  Errors: EINVAL. */
 syk_status syk_select_variant(const syk_ham *h, syk_dtype dt, int variant);
 

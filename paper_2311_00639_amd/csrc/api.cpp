@@ -834,6 +834,13 @@ syk_status syk_autotune(const syk_ham *h, syk_dtype dt, int *variant, float *ms,
                     : syk::autotune<double>(H, reinterpret_cast<double *>(ws.ptr()),
                                             reinterpret_cast<double *>(ws.ptr() + n * es), s, true, &times);
         SYK_HIP(hipStreamSynchronize(s));
+        {
+            // the kernels are chosen anew: a variant pinned before is forgotten
+            int dev = 0;
+            SYK_HIP(hipGetDevice(&dev));
+            std::lock_guard<std::mutex> g(H.dev_mu);
+            H.pinned.erase({dt == SYK_C128 ? 1 : 0, dev});
+        }
         if (variant) *variant = v;
         if (ms)
             for (int k = 0; k < cap; ++k) ms[k] = k < static_cast<int>(times.size()) ? times[k] : -1.0f;

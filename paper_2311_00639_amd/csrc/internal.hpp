@@ -222,7 +222,7 @@ struct Hamiltonian {
     std::map<std::tuple<int, int, int, int, int>, ApplyPlan> plans;
     std::map<std::pair<int, int>, int> rotation;               // (double?, variant) -> planned rotation
     std::map<std::pair<int, int>, int> tuned;                   // (double?, device) -> variant
-    std::set<std::pair<int, int>> pinned;                       // those of them chosen by syk_select_variant
+    std::set<std::pair<int, int>> pinned;                       // those of them chosen by syk_select_variant, until syk_autotune
     // whether the tiled kernel serves the block on the current device: blocks of at least
     // 2^kTiledMinL amplitudes, except, unless a tiled variant is pinned, those that fit an L2
     // (kGatherBytes) and dense ones that the grouped gather kernel serves
