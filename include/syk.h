@@ -213,7 +213,10 @@ typedef struct {
     syk_krylov_opts krylov;
     int profile;           /* 1: time every apply_H launch with HIP events on `stream` */
     int layout;            /* -1: internal vector layout chosen by the planner (see
-                              syk_plan_describe); r >= 0: bit rotation r (0 = standard order) */
+                              syk_plan_describe; the standard order where a gather kernel
+                              serves the block); r >= 0: bit rotation r (0 = standard order).
+                              Blocks with L >= 18 run in the tiled kernel for r > 0, which the
+                              gather kernels cannot; smaller ones ignore it */
     int autotune;          /* 1: before the first run of this handle/precision/device, time the
                               tiled apply_H variants and keep the fastest (syk_autotune) */
     syk_progress_fn progress;   /* optional (NULL = none) */

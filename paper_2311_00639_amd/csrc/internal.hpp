@@ -269,6 +269,10 @@ class DeviceBuffer {
 // per-(device, thread) cached workspace used by the convenience entry points
 DeviceBuffer &thread_workspace(int slot);
 
+// whether the tiled kernel serves vectors in layout rotation `rot`: any rotated layout (the gather kernels
+// know the standard one only), and the standard one where Hamiltonian::tiled() says so
+template <typename T>
+bool served_tiled(Hamiltonian &h, int rot);
 // y = H_blk x on the device: tiled kernel for large blocks, gather kernels otherwise
 template <typename T>
 void apply_block(Hamiltonian &h, int blk, int rot, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s);

@@ -232,8 +232,9 @@ KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, cha
     p += up(static_cast<size_t>(8 * (m + 4)) * sizeof(double));
     fused_ = reinterpret_cast<double *>(p);
     norms_ = fused_ + fused_partials(n);
-    big_ = n > kBigBlock && h_.tiled<T>();
-    plain_ = !h_.tiled<T>() && !fused_range<T>(h_.c_max);
+    const bool tiled = served_tiled<T>(h_, rot);
+    big_ = n > kBigBlock && tiled;
+    plain_ = !tiled && !fused_range<T>(h_.c_max);
     one_ = one_launch_steps<T>(h_);
     n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ ? n / 256 : kNormParts));
 }

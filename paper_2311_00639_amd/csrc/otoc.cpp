@@ -58,9 +58,10 @@ void otoc_run(Hamiltonian &h, int i, int j, double beta, const std::vector<doubl
     char *kws = ws + 4 * vb;
     // every vector of the chain lives in the planner's layout rotation; overlaps are
     // invariant under the permutation
-    const bool tiled = h.tiled<T>();
+    const int asked = h.L >= kTiledMinL ? o.layout : 0;
+    const bool tiled = asked > 0 || h.tiled<T>();
     if (tiled && o.autotune) autotune<T>(h, l, tmp, s, false);     // l, tmp: scratch here
-    const int rot = !tiled ? 0 : (o.layout >= 0 ? o.layout : h.internal_rotation<T>(h.variant<T>()));
+    const int rot = asked >= 0 ? asked : tiled ? h.internal_rotation<T>(h.variant<T>()) : 0;
     KrylovRun<T> kr[2] = {KrylovRun<T>(h, 0, rot, n, o.krylov.m, kws, s),
                           KrylovRun<T>(h, 1, rot, n, o.krylov.m, kws, s)};
     ApplyTimer timer;

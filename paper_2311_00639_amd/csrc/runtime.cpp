@@ -340,11 +340,18 @@ template int Hamiltonian::variant<float>();
 template int Hamiltonian::variant<double>();
 
 template <typename T>
+bool served_tiled(Hamiltonian &h, int rot) {
+    if (rot != 0 && h.L < kTiledMinL) fail(SYK_EDEVICE, "rotated layouts are only planned for tiled blocks");
+    return rot != 0 || h.tiled<T>();
+}
+template bool served_tiled<float>(Hamiltonian &, int);
+template bool served_tiled<double>(Hamiltonian &, int);
+
+template <typename T>
 void apply_block(Hamiltonian &h, int blk, int rot, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s) {
-    if (h.tiled<T>()) {
+    if (served_tiled<T>(h, rot)) {
         launch_apply_tiled<T>(h.plan<T>(blk, rot, h.variant<T>()), x, y, nvec, ld, s);
     } else {
-        if (rot != 0) fail(SYK_EDEVICE, "rotated layouts are only planned for tiled blocks");
         apply_gather<T>(h, {blk, blk}, 1, x, y, nvec, ld, s);
     }
 }
@@ -367,8 +374,7 @@ template void apply_block<double>(Hamiltonian &, int, int, const double *, doubl
 template <typename T>
 int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s) {
-    if (!h.tiled<T>()) {
-        if (rot != 0) fail(SYK_EDEVICE, "rotated layouts are only planned for tiled blocks");
+    if (!served_tiled<T>(h, rot)) {
         return apply_gather<T>(h, {blk, blk}, 1, x, y, 1, 1ULL << h.L, s, &lf);
     }
     const ApplyPlan &pl = h.plan<T>(blk, rot, h.variant<T>());

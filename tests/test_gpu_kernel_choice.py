@@ -1,4 +1,4 @@
-"""The kernel that serves a block, where a GPU decides: pinned variants and autotuning."""
+"""The kernel that serves a block, where a GPU decides: pinned variants, autotuning and vector layouts."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -32,3 +32,29 @@ def test_autotune_forgets_a_pinned_variant(dt):
     syk.select_variant(big, dt, 9)
     syk.autotune(big, dt)
     assert syk.apply_kernel(big, dt) == syk.KERNEL_TILED
+
+
+@pytest.mark.parametrize("N,dt", [(38, syk.C64), (38, syk.C128), (40, syk.C64), (42, syk.C64), (42, syk.C128)])
+def test_otoc_in_an_explicit_layout_runs_in_the_tiled_kernel(N, dt):
+    """Blocks that are gathered by default (2^18, and 2^19 in complex64) and tiled ones: a rotated layout is
+    the tiled kernel's, bit for bit what a handle pinned to it gives.  All agree within the bound of the
+    precision's correlators in the parity tests."""
+    h, pinned = (syk.create_hamiltonian(N, 4, 2, 7) for _ in range(2))
+    syk.select_variant(pinned, dt, syk.plan_describe(h, 0, dt)["variant"])
+    gathered = syk.apply_kernel(h, dt) == syk.KERNEL_GATHER
+    assert gathered == (N == 38 or (N == 40 and dt == syk.C64))
+    ts = [0.0, 1.0]
+
+    def run(ham, layout):
+        return syk.otoc(ham, N - 1, N - 2, 2.0, ts, nvec=1, state_seed=3, dtype=dt, layout=layout, autotune=False)[0]
+
+    ref = run(h, 0)
+    tol = 1e-9 if dt == syk.C128 else 1e-5
+    rotated = [(run(h, r), run(pinned, r)) for r in (1, 7, N // 2 - 2)]
+    for a, b in rotated + [(run(h, -1), ref), (run(pinned, 0), ref)]:
+        assert abs(a - ref).max() <= tol * max(1.0, abs(ref).max())
+    for a, b in rotated:
+        assert (a == b).all()
+    assert any((a != ref).any() for a, b in rotated)      # another order of sums, so not the kernel of `ref`
+    if gathered:
+        assert (run(h, -1) == ref).all()
