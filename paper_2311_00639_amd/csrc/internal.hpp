@@ -104,8 +104,11 @@ struct DeviceTables {            // per device, per block: the gather kernels' t
     DenseTerm<double> *d64 = nullptr;
 };
 // Blocks whose terms share x masks this often or more (terms per mask) use the grouped form,
-// from one 64-amplitude tile up to 2^22 amplitudes (where the gathers still come from the
-// 256 MB last-level cache; larger dense blocks stay with the tiled kernel, unmeasured).
+// from one 64-amplitude tile up to 2^22 amplitudes, where the gathers still come from the
+// 256 MB last-level cache.  Dense SYK, grouped / best tiled variant, complex64 and complex128: N = 38 0.73 / 8.2
+// and 1.21 / 10.6 ms, N = 42 3.9 / 17 and 6.3 / 25 ms, N = 46 (2^22) 20.7 / 88 and 35 / 155 ms.  It is four times as
+// fast at the limit and would be beyond it; larger dense blocks stay with the tiled kernel,
+// which they had, until they are tested here.
 constexpr int kDenseTermsPerMask = 4;
 constexpr int kDenseMinL = 6, kDenseMaxL = 22;
 // complex64 blocks up to this size take 64-amplitude tiles (complex128: one more)
