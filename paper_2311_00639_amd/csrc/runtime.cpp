@@ -389,9 +389,11 @@ template int apply_block_lanczos<double>(Hamiltonian &, int, int, const double *
 
 // Step j of one launch reads three vectors per term where two launches read one, and adds up three sums
 // before its first term.  That costs less than a launch (about 4 us from one dependent launch to the
-// next) while the further reads stay below 16 MB.  A propagation of 12 steps at k = 4, two launches / one: N = 16
-// 135 / 111 us, N = 26 153 / 139 us (14 MB), N = 30 165 / 179 us (63 MB) in complex128; N = 20 118 / 96 us, N = 28
-// 120 / 103 us (15 MB) in complex64.
+// next) while the further reads stay below 16 MB.  Two launches / one, a propagation of 12 steps in
+// complex128: N = 16 151 / 136 us, N = 24 154 / 147 us (6 MB), N = 26 155 / 148 us (14 MB), N = 28 k = 2 153 / 152 us
+// (15 MB), N = 26 k = 8 161 / 162 us (27 MB), N = 28 k = 4 155 / 157 us (29 MB) and k = 8 162 / 174 us (59 MB); of 10 steps in
+// complex64: N = 20 133 / 121 us, N = 28 k = 2 135 / 128 us (7 MB), N = 26 k = 8 141 / 142 us (14 MB), N = 28 k = 4 137 / 134
+// us (15 MB) and k = 8 143 / 148 us (29 MB).
 template <typename T>
 bool one_launch_steps(Hamiltonian &h) {
     return h.L <= 13 && !h.grouped() && 2.0 * h.K * static_cast<double>(1u << h.L) * 2 * sizeof(T) <= 16e6;
