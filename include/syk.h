@@ -304,7 +304,10 @@ typedef struct {
 
 /* F_raw, F_norm, F_imag: host, n_items x nt doubles (row r = item r; any may be NULL),
  * as syk_otoc's outputs of each item.  t: host, nt non-decreasing times >= 0.  Synchronises
- * `stream`.  Errors: EINVAL, EUNSUPPORTED (block size outside every shape), ENOMEM,
+ * `stream`.  The vectors of the slots, at most (m + 5) 2^L complex64 amplitudes for each of one to
+ * four workgroups per CU (4.4 GB at N = 32, m = 60), live in the calling thread's cached workspace, which
+ * keeps its size until syk_release_workspace; where that much cannot be allocated the call runs with
+ * fewer slots, one at least.  Errors: EINVAL, EUNSUPPORTED (block size outside every shape), ENOMEM,
  * EDEVICE, ENOTCONV, ENUMERIC. */
 syk_status syk_otoc_batch(const syk_batch_item *items, int n_items, const double *t, int nt,
                           const syk_batch_opts *o, double *F_raw, double *F_norm, double *F_imag,
@@ -583,7 +586,8 @@ syk_status syk_autotune(const syk_ham *h, syk_dtype dt, int *variant, float *ms,
  * a device it applies to device 0, e.g. for syk_plan_describe).  Errors: EINVAL. */
 syk_status syk_select_variant(const syk_ham *h, syk_dtype dt, int variant);
 
-/* Release the library's cached device workspaces on the current device. */
+/* Release the library's cached workspaces: the calling thread's device workspaces on the current
+ * device, and the idle blocks of pinned host memory of the Lanczos runs (all threads). */
 syk_status syk_release_workspace(void);
 
 /* Identifier of the apply_H kernel revision built into this library (changes whenever the

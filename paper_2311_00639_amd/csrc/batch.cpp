@@ -223,7 +223,7 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
 
     const int slots = device_cus() * shape.occ;
     const std::vector<BatchPart> parts = make_parts(jobs, ts, o.beta, o.tol, slots);
-    const int grid = std::min<int>(static_cast<int>(parts.size()), slots);
+    int grid = std::min<int>(static_cast<int>(parts.size()), slots);
 
     BatchParams p{};
     p.n_parts = static_cast<int>(parts.size());
@@ -248,8 +248,18 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
     const size_t at_terms = piece(terms.size() * sizeof(BatchTerm)), at_ts = piece(ts.size() * sizeof(double));
     const size_t at_F = piece(n_F * sizeof(double)), at_res = piece(parts.size() * sizeof(BatchResult));
     const size_t at_counter = piece(sizeof(unsigned));
-    const size_t at_ws = piece(static_cast<size_t>(grid) * p.slot_stride * sizeof(float2));
-    ws.ensure(need);
+    // The slots' vectors last.  A few jobs cut into many parts ask for more slots than there are jobs;
+    // where memory is short fewer serve them all (a workgroup takes parts until none is left).
+    const size_t at_ws = need, per_slot = p.slot_stride * sizeof(float2);
+    for (;;) {
+        try {
+            ws.ensure(at_ws + static_cast<size_t>(grid) * per_slot);
+            break;
+        } catch (const Error &e) {
+            if (e.status != SYK_ENOMEM || grid == 1) throw;
+            grid = (grid + 1) / 2;
+        }
+    }
     char *base = ws.ptr();
     auto put = [&](size_t at, const auto &v) {
         if (!v.empty())

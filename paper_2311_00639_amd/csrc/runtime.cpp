@@ -502,7 +502,11 @@ void DeviceBuffer::ensure(size_t bytes) {
                              std::to_string(n_));
     release();
     void *p = nullptr;
-    SYK_HIP(hipMalloc(&p, bytes));
+    const hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess) {
+        ignore_status(hipGetLastError());        // reported here, not by the next launch's check too
+        hip_check(e, "hipMalloc of a workspace");
+    }
     p_ = static_cast<char *>(p);
     n_ = bytes;
 }

@@ -1,5 +1,6 @@
-"""That batched jobs are cut: a lone item fills more workgroups than its whole jobs would, and a large batch
-none.  A job is an (item, vector) pair of two parity-block chains; a part is a range of one chain's t points."""
+"""Parts and slots of the batched OTOC.  Jobs are cut so that a lone item fills more workgroups than its
+whole jobs would, and a large batch is not.  A job is an (item, vector) pair of two parity-block chains; a
+part is a range of one chain's t points."""
 import numpy as np
 import pytest
 
@@ -30,3 +31,24 @@ def test_a_lone_item_is_cut_at_its_t_points(N, variant, ts):
         assert many[3]["matvecs"] == count * one[3]["matvecs"]
         for a, b in zip(one[:3], many[:3]):
             assert all(np.array_equal(a[0], row) for row in b)
+
+
+def test_short_of_memory_runs_with_fewer_slots():
+    """With about 1 GiB left, fewer slots than the item's parts (2.8 GB of vectors) serve them, with the same result."""
+    torch.cuda.set_device(0)
+    item, ts = [(32, 2, 300, 31, 30, 900)], [0.02 * k for k in range(40)]
+    full = syk.otoc_batch(item, 0.5, ts, nvec=2, m=60)
+    assert full[3]["slots"] >= 150
+    syk.release_workspace()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    hold = torch.empty(free - (1 << 30), dtype=torch.uint8, device="cuda")
+    try:
+        few = syk.otoc_batch(item, 0.5, ts, nvec=2, m=60)
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+        syk.release_workspace()
+    assert 1 <= few[3]["slots"] < 100
+    for a, b in zip(full[:3], few[:3]):
+        assert np.array_equal(a, b)
