@@ -571,6 +571,14 @@ syk_status syk_apply_kernel(const syk_ham *h, syk_dtype dt, int *kernel);
 syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, uint32_t *out, size_t cap,
                            size_t *n_words);
 
+/* The same blocks as the kernel reads them (uploaded form): the words of record j are the LDS byte
+ * offset mask of the partner (thread and register bits of x, times the amplitude size) | (register
+ * sign mask) << 24; the bits of z below the register bits and, next to them, those above; the
+ * coefficient (one or two words); the last word of a record is not read.  Lanes 60 to 63 are
+ * those of syk_plan_blocks.  Arguments and errors as there. */
+syk_status syk_plan_device_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, uint32_t *out,
+                                  size_t cap, size_t *n_words);
+
 /* Schedule autotuner: time each compiled variant of the tiled apply_H kernel (tile size,
  * LDS buffering, prefetch depth; each in its planned layout) on this Hamiltonian and keep
  * the fastest for the current device and precision.  A variant pinned by syk_select_variant is

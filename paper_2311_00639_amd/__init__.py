@@ -49,6 +49,7 @@ from ._lib import (  # noqa: F401
     otoc_ensemble,
     plan_blocks,
     plan_describe,
+    plan_device_blocks,
     release_workspace,
     select_variant,
     tridiag_expm,

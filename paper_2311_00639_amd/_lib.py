@@ -148,6 +148,7 @@ _SIGS = {
     "syk_plan_describe": [_vp, _i, _i, _i, ct.POINTER(PlanDesc)],
     "syk_apply_kernel": [_vp, _i, ct.POINTER(_i)],
     "syk_plan_blocks": [_vp, _i, _i, _i, ct.c_void_p, ct.c_size_t, ct.POINTER(ct.c_size_t)],
+    "syk_plan_device_blocks": [_vp, _i, _i, _i, ct.c_void_p, ct.c_size_t, ct.POINTER(ct.c_size_t)],
     "syk_autotune": [_vp, _i, ct.POINTER(_i), ct.POINTER(ct.c_float), _i, _vp],
     "syk_select_variant": [_vp, _i, _i],
     "syk_op_create": [_i, ct.c_size_t, _vp, _vp, _dp, _dp, ct.POINTER(_vp)],
@@ -560,13 +561,22 @@ def apply_kernel(ham: Hamiltonian, dtype: int) -> int:
     return k.value
 
 
+def _plan_words(call, ham, block, dtype, layout):
+    n = ct.c_size_t()
+    _check(call(ham.handle, block, dtype, layout, None, 0, ct.byref(n)))
+    out = np.zeros(n.value, dtype=np.uint32)
+    _check(call(ham.handle, block, dtype, layout, out.ctypes.data, n.value, ct.byref(n)))
+    return out.reshape(-1, 64)
+
+
 def plan_blocks(ham: Hamiltonian, block: int, dtype: int, layout: int = -1):
     """Control blocks of the tiled apply_H plan (host-only): uint32 array (blocks, 64)."""
-    n = ct.c_size_t()
-    _check(_lib.syk_plan_blocks(ham.handle, block, dtype, layout, None, 0, ct.byref(n)))
-    out = np.zeros(n.value, dtype=np.uint32)
-    _check(_lib.syk_plan_blocks(ham.handle, block, dtype, layout, out.ctypes.data, n.value, ct.byref(n)))
-    return out.reshape(-1, 64)
+    return _plan_words(_lib.syk_plan_blocks, ham, block, dtype, layout)
+
+
+def plan_device_blocks(ham: Hamiltonian, block: int, dtype: int, layout: int = -1):
+    """The same control blocks as they are uploaded (host-only): uint32 array (blocks, 64)."""
+    return _plan_words(_lib.syk_plan_device_blocks, ham, block, dtype, layout)
 
 
 def autotune(ham: Hamiltonian, dtype: int, stream=None):

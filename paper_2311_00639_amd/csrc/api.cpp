@@ -729,8 +729,9 @@ syk_status syk_tridiag_expm(int n, const double *alpha, const double *beta, doub
     });
 }
 
-syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, uint32_t *out, size_t cap,
-                           size_t *n_words) {
+// the control blocks of a plan, as planned or as uploaded
+static syk_status plan_words(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, bool uploaded, uint32_t *out,
+                             size_t cap, size_t *n_words) {
     return guarded([&] {
         require(h && n_words, "NULL argument");
         require(blk == SYK_BLOCK_U || blk == SYK_BLOCK_D, "invalid block");
@@ -746,12 +747,23 @@ syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int la
         const int rot = layout >= 0 ? layout : (c64 ? H.internal_rotation<float>(var) : H.internal_rotation<double>(var));
         const syk::HostPlan hp = syk::build_host_plan(H.block_terms[blk], H.L, tv.bt, tv.rb, tv.nbuf, tv.pf, rot,
                                                       c64 ? 8u : 16u, syk::resident_bits(tv), tv.sr, tv.w);
-        *n_words = hp.meta.size();
+        const std::vector<uint32_t> words = uploaded ? syk::device_blocks(hp, tv.bt, tv.rb, c64 ? 8u : 16u) : hp.meta;
+        *n_words = words.size();
         if (out) {
-            require(cap >= hp.meta.size(), "cap is smaller than the control blocks");
-            std::copy(hp.meta.begin(), hp.meta.end(), out);
+            require(cap >= words.size(), "cap is smaller than the control blocks");
+            std::copy(words.begin(), words.end(), out);
         }
     });
+}
+
+syk_status syk_plan_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, uint32_t *out, size_t cap,
+                           size_t *n_words) {
+    return plan_words(h, blk, dt, layout, false, out, cap, n_words);
+}
+
+syk_status syk_plan_device_blocks(const syk_ham *h, syk_block blk, syk_dtype dt, int layout, uint32_t *out,
+                                  size_t cap, size_t *n_words) {
+    return plan_words(h, blk, dt, layout, true, out, cap, n_words);
 }
 
 syk_status syk_apply_kernel(const syk_ham *h, syk_dtype dt, int *kernel) {

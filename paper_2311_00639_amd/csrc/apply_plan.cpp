@@ -466,7 +466,7 @@ void free_plan(ApplyPlan &p) {
 // term decodes with one vector operation less per mask.  Word 0: LDS byte mask of the
 // partner (thread bits, then register bits, times the amplitude size) | register sign mask << 24;
 // word 1: thread bits of z, then the tile bits; word 2 (and 3): the coefficient.
-static std::vector<uint32_t> device_blocks(const HostPlan &hp, int bt, int rb, uint32_t elem_bytes) {
+std::vector<uint32_t> device_blocks(const HostPlan &hp, int bt, int rb, uint32_t elem_bytes) {
     std::vector<uint32_t> m = hp.meta;
     const uint32_t rd = block_record_dwords(elem_bytes), es = elem_bytes == 8 ? 3 : 4;
     const int tb = bt - rb;

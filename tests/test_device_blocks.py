@@ -1,0 +1,67 @@
+"""The control blocks of the tiled kernel as they are uploaded, decoded with the kernel's own operations and
+compared with the Hamiltonian's terms (without a GPU)."""
+import numpy as np
+import pytest
+
+import paper_2311_00639_amd as syk
+
+# control-block variants: (tile bits, register bits, log2 tiles per workgroup)
+C64 = {8: (13, 3, 0), 9: (13, 3, 1), 10: (13, 3, 2), 11: (11, 2, 0), 12: (10, 2, 0), 13: (11, 2, 1), 14: (12, 3, 2),
+       15: (12, 2, 2), 16: (12, 3, 1)}
+C128 = {8: (12, 2, 0), 9: (12, 2, 1), 10: (12, 2, 2), 11: (11, 2, 0), 12: (10, 2, 0), 13: (11, 2, 1), 14: (11, 2, 2),
+        15: (11, 1, 2), 16: (10, 1, 2)}
+
+
+def _par(v):
+    return bin(int(v)).count("1") & 1
+
+
+def _rotr(v, s, L):
+    return ((v >> s) | (v << (L - s))) & ((1 << L) - 1) if s else v
+
+
+@pytest.mark.parametrize("dt,variant", [(syk.C64, v) for v in C64] + [(syk.C128, v) for v in C128])
+@pytest.mark.parametrize("N,blk,layout", [(40, 0, -1), (42, 1, 0), (56, 1, 5)])
+def test_uploaded_records_act_as_the_terms(N, blk, layout, dt, variant):
+    """Each record's partner offset and the signs that the kernel forms at single index bits give back one
+    term's masks and coefficient, and every (tile, term) pair occurs once."""
+    bt, rb, w = (C64 if dt == syk.C64 else C128)[variant]
+    es, rd, f = (3, 4, np.float32) if dt == syk.C64 else (4, 5, np.float64)
+    h = syk.create_hamiltonian(N, 4, 3, N)
+    syk.select_variant(h, dt, variant)
+    d = syk.plan_describe(h, blk, dt, layout)
+    assert d["tile_bits"] == bt and d["tiles_per_wg"] == 1 << w
+    L, tb, R = N // 2 - 1, bt - rb, 1 << rb
+    planned, blocks = syk.plan_blocks(h, blk, dt, layout), syk.plan_device_blocks(h, blk, dt, layout)
+    assert (blocks[:, 60:] == planned[:, 60:]).all()
+    T = h.terms()
+    want = {}
+    for a in range(len(T["J"])):
+        x, z = int(T["xmask"][a]), int(T["zmask"][a])
+        p = (int((T["phase_U"] if blk == 0 else T["phase_D"])[a]) + 2 * _par(x & z)) & 3
+        c = f(0.25 * T["J"][a] * (-1.0 if p in (2, 3) else 1.0))
+        key = (_rotr(x, d["rot"], L) & ((1 << bt) - 1), _rotr(z, d["rot"], L), c.tobytes(), p & 1)
+        want[key] = want.get(key, 0) + (1 << w)
+    got = {}
+    for b in blocks[:-1]:
+        cnt, j = int(b[60]), 0
+        for i in range(1 << w):
+            for imag in (0, 1):
+                for _ in range((cnt >> (8 * i + 4 * imag)) & 15):
+                    w0, w1 = int(b[rd * j]), int(b[rd * j + 1])
+
+                    def sign(tid, r, tile):
+                        tz = tid | tile << tb                      # the kernel's thread word
+                        return _par(tz & w1) ^ (((w0 << (7 - r)) >> 31) & 1 if r else 0)
+
+                    off = w0 & 0xffffff
+                    assert off & ((1 << es) - 1) == 0 and off >> (es + bt) == 0
+                    z = sum(sign(1 << q, 0, 0) << q for q in range(tb))
+                    z |= sum(sign(0, 1 << q, 0) << (tb + q) for q in range(rb))
+                    z |= sum(sign(0, 0, 1 << q) << (bt + q) for q in range(L - bt))
+                    for r in range(R):                             # the mask is that of every register
+                        assert sign(0, r, 0) == _par(r & (z >> tb))
+                    key = (off >> es, z, b[rd * j + 2:rd * j + 2 + f().nbytes // 4].tobytes(), imag)
+                    got[key] = got.get(key, 0) + 1
+                    j += 1
+    assert got == want
