@@ -283,9 +283,10 @@ void apply_block(Hamiltonian &h, int blk, int rot, const T *x, T *y, int nvec, u
 template <typename T>
 void apply_full(Hamiltonian &h, const T *x, T *y, int nvec, uint64_t ld, hipStream_t s);
 // y = H_blk x with the fused Lanczos epilogue; returns the number of partials written (one per
-// workgroup)
+// workgroup).  tiled: served_tiled() as it was when the run began (a variant pinned or forgotten by
+// another thread must not change who adds the partials up)
 template <typename T>
-int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
+int apply_block_lanczos(Hamiltonian &h, int blk, int rot, bool tiled, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s);
 // whether one launch per Lanczos step serves the block (apply_step)
 template <typename T>

@@ -232,9 +232,9 @@ KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, cha
     p += up(static_cast<size_t>(8 * (m + 4)) * sizeof(double));
     fused_ = reinterpret_cast<double *>(p);
     norms_ = fused_ + fused_partials(n);
-    const bool tiled = served_tiled<T>(h_, rot);
-    big_ = n > kBigBlock && tiled;
-    plain_ = !tiled && !fused_range<T>(h_.c_max);
+    tiled_ = served_tiled<T>(h_, rot);
+    big_ = n > kBigBlock && tiled_;
+    plain_ = !tiled_ && !fused_range<T>(h_.c_max);
     one_ = one_launch_steps<T>(h_);
     n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ ? n / 256 : kNormParts));
 }
@@ -491,7 +491,7 @@ void KrylovRun<T>::enqueue(int j, const T *u0) {
     lf.norm2_host = host_.dev(host_.norm2(j));
     pending_ = true;
     if (timer_) timer_->begin(s_);
-    const int np = apply_block_lanczos<T>(h_, blk_, rot_, u, w, lf, s_);
+    const int np = apply_block_lanczos<T>(h_, blk_, rot_, tiled_, u, w, lf, s_);
     if (timer_) timer_->end(s_);
     double *al = alpha_ + j, *al_host = host_.dev(host_.alpha(j));
     const bool reduce = !big_ && np <= kNormParts;

@@ -130,6 +130,7 @@ class KrylovRun {
     T *basis_ = nullptr;
     double *partials_ = nullptr, *alpha_ = nullptr, *beta2_ = nullptr, *coef_ = nullptr, *scratch_ = nullptr;
     double *fused_ = nullptr, *norms_ = nullptr;
+    bool tiled_ = false;                  // the tiled kernel serves the block
     bool plain_ = false;                  // H is too small or large for unnormalised vectors
     bool one_ = false;                    // one launch per step
     int n_step_ = 0;                      // its workgroups

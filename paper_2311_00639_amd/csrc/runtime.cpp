@@ -372,9 +372,9 @@ template void apply_block<float>(Hamiltonian &, int, int, const float *, float *
 template void apply_block<double>(Hamiltonian &, int, int, const double *, double *, int, uint64_t, hipStream_t);
 
 template <typename T>
-int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, const LanczosFuse<T> &lf,
+int apply_block_lanczos(Hamiltonian &h, int blk, int rot, bool tiled, const T *x, T *y, const LanczosFuse<T> &lf,
                         hipStream_t s) {
-    if (!served_tiled<T>(h, rot)) {
+    if (!tiled) {
         return apply_gather<T>(h, {blk, blk}, 1, x, y, 1, 1ULL << h.L, s, &lf);
     }
     const ApplyPlan &pl = h.plan<T>(blk, rot, h.variant<T>());
@@ -382,9 +382,9 @@ int apply_block_lanczos(Hamiltonian &h, int blk, int rot, const T *x, T *y, cons
     launch_apply_tiled<T>(pl, x, y, 1, 1ULL << h.L, s, &lf);
     return static_cast<int>(pl.n_wg);
 }
-template int apply_block_lanczos<float>(Hamiltonian &, int, int, const float *, float *,
+template int apply_block_lanczos<float>(Hamiltonian &, int, int, bool, const float *, float *,
                                         const LanczosFuse<float> &, hipStream_t);
-template int apply_block_lanczos<double>(Hamiltonian &, int, int, const double *, double *,
+template int apply_block_lanczos<double>(Hamiltonian &, int, int, bool, const double *, double *,
                                          const LanczosFuse<double> &, hipStream_t);
 
 // Step j of one launch reads three vectors per term where two launches read one, and adds up three sums

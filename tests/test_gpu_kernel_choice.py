@@ -1,4 +1,4 @@
-"""The kernel that serves a block, where a GPU decides: pinned variants, autotuning and vector layouts."""
+"""The kernel that serves a block, where a GPU decides: pinned variants, autotuning, vector layouts."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -58,3 +58,46 @@ def test_otoc_in_an_explicit_layout_runs_in_the_tiled_kernel(N, dt):
     assert any((a != ref).any() for a, b in rotated)      # another order of sums, so not the kernel of `ref`
     if gathered:
         assert (run(h, -1) == ref).all()
+
+
+def test_a_run_keeps_its_kernel_while_another_thread_pins_and_tunes():
+    """A dense block of 2^22 amplitudes: the two kernels leave their partial sums to be added by different
+    launches, so a run may not change kernels half way.  Results of both kernels agree within the Krylov
+    bound, whichever a run began with."""
+    import threading
+
+    import numpy as np
+    L, rng = 22, np.random.default_rng(5)
+    x = np.repeat(np.array([0, 5, 77, 1 << 21], dtype=np.uint64), 5)
+    z = (np.arange(20, dtype=np.uint64) * np.uint64(7919)) % np.uint64(1 << L)
+    odd = np.array([bin(int(a & b)).count("1") & 1 for a, b in zip(x, z)])
+    h = syk.Operator(L, x, z, rng.standard_normal(20) / 5.0 * np.where(odd, 1j, 1.0)).to_hamiltonian()
+    v = torch.randn(1 << L, dtype=torch.complex64, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    v /= torch.linalg.vector_norm(v)
+    ref = torch.empty_like(v)
+    syk.krylov_expm(h, 0, -0.4 + 0.9j, v, ref, reorth=2)
+    torch.cuda.synchronize()
+    stop, errors = threading.Event(), []
+
+    def flip():
+        try:
+            s = torch.cuda.Stream()
+            while not stop.is_set():
+                syk.select_variant(h, syk.C64, 10)
+                stop.wait(0.002)
+                syk.autotune(h, syk.C64, stream=s)
+            syk.release_workspace()
+        except Exception as e:                            # reported by the test's thread
+            errors.append(e)
+
+    t = threading.Thread(target=flip)
+    t.start()
+    try:
+        out = torch.empty_like(v)
+        for _ in range(60):
+            syk.krylov_expm(h, 0, -0.4 + 0.9j, v, out)
+            assert float(torch.linalg.vector_norm(out - ref)) <= 1e-5
+    finally:
+        stop.set()
+        t.join()
+    assert not errors
