@@ -177,8 +177,9 @@ typedef struct {
 
 /* Fill `o` with defaults for dtype dt (m = 30, tol = 1e-12 for C128 / 1e-7 for C64,
  * reorth = 0, max_substeps = 0).  With reorth = 0 each Lanczos step is one fused apply
- * (w = H v_j - beta v_{j-1} plus the alpha sums) and one residual pass, and steps are enqueued
- * ahead of the host's checks. */
+ * (w = H v_j - beta v_{j-1} plus the alpha sums) and one residual pass, or one launch for both on
+ * small sparse blocks (L <= 13, at most 16 MB of 2 K 2^L amplitudes), and steps are enqueued ahead
+ * of the host's checks. */
 void syk_krylov_default_opts(syk_dtype dt, syk_krylov_opts *o);
 
 /* out = e^{z H_blk} v, z = z_re + i z_im, by Lanczos with restarts (the restarted Krylov

@@ -1,8 +1,9 @@
 // apply_H of small and of dense blocks, straight from memory (gfx950).
 //
 // y[m] = sum_a c_a i^{imag_a} (-1)^{popc(m & z_a)} x[m ^ x_a]   (supplement Algorithm 1, with the
-// sign parity of x_a & z_a folded into c_a).  A parity block of at most 4 MiB sits in every L2, so
-// partners are gathered from there and nothing is staged.
+// sign parity of x_a & z_a folded into c_a).  Partners are gathered and nothing is staged: a sparse
+// block of at most 4 MiB sits in every L2, and a dense one, of up to 2^22 amplitudes (32 or 64 MiB),
+// in the last-level cache, where one gather serves all the terms of an x mask.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -39,7 +40,7 @@ __device__ __forceinline__ double2 load_amp(__amdgpu_buffer_rsrc_t r, uint32_t v
 constexpr uint32_t kBufferWord3 = 0x00020000u;   // raw buffer descriptor: 32-bit data format, no swizzle
 
 // The Lanczos epilogue (LanczosFuse) of a workgroup of S waves, S >= 4.  n_j^2 is the sum of the partials
-// the previous pass left (at most 512): the first 256 threads load them before the apply and the
+// the previous pass left (at most 1024): the first 256 threads load them before the apply and the
 // sum is ready after the barrier that ends it, so no launch of its own is needed for it.
 template <typename T, int S>
 struct Epilogue {
@@ -128,8 +129,8 @@ __device__ __forceinline__ typename Quad<T>::V load_quad(__amdgpu_buffer_rsrc_t 
 // wave-uniform, so term records come through scalar loads; the partner of row r is (lane ^ x) in a
 // VGPR plus a scalar offset, so a gather costs no vector address arithmetic; the sign of the
 // lane and base bits is folded into the coefficient once per term and the sign of the row and the element
-// is one XOR; U terms' gathers are in flight at once.  N = 36, k = 8: complex64 10.6 us against 18.1 us
-// with 8-byte gathers, complex128 18.6 us (K 2^17 16 bytes at 39 TB/s of all vector caches: 15.4 us); 59 / 68 us with
+// is one XOR; U terms' gathers are in flight at once.  N = 36, k = 8: complex64 10.2 us against 18.1 us
+// with 8-byte gathers, complex128 18.5 us (K 2^17 16 bytes at 39 TB/s of all vector caches: 15.4 us); 59 / 68 us with
 // one amplitude per thread and per-lane term loads.
 template <typename T, int R, int S, bool FUSE>
 __global__ void __launch_bounds__(64 * S) gather_sparse(GatherTerms<T> t0, GatherTerms<T> t1,
@@ -491,7 +492,7 @@ __global__ void __launch_bounds__(1024) lanczos_close(LanczosStep<T> st, uint32_
 // six to build A and B and the rest the complex product of a group of 16 terms.  Hence the table
 // pairs a real with an i-phase step, so that a step needs no phase branch and two sums run
 // independently, and the operands of four steps are built before their products, which hides the
-// LDS reads: N = 30 86 -> 59 us (complex128), N = 38 0.82 -> 0.64 / 1.29 -> 1.05 ms (complex64 /
+// LDS reads: N = 30 86 -> 53 us (complex128), N = 38 0.82 -> 0.62 / 1.29 -> 1.04 ms (complex64 /
 // complex128).  Term by term on the vector unit N = 30 took 278 / 391 us, in the tiled kernel N = 38 9.1 ms
 // (complex64).
 //
@@ -703,12 +704,12 @@ int launch_apply_dense(const DeviceTables *const (&tb)[2], int nblk, const T *x,
                                d[nblk - 1], reinterpret_cast<const V *>(x), reinterpret_cast<V *>(y), n, ld,
                                LanczosFuse<T>{});
     };
-    // Small blocks take 64-amplitude tiles to reach more CUs (N = 30: 56 us against 70 us in
-    // complex64 and 59 us against 106 us in complex128 with 256-amplitude tiles), larger ones 256
-    // (four times the amplitudes per step; N = 32, complex64: 92 us against 129 us; N = 32, complex128: 136 us
-    // against 134 us).  Sixteen waves share a tile while the tiles are few, and in complex64 always, as its sums
-    // are then shorter (N = 38: 635 us against 650 us, error 3.1e-7 against 4.2e-7); complex128 takes eight
-    // from 2^17 amplitudes (N = 38: 1.05 ms against 1.13 ms).
+    // Small blocks take 64-amplitude tiles to reach more CUs, larger ones 256 (four times the amplitudes per
+    // step).  64 / 256: complex64 N = 28 39 / 52 us, N = 30 51 / 69 us, N = 32 117 / 89 us; complex128 N = 30 53 / 106 us,
+    // N = 32 122 / 136 us, N = 34 296 / 176 us.  Sixteen waves share a tile while the tiles are few, and in
+    // complex64 always, as its sums are then shorter; complex128 takes eight from 2^17 amplitudes.  Sixteen / eight:
+    // complex64 N = 32 89 / 105 us, N = 38 616 / 644 us, error 3.1e-7 / 4.2e-7; complex128 N = 34 176 / 190 us,
+    // N = 38 1.10 / 1.04 ms.
     constexpr bool f32 = sizeof(T) == 4;
     if (n <= (f32 ? 1u << kDenseRowL32 : 1u << (kDenseRowL32 + 1)))
         go(double(0), MfmaRow{}, std::integral_constant<int, 16>{});

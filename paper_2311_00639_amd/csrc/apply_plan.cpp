@@ -337,9 +337,11 @@ HostPlan build_host_plan(const std::vector<BlockTerm> &terms, int L, int bt, int
     // tiles that the resident workgroups of an XCD read in one step (8 MiB in four sets of 2 MiB
     // for four 64 KiB tiles per workgroup, against 4 MiB of L2): with the steps of a set next to each
     // other its tiles miss L2 once.  Within a set the step with the most terms comes last: the
-    // copy that runs behind it is the first of the next set, which misses.  N = 56, k = 4,
-    // complex64, variant 10 in standard order: 10.4 -> 8.1 ms (seed 2), 11.6 -> 8.9 ms (seed 56); N = 50: 0.76 -> 0.70 ms;
-    // the heaviest-last rule is 1-2% of it.
+    // copy that runs behind it is the first of the next set, which misses.  Six seeds at k = 4,
+    // variant 10, complex64: N = 56 in standard order 9.3-11.5 -> 7.5-9.6 ms (mean 10.5 -> 8.4), in the planned
+    // layout 6.7-10.8 -> 6.8-9.2 ms (mean 8.8 -> 7.8; the more L2 sets the layout leaves, the more it gives:
+    // nothing for two of the six); N = 50 0.68-0.81 -> 0.62-0.63 ms and 0.60-0.79 -> 0.59-0.62 ms; the
+    // heaviest-last rule is 1-2% of it.
     Echelon E5, E8, Ex;
     for (uint32_t v : c.wx) Ex.add(v);
     for (uint32_t v : c.H) {

@@ -183,9 +183,9 @@ void otoc_batch(const syk_batch_item *items, int n_items, const double *t, int n
 
     // Launch shape: the widest workgroups (the longest parts end soonest) that still hold four
     // amplitudes per thread of the largest block; below that the workgroup's fixed costs per step weigh
-    // more than its width.  Kernel times of the eligible shapes (1024, 512, 256 threads), complex64:
-    // 64 realisations x 4 states, N 24-32: 111, 146 ms; N = 28: 32, 33, 59 ms; N = 24: 16.3, 12.9,
-    // 16.0 ms; 256 x 2 at N = 20: -, 11.4, 11.4 ms.
+    // more than its width.  Kernel times of the eligible shapes (1024, 512, 256 threads), beta = 5, four t
+    // points: 64 realisations x 4 states, N 24-32: 40.6, 70.2 ms; N = 28: 22.6, 22.2, 30.5 ms; N = 24: 10.1, 8.2,
+    // 7.6 ms (the rule takes 512 threads); 256 x 2 at N = 20: -, 7.3, 5.7 ms.
     int chosen = o.variant;
     if (chosen < 0) {
         chosen = elig.back();

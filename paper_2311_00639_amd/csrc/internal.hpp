@@ -139,9 +139,9 @@ int default_variant(int L);
 // smallest block (in qubits) that the tiled kernel can serve
 constexpr int kTiledMinL = 18;
 // Blocks that fit the 4 MiB L2 of one XCD are gathered straight from there.  Gather against tiled
-// apply at k = 4: 2^18 amplitudes 11.1 / 26 us in complex64 and 20 / 32 us in complex128 (4 MiB), 2^19
-// amplitudes 21.5 / 34 us in complex64 (4 MiB) and 47 / 43 us in complex128 (8 MiB), 2^20 amplitudes
-// 50 / 48 us in complex64 (8 MiB).
+// apply at k = 4: 2^18 amplitudes 11.2 / 25.7 us in complex64 and 19.5 / 33.8 us in complex128 (4 MiB), 2^19
+// amplitudes 21.5 / 29.8 us in complex64 (4 MiB) and 47 / 41 us in complex128 (8 MiB), 2^20 amplitudes
+// 50 / 42 us in complex64 (8 MiB).
 constexpr uint64_t kGatherBytes = 4ULL << 20;
 
 // bit rotations within L bits: layout rotation s stores qubit (b + s) mod L at index bit b
