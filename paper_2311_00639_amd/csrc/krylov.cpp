@@ -208,11 +208,15 @@ size_t krylov_workspace_bytes(uint64_t n, int m, size_t elem_bytes) {
 // The fused steps read v and the later basis vectors unnormalised, so that H u_j is formed at about c_max
 // times the norm of u_j, which is ||v|| for j = 0 and of the order of c_max else (sums over u_j and H u_j
 // at its third power).  Within these bounds on ||v|| and c_max nothing of that leaves the range
-// of T, nor the sums that of a double.
+// of T (2^18 terms of 2^20 on a vector of 2^80 stay below 2^118), nor the sums that of a double.  The vectors
+// grow in imaginary time: 2^80 leaves room for the chains of a correlator up to about beta = 45 at N = 56.
 template <typename T>
-static bool fused_range(double s) {
-    const int e = sizeof(T) == 4 ? 40 : 300;
-    return s >= std::ldexp(1.0, -e) && s <= std::ldexp(1.0, e);
+static bool fused_norm(double s) {
+    return sizeof(T) == 4 ? s >= 0x1p-40 && s <= 0x1p80 : s >= 0x1p-300 && s <= 0x1p300;
+}
+template <typename T>
+static bool fused_terms(double c_max) {
+    return sizeof(T) == 4 ? c_max >= 0x1p-40 && c_max <= 0x1p20 : c_max >= 0x1p-300 && c_max <= 0x1p300;
 }
 
 template <typename T>
@@ -234,7 +238,7 @@ KrylovRun<T>::KrylovRun(Hamiltonian &h, int blk, int rot, uint64_t n, int m, cha
     norms_ = fused_ + fused_partials(n);
     tiled_ = served_tiled<T>(h_, rot);
     big_ = n > kBigBlock && tiled_;
-    plain_ = !tiled_ && !fused_range<T>(h_.c_max);
+    plain_ = !tiled_ && !fused_terms<T>(h_.c_max);
     one_ = one_launch_steps<T>(h_);
     n_norm_ = static_cast<int>(std::min<uint64_t>(std::max<uint64_t>(n / 256, 1), big_ ? n / 256 : kNormParts));
 }
@@ -620,7 +624,7 @@ void KrylovRun<T>::run_fused(std::complex<double> z, const T *v, T *out, const s
                 n2[0] = host_.wait(host_.norm2(0), s_);
                 if (!std::isfinite(n2[0])) fail(SYK_ENUMERIC, "non-finite norm in Krylov propagation");
                 nrm = std::sqrt(n2[0]);
-                again = !staged && nrm > 0.0 && !fused_range<T>(nrm);
+                again = !staged && nrm > 0.0 && !fused_norm<T>(nrm);
                 if (again) break;
             }
             const int step = check - k;

@@ -34,21 +34,22 @@ def test_a_lone_item_is_cut_at_its_t_points(N, variant, ts):
 
 
 def test_short_of_memory_runs_with_fewer_slots():
-    """With about 1 GiB left, fewer slots than the item's parts (2.8 GB of vectors) serve them, with the same result."""
+    """With about 3 GiB left, fewer slots than one per CU (4.4 GB of vectors) serve an item's parts, with the same
+    result."""
     torch.cuda.set_device(0)
     item, ts = [(32, 2, 300, 31, 30, 900)], [0.02 * k for k in range(40)]
-    full = syk.otoc_batch(item, 0.5, ts, nvec=2, m=60)
-    assert full[3]["slots"] >= 150
+    full = syk.otoc_batch(item, 0.5, ts, nvec=4, m=60)
+    assert full[3]["slots"] >= 240
     syk.release_workspace()
     torch.cuda.empty_cache()
     free = torch.cuda.mem_get_info()[0]
-    hold = torch.empty(free - (1 << 30), dtype=torch.uint8, device="cuda")
+    hold = torch.empty(free - (3 << 30), dtype=torch.uint8, device="cuda")
     try:
-        few = syk.otoc_batch(item, 0.5, ts, nvec=2, m=60)
+        few = syk.otoc_batch(item, 0.5, ts, nvec=4, m=60)
     finally:
         del hold
         torch.cuda.empty_cache()
         syk.release_workspace()
-    assert 1 <= few[3]["slots"] < 100
+    assert 1 <= few[3]["slots"] < 240
     for a, b in zip(full[:3], few[:3]):
         assert np.array_equal(a, b)

@@ -91,7 +91,7 @@ def test_vectors_near_the_ends_of_the_range(N, k, dt):
                                syk.BERNOULLI if dense else syk.EXACT_K)
     n, z = 1 << (N // 2 - 1), -0.4 + 0.9j
     outs = {}
-    pairs = ((-112, -80), (110, 80)) if dt == syk.C64 else ((-480, -400), (480, 400))
+    pairs = ((-112, -80), (110, 90)) if dt == syk.C64 else ((-480, -400), (480, 400))
     for e in (0,) + pairs[0] + pairs[1]:
         x = _scaled(n, dt, e, N)
         out = torch.empty_like(x)
